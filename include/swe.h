@@ -105,22 +105,23 @@ typedef struct {
     double cfl;        /* default 0.45 */
     double eps;        /* wet/dry threshold [m], default 1e-6 */
     double dt_max;     /* cap on the CFL step (<= 0: none); step used when no cell is wet */
-    int block;         /* threads per block = cells per tile: 64, 128, 256 or 512 (0: 256,
-                          64 for FP32 WAF with explicit Euler on the tiled kernel);
-                          the one-thread-per-cell kernel, FP64 and WAF use at most 256
-                          (FP64 WAF tiles at most 128) */
+    int block;         /* cells per tile of the tiled kernels, threads per block of the
+                          one-thread-per-cell kernel: 64, 128, 256 or 512 (0: by size; 64 for
+                          FP32 WAF with explicit Euler on the tiled kernel); the
+                          one-thread-per-cell kernel, FP64 and WAF use at most 256
+                          (FP64 WAF tiles at most 128), and a mesh whose numbering has no
+                          locality gets smaller tiles */
     int cell_kernel;   /* 1: one-thread-per-cell stage kernel for every scheme; 0: the
                           tiled kernels (HLLC1, MUSCL, and WAF with Euler steps; WAF with
                           RK2 uses the cell kernel) */
     void *stream;      /* NULL: the context creates its own stream (default priority,
                           non-blocking); else a hipStream_t on `device`, borrowed: all of
                           the context's work goes to it and it is never destroyed */
-    int waves;         /* FP32 tiled kernel with 256-cell tiles (first-order HLLC and MUSCL
-                          with a classic limiter): waves per SIMD it is built for, 6 or 7;
-                          0 (default): 7 when that lets the chip hold every tile of a mesh
-                          of up to two rounds at once, or when a launch spans 8 or more
-                          rounds (then a persistent grid of 7 blocks per compute unit),
-                          else 6.  Same results either way. */
+    int waves;         /* FP32 MUSCL tiled kernel with 256-cell tiles and a classic limiter:
+                          register budget it is built for: 6: up to 72 registers (seven
+                          waves per SIMD), 7: up to 64 (eight); 0 (default): 64 when a
+                          launch spans 8 or more rounds of tiles (then a persistent grid of
+                          the blocks the chip holds), else 72.  Same results either way. */
     int phi_every;     /* SWE_LEARNED: phi is evaluated on the steps whose index since the
                           last set_state is a multiple of phi_every (1, 2, 3 or 6; 0: every
                           step), and on the first step after swe_limiter_set_weights or
@@ -231,11 +232,12 @@ int swe_scenario_times(swe_ctx *ctx, double *t);  /* [n_scenarios]; syncs */
 
 /* Autotuner: times n_steps CFL steps for each launch shape of the
  * configured stage kernel (64, 128, 256 or, FP32 tiled kernel only, 512
- * threads per block; one tile per block or a persistent grid of the blocks
- * the chip holds at once; with 256-cell FP32 tiles, builds for
- * 6 and 7 waves per SIMD) from the current state, keeps the fastest and
+ * cells per tile or threads per block; tiled kernel: a thread per cell or per
+ * edge of a tile; one tile per block or a persistent grid of the blocks
+ * the chip holds at once; with 256-cell FP32 tiles, both register budgets)
+ * from the current state, keeps the fastest and
  * restores the state, clocks and time.  The choice never changes results
- * (the tiled kernel is bitwise independent of the tiling, and both builds
+ * (the tiled kernel is bitwise independent of the tiling, and all builds
  * perform the same operations).
  * Outputs may be NULL; *persistent_grid is the chosen grid (-1: one tile per
  * block).  Untuned contexts sweep tiles with a persistent grid of the blocks

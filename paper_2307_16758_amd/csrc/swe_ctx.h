@@ -9,6 +9,17 @@
 #include "swe_internal.h"
 #include "swe_kernels.h"
 
+namespace swe {
+// Tile plan of one tile size (swe_plan.h): one allocation, arrays inside it
+// with strides of hs halo cells and es edges per tile.
+struct TilePlan {
+    int tile = 0;  // cells per tile; 0: not built
+    int hs = 0, es = 0, ntiles = 0;
+    void *mem = nullptr;
+    void *desc = nullptr, *halo = nullptr, *ent = nullptr, *nrm = nullptr, *wgt = nullptr, *gam = nullptr;
+};
+}  // namespace swe
+
 struct swe_ctx {
     swe_config cfg{};
     int dev = 0;
@@ -34,6 +45,7 @@ struct swe_ctx {
     int ncopy = 64;
     swe::ScenParams *scen = nullptr;
     double *ser_t = nullptr, *ser_q = nullptr, *t0 = nullptr;
+    swe::TilePlan plans[4];  // 64, 128, 256 and 512 cells per tile, built when first needed
     int *health = nullptr, *flag = nullptr, *send_idx = nullptr;
     int *pk_off = nullptr, *pk_ent = nullptr;  // send entries per send cell (CSR)
     // host mirrors
@@ -44,12 +56,13 @@ struct swe_ctx {
     // launch shape: threads per block and blocks of a persistent launch (0:
     // one tile per block); picked by swe_autotune when tuned
     int grid_persist = 0;
-    int waves = 0;  // tiled FP32 kernel, 256-cell tiles: 0 automatic, 6 or 7
+    int wide = -1;  // tiled kernel: a thread per edge (1) or per cell (0), -1 by size
+    int eight = -1; // tiled FP32 kernel, 256-cell tiles: eight waves per SIMD, -1 by size
     int ncu = 0;    // compute units of the device
     bool tuned = false;
     double computed_inflow_len = 0.0, given_inflow_len = 0.0;
     long long step_count = 0;  // steps since set_state (selects clock slots and buffers)
-    int block = 256;
+    int block = 0;  // cells per tile or threads per block; 0: by size
     // graphs: chunk of kGraphSteps steps starting at a step index multiple of it
     hipGraphExec_t graph = nullptr;
     double graph_dt = -1.0;

@@ -25,6 +25,7 @@
 #include "swe_mlp_dev.h"
 #include "swe_internal.h"
 #include "swe_kernels.h"
+#include "swe_plan.h"
 
 using namespace swe;
 
@@ -189,7 +190,7 @@ __device__ __forceinline__ DtPrefetch dt_prefetch(const ClockWord *clk, int ncop
     p.S = act ? lane_value(s_own, __builtin_ctzll(act)) : 0;
     p.mn = 0.0;
     p.mx = 0.0;
-    if (dt_fixed <= 0.0) {
+    if (dt_fixed <= 0.0 && act != 0ull) {
         const ClockWord *q = clk + clock_off(ncopy, p.S, slot) +
                              (size_t)(1 + ((int)threadIdx.x & (ncopy - 1))) * kClockLine;
         p.mn = bitsd(q[kCfqMin]);
@@ -333,6 +334,15 @@ template <typename T> struct StageArgs {
     const typename V2<T>::type *he_nrm;  // tiled WAF: unit normal per half-edge (edge-major)
     const T4 *Uin, *U0;
     T4 *Uout;
+    // tile plan of the tiled kernels (see PlanView)
+    const int4 *tdesc;
+    const int *thalo;
+    const uint2 *tent;
+    const typename V2<T>::type *tnrm;
+    const T4 *twgt;
+    const typename V2<T>::type *tgam;
+    int hs, es, ntiles;
+    int n_owned;
     ClockWord *clock;
     int ncopy;                   // CFL partial copies per clock slot (power of two <= 64)
     const ScenParams *scen;
@@ -356,6 +366,18 @@ template <typename T> struct StageArgs {
     T *pk_buf;
     int pk_ncell, pk_nsend;
 };
+
+// The kernel's argument (the only one) read again from the kernel-argument
+// segment: what a later part of a kernel needs is then not held in scalar
+// registers from its start (with all of it the tiled kernel spilled 60 of
+// them to vector registers).
+template <typename T> __device__ __forceinline__ const StageArgs<T> &args_again()
+{
+    typedef const __attribute__((address_space(4))) StageArgs<T> ConstArgs;
+    ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));  // an unknown pointer: nothing loaded before counts
+    return *(const StageArgs<T> *)p;
+}
 
 // Fused pack: the thread that has just computed send cell c's new state
 // writes it to every send entry of c (bitwise the stored state).
@@ -686,396 +708,317 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<T> a)
 
 // ------------------------------------------------------------------------
 // Tiled stage kernel (first-order HLLC and MUSCL-HLLC).  A block owns one
-// tile of TILE consecutive (Morton-ordered) cells:
-//  1. every thread forms the primitive values of its cell and its 1-ring,
-//     reconstructs its interior half-edges into LDS (with the centred bed
-//     term of each), and files its edges as tasks: an edge to a cell of the
-//     same tile is filed once, by the cell that is the L side of the
-//     canonical orientation; an edge to a cell outside the tile is filed by
-//     each side;
-//  2. the block sweeps both task lists as one dense range (outside edges
-//     first: they also reconstruct the far side from its 2-ring; then inside
-//     edges, whose far side is already in LDS): hydrostatic reconstruction,
-//     HLLC in the canonical orientation, side corrections; each half-edge's
-//     share replaces its interface values in LDS (a slot is read and written
-//     by one task only);
+// tile of TILE consecutive (Morton-ordered) cells and works from the tile
+// plan (swe_plan.h):
+//  1. the primitive values of the tile's cells and of its halo go to LDS,
+//     each cell once;
+//  2. one thread per edge, in canonical orientation: both sides'
+//     reconstructions, hydrostatic reconstruction, one HLLC, both cells'
+//     shares (with side correction and centred bed term) into LDS;
 //  3. every thread sums its three half-edge shares weighted by L / area,
 //     updates, applies Manning and the cleanup, and the block commits its
 //     CFL quantities.
-// Boundary half-edges are tasks of the first list too (their flux needs
-// only the cell's own state).
-// The flux of an edge is the same function of the same operands wherever it
-// is evaluated (operands selected, one evaluation, multiply-adds fused per
-// expression only), so results do not depend on the tiling (sub-domain runs
-// stay bitwise equal to undecomposed runs) and mass contributions cancel
-// bitwise.  Momentum is summed in pressure-deviation form: every share of a
-// cell is taken less the cell's own hydrostatic pressure g h^2 / 2 along its
-// normal, which changes nothing exactly (the outward normals of a triangle
-// times its edge lengths sum to zero) but makes a lake at rest exactly at
-// rest in floating point and removes the rounding of the large cancelling
-// pressure terms (Sec. 6.2.3's side corrections and centred bed term become
+// The flux of an edge is the same function of the same operands in whichever
+// tile it is evaluated (multiply-adds fused per expression only), so results
+// do not depend on the tiling (sub-domain runs stay bitwise equal to
+// undecomposed runs) and mass contributions cancel bitwise.  Momentum is
+// summed in pressure-deviation form: every share of a cell is taken less the
+// cell's own hydrostatic pressure g h^2 / 2 along its normal, which changes
+// nothing exactly (the outward normals of a triangle times its edge lengths
+// sum to zero) but makes a lake at rest exactly at rest in floating point and
+// removes the rounding of the large cancelling pressure terms (Sec. 6.2.3's
+// side corrections and centred bed term become
 // g (h- + h)(eta- - eta) / 2; hllc_dev gives F1 - g h*^2 / 2 per side).
-// LDS per cell: 3 x (4 + 1) values, 3 task slots, 3 neighbour indices and
-// the word (22.5 KB per 256-cell FP32 tile, seven tiles per CU); phase 2
-// reads no global memory for edges inside the tile but the normal.  Half-edge
-// slots are local-edge-major (slot of cell l, edge m at m * TILE + l), so a
-// wave's per-cell accesses are consecutive.
 // Learned limiter in the step's first stage: the tiled instance that also
 // evaluates the network and stores phi (the second stage reads it)
 constexpr int kLearnedNet = 5;
 #ifndef SWE_TILED_WAVES
-#define SWE_TILED_WAVES 6  // FP32: waves per SIMD the register budget is sized for
+#define SWE_TILED_WAVES 7  // FP32: waves per SIMD the register budget is sized for
 #endif
 #ifndef SWE_TILED_WAVES_LEARNED
-#define SWE_TILED_WAVES_LEARNED 5  // the learned-limiter instance needs 96 registers
+#define SWE_TILED_WAVES_LEARNED 5
 #endif
 #ifndef SWE_TILED_WAVES_NET
-#define SWE_TILED_WAVES_NET 4  // the instance that also evaluates the network (128 registers)
+#define SWE_TILED_WAVES_NET 4  // the instance that also evaluates the network
 #endif
-template <typename T, bool MUSCL_, int LIM, int TILE, int OCC = SWE_TILED_WAVES>
-__global__ void __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(
+
+// Threads of a tile: one per cell, or ("wide") one per edge, about 1.75 per
+// cell.  With one per cell two sweeps take the 421 edges of 256 cells; one
+// per edge shortens the tile's chain of latencies (edges and halo in one
+// sweep, the update's operands loaded up front) at the price of waves that
+// only wait in the update.
+constexpr int tile_threads(int tile, bool wide)
+{
+    return !wide || tile == 512 ? tile : (tile == 64 ? 128 : (tile == 128 ? 256 : 448));
+}
+
+// Bytes of dynamic LDS of a tiled launch: the slots' primitive values (and,
+// where the network is evaluated, their states and its input rows; with the
+// learned limiter the halo's cells) and the shares of 3 half-edges per cell.
+template <typename T> size_t tiled_lds(int tile, int hs, bool learned, bool net)
+{
+    const size_t slots = (size_t)(tile + hs);
+    return 4 * sizeof(T) * slots * (net ? 2 : 1) + 9 * sizeof(T) * (size_t)tile +
+           (learned ? sizeof(int) * (((size_t)hs + 3) & ~(size_t)3) : 0) + (net ? 32 * (size_t)tile_threads(tile, true) : 0);
+}
+
+// Entry words of a tile: first-order fluxes need the first one only.
+template <bool TWO> __device__ __forceinline__ uint2 load_entry(const uint2 *e, unsigned i)
+{
+    if constexpr (TWO) return ldx(e, i);
+    return make_uint2(ldx(reinterpret_cast<const unsigned *>(e), 2 * i), 0u);
+}
+
+template <typename T, bool MUSCL_, int LIM, int TILE, int NT, int OCC = SWE_TILED_WAVES>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 ? (LIM == kLearned ? SWE_TILED_WAVES_LEARNED
                                       : (LIM == kLearnedNet ? SWE_TILED_WAVES_NET : OCC))
                    : 2)))
-k_stage_tiled(StageArgs<T> a)
+k_stage_tiled(StageArgs<T> args)
 {
     using T4 = typename V4<T>::type;
-    static_assert(TILE <= 1024, "10-bit tile-local indices in task entries");
-    __shared__ T4 sR[3 * TILE];
-    __shared__ T sB[3 * TILE];
-    // tasks: outside-tile and boundary half-edges from the front, inside
-    // edges from the back; an entry packs m (2 bits), the filing cell (10),
-    // the neighbour's local edge jb (2), the L-side bit and, inside the
-    // tile, the neighbour's tile-local index (10)
-    __shared__ unsigned sTask[3 * TILE];
-    __shared__ int sK[3 * TILE];       // neighbour (or boundary tag) of each half-edge
-    __shared__ unsigned sW[TILE];      // packed word of each cell
-    __shared__ int sCount[2];
-    __shared__ CflVal<T> sCfl[TILE / 64];
-    // learned limiter: kNet evaluates phi (input rows of the network in LDS,
-    // 64 per wave), kLrn reads it; RL is the limiter of the reconstruction
+    using T2 = typename V2<T>::type;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr bool kWide = NT > TILE;
+    __shared__ CflVal<T> sCfl[NT / 64];
+    // learned limiter: kNet evaluates phi, kLrn reads it; RL is the limiter
+    // of the reconstruction
     constexpr bool kNet = MUSCL_ && LIM == kLearnedNet;
     constexpr bool kLrn = MUSCL_ && (LIM == kLearned || LIM == kLearnedNet);
     constexpr int RL = LIM == kLearnedNet ? kLearned : LIM;
-    __shared__ __align__(16) uint16_t sX[kNet ? TILE : 1][16];
-    clock_upkeep(a);
-    const T g = a.g, eps = a.eps;
-    const int ntiles = (a.n + TILE - 1) / TILE;
-    for (int tile = xcd_tile(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
-        const int c0 = tile * TILE, cl = threadIdx.x, c = c0 + cl;
-        const bool active = c < a.n;
-        if (threadIdx.x < 2) sCount[threadIdx.x] = 0;
-        __syncthreads();
-        // a tile's first phase issues its chains of dependent loads (the
-        // neighbour quads, then the stencil): waves in it go first, ahead
-        // of waves sweeping edges or updating (measured: 1.8% on the
-        // 13M-cell river, 2.2% with the update's priority below, even on
-        // config 2; the WAF kernel gains nothing)
-        __builtin_amdgcn_s_setprio(3);
-        // ---- 1: primitives, own half-edges, task lists
-        DtPrefetch dtp;
-        int4 nb4 = make_int4(-1, -1, -1, 0);
-        if (active) nb4 = ldx(a.nbr, c);
-        dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur, active ? (int)((unsigned)nb4.w >> kScenShift) : -1,
-                          a.dt_fixed);
-        T4 Ukeep;  // the cell's state, kept for phase 3
-        if constexpr (kLrn) {
-            // phi of the cell's three half-edges: in the step's first stage
-            // from the network on U^n (the wave evaluates its 64 half-edges
-            // of one local edge at a time) and stored for the second, else
-            // the stored values
-            const bool hn0 = active && nb4.x >= 0, hn1 = active && nb4.y >= 0, hn2 = active && nb4.z >= 0;
-            float ph[3] = {0.0f, 0.0f, 0.0f};
-            if constexpr (kNet) {
-                T4 Uc{}, Un0{}, Un1{}, Un2{}, co0{}, co1{}, co2{};
-                if (active) {
-                    Uc = ldx(a.Uin, c);
-                    Un0 = ldx(a.Uin, hn0 ? nb4.x : c);
-                    Un1 = ldx(a.Uin, hn1 ? nb4.y : c);
-                    Un2 = ldx(a.Uin, hn2 ? nb4.z : c);
-                    co0 = ldx(a.he_co, c);
-                    co1 = ldx(a.he_co, a.n + c);
-                    co2 = ldx(a.he_co, 2 * a.n + c);
-                }
-                const int lane = threadIdx.x & 63;
-                uint16_t(*X)[16] = sX + (threadIdx.x & ~63);
-#pragma unroll
-                for (int m = 0; m < 3; ++m) {
-                    const int ma = (m + 1) % 3, mb = (m + 2) % 3;
-                    const T4 Um = m == 0 ? Un0 : (m == 1 ? Un1 : Un2);
-                    const T4 Ua = ma == 0 ? Un0 : (ma == 1 ? Un1 : Un2);
-                    const T4 Ub = mb == 0 ? Un0 : (mb == 1 ? Un1 : Un2);
-                    const bool hm = m == 0 ? hn0 : (m == 1 ? hn1 : hn2);
-                    const bool ha = ma == 0 ? hn0 : (ma == 1 ? hn1 : hn2);
-                    const bool hb = mb == 0 ? hn0 : (mb == 1 ? hn1 : hn2);
-                    const T4 co = m == 0 ? co0 : (m == 1 ? co1 : co2);
-                    float f[kMlpIn];
-                    const bool ok = limiter_features<T, T4>(Uc, Um, hm, Ua, ha, Ub, hb, co.x, co.y,
-                                                            co.z, co.w, g, eps, f);
-                    mlp_write_row(X[lane], f, ok);
-                    wave_lds_sync();
-                    // the weights are loaded where they are used (L1 hits), so
-                    // that they do not hold registers across the features
-                    const MlpLane L = mlp_lane(a.mlp, lane);
-                    ph[m] = mlp_phi(mlp_rows_z(L, X, lane), ok);
-                    wave_lds_sync();  // the rows are rewritten for the next edge
-                    if (active) a.phi[3 * c + m] = ph[m];
-                }
-            } else if (active) {
-#pragma unroll
-                for (int m = 0; m < 3; ++m) ph[m] = ldx(a.phi, 3 * c + m);
-            }
-            T4 Uc{}, Un0{}, Un1{}, Un2{}, co0{}, co1{}, co2{};
-            if (active) {
-                Uc = ldx(a.Uin, c);
-                Un0 = ldx(a.Uin, hn0 ? nb4.x : c);
-                Un1 = ldx(a.Uin, hn1 ? nb4.y : c);
-                Un2 = ldx(a.Uin, hn2 ? nb4.z : c);
-                co0 = ldx(a.he_co, c);
-                co1 = ldx(a.he_co, a.n + c);
-                co2 = ldx(a.he_co, 2 * a.n + c);
-            }
-            if (active) {
-                Ukeep = Uc;
-                const unsigned word = (unsigned)nb4.w;
-                sW[cl] = word;
-                const Prim<T> pc = prim(Uc, eps);
-                // a missing neighbour's slot holds the cell's own state
-                const Prim<T> pn[3] = {prim(Un0, eps), prim(Un1, eps), prim(Un2, eps)};
-                const bool hn[3] = {hn0, hn1, hn2};
-                const int nb[3] = {nb4.x, nb4.y, nb4.z};
-#pragma unroll
-                for (int m = 0; m < 3; ++m) {
-                    const int k = nb[m];
-                    sK[m * TILE + cl] = k;
-                    const unsigned jb = (word >> (2 * m)) & 3u, isL = (word >> (6 + m)) & 1u;
-                    const unsigned ent = (unsigned)m | ((unsigned)cl << 2) | (jb << 12) | (isL << 14);
-                    if (k < 0) {  // boundary half-edge: a task of its own
-                        sTask[atomicAdd(&sCount[0], 1)] = ent;
-                        continue;
-                    }
-                    const T4 co = m == 0 ? co0 : (m == 1 ? co1 : co2);
-                    const T ga = ldx(a.he_gam, m * a.n + c);
-                    const int ma = (m + 1) % 3, mb = (m + 2) % 3;
-                    const Half<T> r = recon3<T, MUSCL_, RL>(pc, pn[m], pn[ma], hn[ma], pn[mb], hn[mb],
-                                                             co.x, co.y, co.z, co.w, ga, ph[m], eps);
-                    T4 rv;
-                    rv.x = r.h; rv.y = r.b; rv.z = r.un; rv.w = r.ut;
-                    sR[m * TILE + cl] = rv;
-                    sB[m * TILE + cl] = T(0.5) * g * (r.h + Uc.x) * (r.eta - (pc.h + pc.b));
-                    const int kl = k - c0;
-                    if (kl >= 0 && kl < TILE) {
-                        if (isL) sTask[3 * TILE - 1 - atomicAdd(&sCount[1], 1)] = ent | ((unsigned)kl << 15);
-                    } else {
-                        sTask[atomicAdd(&sCount[0], 1)] = ent;
-                    }
-                }
-            }
-        } else if (active) {
-            const T4 Uc = ldx(a.Uin, c);
-            Ukeep = Uc;
-            const int nb[3] = {nb4.x, nb4.y, nb4.z};
-            const unsigned word = (unsigned)nb4.w;
-            sW[cl] = word;
-            const Prim<T> pc = prim(Uc, eps);
-            Prim<T> pn[3];
-            bool hn[3];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                hn[m] = nb[m] >= 0;
-                pn[m] = hn[m] ? prim(a.Uin[nb[m]], eps) : pc;
-            }
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int k = nb[m];
-                sK[m * TILE + cl] = k;
-                const unsigned jb = (word >> (2 * m)) & 3u, isL = (word >> (6 + m)) & 1u;
-                const unsigned ent = (unsigned)m | ((unsigned)cl << 2) | (jb << 12) | (isL << 14);
-                if (k < 0) {  // boundary half-edge: a task of its own
-                    sTask[atomicAdd(&sCount[0], 1)] = ent;
-                    continue;
-                }
-                const T4 co = ldx(a.he_co, m * a.n + c);
-                const int ma = (m + 1) % 3, mb = (m + 2) % 3;
-                const Half<T> r = recon3<T, MUSCL_, LIM>(pc, pn[m], pn[ma], hn[ma], pn[mb], hn[mb],
-                                                          co.x, co.y, co.z, co.w, T(0), 0.0f, eps);
-                T4 rv;
-                rv.x = r.h; rv.y = r.b; rv.z = r.un; rv.w = r.ut;
-                sR[m * TILE + cl] = rv;
-                // side correction and centred bed term less the cell's
-                // hydrostatic pressure: g (h- + h)(eta- - eta) / 2 along n
-                sB[m * TILE + cl] = T(0.5) * g * (r.h + Uc.x) * (r.eta - (pc.h + pc.b));
-                const int kl = k - c0;
-                if (kl >= 0 && kl < TILE) {
-                    if (isL) sTask[3 * TILE - 1 - atomicAdd(&sCount[1], 1)] = ent | ((unsigned)kl << 15);
-                } else {
-                    sTask[atomicAdd(&sCount[0], 1)] = ent;
-                }
-            }
+    T4 *const sP = reinterpret_cast<T4 *>(smem);          // h, b, u, v per slot
+    const int hs = args.hs;
+    T *const sF = reinterpret_cast<T *>(sP + TILE + hs);  // shares: component f of half-edge m, cell l at (3 f + m) TILE + l
+    int *const sId = reinterpret_cast<int *>(sF + 9 * TILE);  // learned: the halo's cells
+    T4 *const sU = reinterpret_cast<T4 *>(sId + ((hs + 3) & ~3));  // network: h, hu, hv, b per slot
+    uint16_t(*const sX)[16] = reinterpret_cast<uint16_t(*)[16]>(sU + TILE + hs);
+    clock_upkeep(args_again<T>());
+    const T g = args.g, eps = args.eps;
+    const int ntiles = args.ntiles;
+    for (int tv = xcd_tile(blockIdx.x, gridDim.x); tv < ntiles; tv += gridDim.x) {
+        const int tile = __builtin_amdgcn_readfirstlane(tv);  // uniform: scalar bases
+        const int cl = threadIdx.x;
+        const StageArgs<T> &a = args_again<T>();
+        // ---- 1: states into LDS; the first round of edge data is on its way
+        // before they arrive
+        const int *halo = a.thalo + (size_t)tile * a.hs;
+        const uint2 *const ent = a.tent + (size_t)tile * a.es;
+        const T2 *nrm = a.tnrm + (size_t)tile * a.es;
+        const T4 *wgt = a.twgt + (size_t)tile * a.es;
+        const T2 *gam = a.tgam + (size_t)tile * a.es;
+        const int4 d = a.tdesc[tile];
+        // wide: the threads after the cells' take the halo, else each thread
+        // takes a cell and then a halo cell
+        const int hj = kWide ? cl - TILE : cl;
+        int hid = -1;
+        if (hj >= 0 && hj < a.hs) hid = ldx(halo, hj);
+        uint2 en = make_uint2(0u, 0u);
+        T2 nn{};
+        T4 ww{};
+        if (cl < a.es) {
+            en = load_entry<MUSCL_>(ent, cl);
+            nn = ldx(nrm, cl);
+            if (MUSCL_) ww = ldx(wgt, cl);
         }
-        __builtin_amdgcn_s_setprio(0);
+        const int c0 = d.x, c = c0 + cl, nt = d.w & 0xffff;
+        const bool active = cl < d.y;
+        int s = -1;
+        if (active) s = a.n_scen == 1 ? 0 : d.z;
+        if (a.n_scen > 1 && d.z < 0 && active) s = (int)((unsigned)a.nbr[c].w >> kScenShift);
+        const DtPrefetch dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur, s, a.dt_fixed);
+        const auto put = [&](int slot, const T4 &U) {
+            const Prim<T> p = prim(U, eps);
+            T4 v;
+            v.x = p.h; v.y = p.b; v.z = p.u; v.w = p.v;
+            sP[slot] = v;
+            if constexpr (kNet) sU[slot] = U;
+        };
+        T4 Uc{};
+        if (active) Uc = ldx(a.Uin, c);
+        if constexpr (kWide) {
+            if (hid >= 0) Uc = ldx(a.Uin, hid);
+            if (active || hid >= 0) put(cl, Uc);
+        } else {
+            if (active) put(cl, Uc);
+            if (hid >= 0) put(TILE + cl, ldx(a.Uin, hid));
+        }
+        if constexpr (kLrn) {
+            if (hid >= 0) sId[hj] = hid;
+        }
+        for (int j = hj + NT; j < a.hs; j += NT) {
+            hid = ldx(halo, j);
+            if (hid < 0) break;
+            put(TILE + j, ldx(a.Uin, hid));
+            if constexpr (kLrn) sId[j] = hid;
+        }
+        // the update's operands (not wide: loaded there, they would cost
+        // registers: 4% on a million cells)
+        T lam0 = T(0), lam1 = T(0), lam2 = T(0), man2 = T(0);
+        if (kWide && active) {
+            lam0 = ldx(a.he_lam, c);
+            lam1 = ldx(a.he_lam, a.n + c);
+            lam2 = ldx(a.he_lam, 2 * a.n + c);
+            man2 = ldx(a.man2, c);
+        }
+        // the step: one value for the tile but where it holds several scenarios
+        double dtd = 0.0;
+        if (a.n_scen == 1 || d.z >= 0) {
+            const StageArgs<T> &a = args_again<T>();
+            dtd = lane_value(dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max,
+                                       a.dt_fixed), 0);
+        }
         __syncthreads();
-        // ---- 2: edge tasks, one dense sweep (outside-tile edges first)
-        {
-            const int n0 = sCount[0], nt = n0 + sCount[1];
-            // learned limiter: every thread runs the same number of sweeps,
-            // so that a wave evaluates the network as a whole
-            const int iend = kNet ? (nt + TILE - 1) / TILE * TILE : nt;
-            for (int i = threadIdx.x; i < iend; i += TILE) {
-                float phin = 0.0f;  // learned, first stage: phi of an outside edge's far side
+        // ---- 2: edges
+        const int iend = kNet ? (nt + 63) & ~63 : nt;  // the network is evaluated by whole waves
+        for (int i = cl; i < iend; i += NT) {
+            if (i >= NT) {
+                en = load_entry<MUSCL_>(ent, i);
+                nn = ldx(nrm, i);
+                if (MUSCL_) ww = ldx(wgt, i);
+            }
+            const uint2 e = en;
+            const T nx = nn.x, ny = nn.y;
+            const T4 w = ww;
+            const int iL = e.x & 1023u, iR = (e.x >> 10) & 1023u, mL = (e.x >> 20) & 3u,
+                      mR = (e.x >> 22) & 3u;
+            const int iLa = e.y & 1023u, iLb = (e.y >> 10) & 1023u, iRa = (e.y >> 20) & 1023u,
+                      iRb = (e.y >> 30 << 8) | (e.x >> 24);
+            float phL = 0.0f, phR = 0.0f;
+            if constexpr (kLrn) {
+                const bool edge = i < nt;
+                const auto cell = [&](int slot) { return slot < TILE ? c0 + slot : sId[slot - TILE]; };
                 if constexpr (kNet) {
-                    if (i - (int)threadIdx.x < n0) {
-                        // the far side's own half-edge, from its 1-ring of U^n
-                        // (the tile that owns it evaluates the same bits)
-                        T4 Uk{}, Ut{}, Ua{}, Ub{}, ck{};
-                        bool hk = false, ha = false, hb = false;
-                        if (i < n0) {
-                            const unsigned task = sTask[i];
-                            const int m = task & 3u, tl = (task >> 2) & 1023u, jb = (task >> 12) & 3u;
-                            const int k = sK[m * TILE + tl];
-                            if (k >= 0) {
-                                const int4 nk = ldx(a.nbr, k);
-                                const int ka = pick3(nk, (jb + 1) % 3), kb = pick3(nk, (jb + 2) % 3);
-                                hk = true;
-                                ha = ka >= 0;
-                                hb = kb >= 0;
-                                Uk = ldx(a.Uin, k);
-                                Ut = ldx(a.Uin, c0 + tl);
-                                Ua = ldx(a.Uin, ha ? ka : k);
-                                Ub = ldx(a.Uin, hb ? kb : k);
-                                ck = ldx(a.he_co, jb * a.n + k);
-                            }
-                        }
+                    // the wave evaluates its 64 L sides, then its 64 R sides
+                    // (a tile on the other side of an edge evaluates the same
+                    // bits); a cell's own tile stores its phi
+                    const int lane = threadIdx.x & 63;
+                    uint16_t(*X)[16] = sX + (threadIdx.x & ~63);
+#pragma unroll 1
+                    for (int side = 0; side < 2; ++side) {
+                        const int ic = side ? iR : iL, ik = side ? iL : iR, ia = side ? iRa : iLa,
+                                  ib = side ? iRb : iLb;
                         float f[kMlpIn];
-                        const bool ok = limiter_features<T, T4>(Uk, Ut, hk, Ua, ha, Ub, hb, ck.x, ck.y,
-                                                                ck.z, ck.w, g, eps, f);
-                        const int lane = threadIdx.x & 63;
-                        uint16_t(*X)[16] = sX + (threadIdx.x & ~63);
-                        const MlpLane L = mlp_lane(a.mlp, lane);
+                        T4 Us{}, Uk{}, Ua{}, Ub{};
+                        bool hu = false;
+                        if (edge) {
+                            Us = sU[ic]; Uk = sU[ik]; Ua = sU[ia]; Ub = sU[ib];
+                            hu = ia != ic;
+                        }
+                        // a missing upwind cell's place holds the other one:
+                        // their mean is that one
+                        const bool ok = limiter_features<T, T4>(Us, Uk, edge, Ua, hu, Ub, hu, side ? -nx : nx,
+                                                                side ? -ny : ny, side ? w.z : w.x,
+                                                                side ? w.w : w.y, g, eps, f);
                         mlp_write_row(X[lane], f, ok);
                         wave_lds_sync();
-                        phin = mlp_phi(mlp_rows_z(L, X, lane), ok);
-                        wave_lds_sync();
+                        const MlpLane L = mlp_lane(a.mlp, lane);
+                        const float ph = mlp_phi(mlp_rows_z(L, X, lane), ok);
+                        wave_lds_sync();  // the rows are rewritten next
+                        if (side) phR = ph;
+                        else phL = ph;
+                        if (edge && ic < TILE) a.phi[3 * (c0 + ic) + (side ? mR : mL)] = ph;
                     }
-                    if (i >= nt) continue;
+                } else if (edge) {
+                    phL = ldx(a.phi, 3 * cell(iL) + mL);
+                    phR = ldx(a.phi, 3 * cell(iR) + mR);
                 }
-                const bool inside = i >= n0;
-                const unsigned task = inside ? sTask[3 * TILE - 1 - (i - n0)] : sTask[i];
-                const int m = task & 3u, tl = (task >> 2) & 1023u, jb = (task >> 12) & 3u;
-                const bool isL = (task >> 14) & 1u;
-                const int kl = inside ? (int)((task >> 15) & 1023u) : -1;
-                const int tc = c0 + tl;
-                const int k = inside ? c0 + kl : sK[m * TILE + tl];
-                const T4 co = ldx(a.he_co, m * a.n + tc);
-                const T nx = co.x, ny = co.y;
-                if (k < 0) {  // boundary flux (Sec. 6.1), in the global frame
-                    const T4 Ut = ldx(a.Uin, tc);
-                    const int st = (int)(sW[tl] >> kScenShift);
-                    const ScenParams sp = a.scen[st];
-                    T q_in = T(0);
-                    if (k == kBcInflow) {
-                        const double t_st =
-                            bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)]) +
-                            (a.kind == 2 ? lane_step_dt(a.clock, a.ncopy, a.slot_cur, st, a.cfl_rule,
-                                                        a.cfl, a.dt_max, a.dt_fixed)
-                                         : 0.0);
-                        q_in = T(inflow_at(sp, a.ser_t, a.ser_q, t_st) * sp.inv_inflow_len);
-                    }
-                    T G[3];
-                    boundary_flux_dev<T, T4>(k, Ut, nx, ny, g, eps, q_in, T(sp.outflow_stage), G);
-                    T4 fb;
-                    fb.x = G[0]; fb.y = G[1]; fb.z = G[2]; fb.w = T(0);
-                    sR[m * TILE + tl] = fb;
-                    continue;
-                }
-                const T4 ov = sR[m * TILE + tl];
-                const T sbo = sB[m * TILE + tl];
-                T4 kv;
-                T sbk = T(0);
-                if (inside) {
-                    kv = sR[jb * TILE + kl];
-                    sbk = sB[jb * TILE + kl];
-                } else {
-                    // far side: its own reconstruction across this edge, from its 2-ring
-                    const Prim<T> pk = prim(ldx(a.Uin, k), eps);
-                    const Prim<T> pc = prim(ldx(a.Uin, tc), eps);
-                    Prim<T> pka = pk, pkb = pk;
-                    bool hka = false, hkb = false;
-                    T al = T(0), be = T(0), ga = T(0);
-                    float phik = 0.0f;
-                    if (MUSCL_) {
-                        const int4 nk = ldx(a.nbr, k);
-                        const int ka = pick3(nk, (jb + 1) % 3), kb = pick3(nk, (jb + 2) % 3);
-                        hka = ka >= 0;
-                        hkb = kb >= 0;
-                        if (hka) pka = prim(ldx(a.Uin, ka), eps);
-                        if (hkb) pkb = prim(ldx(a.Uin, kb), eps);
-                        const T4 ck = ldx(a.he_co, jb * a.n + k);
-                        al = ck.z;
-                        be = ck.w;
-                        if (RL == kLearned) {
-                            ga = ldx(a.he_gam, jb * a.n + k);
-                            phik = kNet ? phin : ldx(a.phi, 3 * k + jb);
-                        }
-                    }
-                    const Half<T> r = recon3<T, MUSCL_, RL>(pk, pc, pka, hka, pkb, hkb, -nx, -ny, al,
-                                                              be, ga, phik, eps);
-                    kv.x = r.h; kv.y = r.b; kv.z = r.un; kv.w = r.ut;
-                }
-                // hydrostatic reconstruction
-                const T bmax = tmax(ov.y, kv.y);
-                const T hso = tmax(T(0), ov.x + ov.y - bmax);
-                const T hsk = tmax(T(0), kv.x + kv.y - bmax);
-                // HLLC in the canonical orientation: operands selected, one
-                // evaluation, whichever side files the edge
-                const T hL = isL ? hso : hsk, uL = isL ? ov.z : kv.z, vL = isL ? ov.w : kv.w;
-                const T hR = isL ? hsk : hso, uR = isL ? -kv.z : -ov.z, vR = isL ? -kv.w : -ov.w;
-                const T nLx = isL ? nx : -nx, nLy = isL ? ny : -ny;
-                T F0, DL, DR, F2;
-                hllc_dev(g, eps, hL, uL, vL, hR, uR, vR, F0, DL, DR, F2);
-                const T sg = isL ? T(1) : T(-1);
-                // each side's normal momentum flux less its own hydrostatic
-                // pressure, rotated back from the canonical frame
-                const T Do = isL ? DL : DR;
-                T4 fo;
-                half_edge_flux(sg, F0, Do * nLx - F2 * nLy, Do * nLy + F2 * nLx, sbo, nx, ny, fo.x,
-                               fo.y, fo.z);
-                fo.w = T(0);
-                sR[m * TILE + tl] = fo;
-                if (inside) {  // the other cell's half-edge: normal -n, sign -sg
-                    const T Dk = isL ? DR : DL;
-                    T4 fk;
-                    half_edge_flux(-sg, F0, Dk * nLx - F2 * nLy, Dk * nLy + F2 * nLx, sbk, -nx, -ny,
-                                   fk.x, fk.y, fk.z);
-                    fk.w = T(0);
-                    sR[jb * TILE + kl] = fk;
-                }
+                if (i >= nt) continue;
+            }
+            const T4 L = sP[iL];
+            const T4 R = sP[iR];
+            // both sides' values in L's frame (a limiter is odd in its two
+            // slopes, so R's reconstruction in its own opposite frame is the
+            // same but for the signs)
+            const T qL[4] = {L.x, L.x + L.y, L.z * nx + L.w * ny, -L.z * ny + L.w * nx};
+            const T qR[4] = {R.x, R.x + R.y, R.z * nx + R.w * ny, -R.z * ny + R.w * nx};
+            Half<T> hL, hR;
+            hL.h = qL[0]; hL.b = L.y; hL.un = qL[2]; hL.ut = qL[3]; hL.eta = qL[1];
+            hR.h = qR[0]; hR.b = R.y; hR.un = qR[2]; hR.ut = qR[3]; hR.eta = qR[1];
+            if (MUSCL_) {
+                T gL = T(0), gR = T(0);
+                if (RL == kLearned) { const T2 gg = ldx(gam, i); gL = gg.x; gR = gg.y; }
+                const bool wet = L.x > eps && R.x > eps;
+                recon_side<T, RL>(hL, qL, qR, sP[iLa], sP[iLb], wet, nx, ny, w.x, w.y, gL, phL, eps);
+                __builtin_amdgcn_sched_barrier(0);  // R's upwind states after L's side: fewer registers
+                recon_side<T, RL>(hR, qR, qL, sP[iRa], sP[iRb], wet, nx, ny, w.z, w.w, gR, phR, eps);
+            }
+            // side correction and centred bed term less the cell's
+            // hydrostatic pressure: g (h- + h)(eta- - eta) / 2 along n
+            const T sbL = T(0.5) * g * (hL.h + L.x) * (hL.eta - (L.x + L.y));
+            const T sbR = T(0.5) * g * (hR.h + R.x) * (hR.eta - (R.x + R.y));
+            // hydrostatic reconstruction
+            const T bmax = tmax(hL.b, hR.b);
+            const T hsL = tmax(T(0), hL.h + hL.b - bmax);
+            const T hsR = tmax(T(0), hR.h + hR.b - bmax);
+            T F0, DL, DR, F2;
+            hllc_dev(g, eps, hsL, hL.un, hL.ut, hsR, hR.un, hR.ut, F0, DL, DR, F2);
+            // each side's normal momentum flux less its own hydrostatic
+            // pressure, rotated back from the canonical frame
+            if (iL < TILE) {
+                T f0, f1, f2;
+                half_edge_flux(T(1), F0, DL * nx - F2 * ny, DL * ny + F2 * nx, sbL, nx, ny, f0, f1, f2);
+                sF[mL * TILE + iL] = f0;
+                sF[(3 + mL) * TILE + iL] = f1;
+                sF[(6 + mL) * TILE + iL] = f2;
+            }
+            if (iR < TILE) {
+                T f0, f1, f2;
+                half_edge_flux(T(-1), F0, DR * nx - F2 * ny, DR * ny + F2 * nx, sbR, -nx, -ny, f0, f1, f2);
+                sF[mR * TILE + iR] = f0;
+                sF[(3 + mR) * TILE + iR] = f1;
+                sF[(6 + mR) * TILE + iR] = f2;
             }
         }
+        // boundary fluxes (Sec. 6.1), in the global frame
+        for (int i = nt + cl; i < nt + (d.w >> 16); i += NT) {
+            const StageArgs<T> &a = args_again<T>();
+            const unsigned e = load_entry<false>(ent, i).x;
+            const int l = e & 1023u, m = (e >> 20) & 3u, k = -(int)(e >> 24);
+            const T2 nb = ldx(nrm, i);
+            const T4 Ub = ldx(a.Uin, c0 + l);
+            const int st = a.n_scen == 1 ? 0 : (d.z >= 0 ? d.z : (int)((unsigned)a.nbr[c0 + l].w >> kScenShift));
+            const ScenParams sp = a.scen[st];
+            T q_in = T(0);
+            if (k == kBcInflow) {
+                const double t_st =
+                    bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)]) +
+                    (a.kind == 2 ? lane_step_dt(a.clock, a.ncopy, a.slot_cur, st, a.cfl_rule,
+                                                a.cfl, a.dt_max, a.dt_fixed)
+                                 : 0.0);
+                q_in = T(inflow_at(sp, a.ser_t, a.ser_q, t_st) * sp.inv_inflow_len);
+            }
+            T G[3];
+            boundary_flux_dev<T, T4>(k, Ub, nb.x, nb.y, g, eps, q_in, T(sp.outflow_stage), G);
+            sF[m * TILE + l] = G[0];
+            sF[(3 + m) * TILE + l] = G[1];
+            sF[(6 + m) * TILE + l] = G[2];
+        }
         __syncthreads();
-        // the update ends the tile and frees its slot for the next one: above
-        // the edge sweeps of other tiles, below their first phases
-        __builtin_amdgcn_s_setprio(2);
         // ---- 3: cell sums, update, friction, cleanup, CFL
+        const StageArgs<T> &b = args_again<T>();
         CflVal<T> cfl = cfl_none<T>();
-        const T4 Uc = Ukeep;
-        const unsigned word = active ? sW[cl] : 0u;
-        const int s = active ? (int)(word >> kScenShift) : -1;
-        const double dtd = dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl,
-                                     a.dt_max, a.dt_fixed);
+        const bool owned = c < b.n_owned;
+        if (b.n_scen > 1 && d.z < 0)
+            dtd = wave_step_dt(b.clock, b.ncopy, b.slot_cur, s, b.cfl_rule, b.cfl, b.dt_max, b.dt_fixed);
         if (active) {
+            const T4 Pc = sP[cl];  // h and b of the cell (hu and hv: kept)
             const T dt = T(dtd);
+            if (!kWide) {
+                lam0 = ldx(b.he_lam, c);
+                lam1 = ldx(b.he_lam, b.n + c);
+                lam2 = ldx(b.he_lam, 2 * b.n + c);
+                man2 = ldx(b.man2, c);
+            }
+            const T lam[3] = {lam0, lam1, lam2};
             T acc0 = T(0), acc1 = T(0), acc2 = T(0), lsum = T(0);
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-                const T lam = ldx(a.he_lam, m * a.n + c);
-                const T4 f = sR[m * TILE + cl];
-                acc0 += lam * f.x;
-                acc1 += lam * f.y;
-                acc2 += lam * f.z;
-                lsum += lam;
+                acc0 += lam[m] * sF[m * TILE + cl];
+                acc1 += lam[m] * sF[(3 + m) * TILE + cl];
+                acc2 += lam[m] * sF[(6 + m) * TILE + cl];
+                lsum += lam[m];
             }
-            T nh = Uc.x - dt * acc0;
+            T nh = Pc.x - dt * acc0;
             T nu = Uc.y - dt * acc1;
             T nv = Uc.z - dt * acc2;
             // the inscribed radius from the edge weights: sum_m L_m / |Omega|
@@ -1083,7 +1026,7 @@ k_stage_tiled(StageArgs<T> a)
             // n^2 is the only per-cell value read (4 bytes, not 16)
             T4 cg;
             cg.y = fdiv(T(2), lsum);
-            cg.z = ldx(a.man2, c);
+            cg.z = man2;
             int flags = 0;
             if (!(isfinite(nh) && isfinite(nu) && isfinite(nv))) flags |= kHealthNonfinite;
             if (nh < T(0)) {
@@ -1098,31 +1041,30 @@ k_stage_tiled(StageArgs<T> a)
                 const T rf = frcp(f);
                 nu *= rf; nv *= rf;
             }
-            if (a.kind == 2) {
-                const T4 U0c = ldx(a.U0, c);
+            if (b.kind == 2) {
+                const T4 U0c = ldx(b.U0, c);
                 nh = T(0.5) * (U0c.x + nh);
                 nu = T(0.5) * (U0c.y + nu);
                 nv = T(0.5) * (U0c.z + nv);
                 if (nh <= eps) { nu = T(0); nv = T(0); }
             }
             T4 out;
-            out.x = nh; out.y = nu; out.z = nv; out.w = Uc.w;
-            stx(a.Uout, c, out);
-            pack_own(a, c, nh, nu, nv);
+            out.x = nh; out.y = nu; out.z = nv; out.w = Pc.y;
+            stx(b.Uout, c, out);
+            pack_own(b, c, nh, nu, nv);
             // health counts owned cells: a ghost cell's new state is provisional
             // (the next exchange replaces it)
-            if (flags && ((word >> kOwnedBit) & 1u)) atomicOr(a.health, flags);
+            if (flags && owned) atomicOr(b.health, flags);
             cfl.scen = s;
-            if (a.kind != 1 && ((word >> kOwnedBit) & 1u) && nh > eps) {
+            if (b.kind != 1 && owned && nh > eps) {
                 const T r = frcp(nh);
                 const T u = nu * r, v = nv * r;
                 const T lm = sqrt(u * u + v * v) + sqrt(g * nh);
-                cfl = cfl_cell<T>(a.cfl_rule, s, cg.y, lm);
+                cfl = cfl_cell<T>(b.cfl_rule, s, cg.y, lm);
             }
         }
-        if (a.kind != 1) cfl_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, cfl, sCfl);
-        __builtin_amdgcn_s_setprio(0);
-        if (tile + (int)gridDim.x < ntiles) __syncthreads();  // LDS is reused by the next tile
+        if (b.kind != 1) cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
+        if (tv + (int)gridDim.x < ntiles) __syncthreads();  // LDS is reused by the next tile
     }
 }
 
@@ -1486,8 +1428,15 @@ template <typename P> void dfree_t(swe_ctx *c, P *&p)
     p = nullptr;
 }
 
+void release_plan(swe_ctx *c, TilePlan &p)
+{
+    dfree(c, p.mem);
+    p = TilePlan{};
+}
+
 void release_mesh(swe_ctx *c)
 {
+    for (TilePlan &p : c->plans) release_plan(c, p);
     if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
     dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->he_geo); dfree(c, c->he_dist);
     dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw); dfree(c, c->he_nrm);
@@ -1574,6 +1523,189 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
     return SWE_OK;
 }
 
+// Launch shape of the tiled kernel: cells per tile, a thread per edge or per
+// cell, and (256 cells, a thread per cell, FP32 with a classic limiter) the
+// register budget: 72 registers for seven waves per SIMD, or 64 for eight,
+// with a few spilled.
+struct Shape {
+    int tile;
+    bool wide, eight;
+};
+
+// Halo cells a tile of this size may have.  Morton-ordered meshes have halos
+// of about 65, 92, 130 and 185 cells (64 to 512 cells per tile; the 99th
+// percentile is 1.3 times that); the bounds keep the LDS of nine 256-cell
+// FP32 tiles within a compute unit.  Tiles of 64 cells have at most 576.
+inline int halo_bound(int tile) { return tile == 64 ? 576 : (tile == 128 ? 160 : (tile == 256 ? 208 : 320)); }
+
+template <int TILE>
+void launch_plan(swe_ctx *c, int nt, int write, int hs, int es, void *desc, void *halo, void *ent)
+{
+    hipLaunchKernelGGL(k_tile_plan<TILE>, dim3(nt), dim3(TILE < 256 ? TILE : 256), 0, c->stream,
+                       (const int4 *)c->nbr, (int)(c->cfg.scheme != SWE_HLLC1), write, hs, es,
+                       (int4 *)desc, (int *)halo, (uint2 *)ent);
+}
+
+void launch_plan_any(swe_ctx *c, int tile, int nt, int write, int hs, int es, void *desc, void *halo,
+                     void *ent)
+{
+    if (tile == 64) launch_plan<64>(c, nt, write, hs, es, desc, halo, ent);
+    else if (tile == 128) launch_plan<128>(c, nt, write, hs, es, desc, halo, ent);
+    else if (tile == 256) launch_plan<256>(c, nt, write, hs, es, desc, halo, ent);
+    else launch_plan<512>(c, nt, write, hs, es, desc, halo, ent);
+}
+
+template <typename T> void launch_plan_geometry(swe_ctx *c, const TilePlan &p)
+{
+    hipLaunchKernelGGL(k_plan_geometry<T>, dim3(p.ntiles), dim3(256), 0, c->stream, c->n_total, p.tile,
+                       (const int4 *)p.desc, (const int *)p.halo, (const uint2 *)p.ent, p.hs, p.es,
+                       (const typename V4<T>::type *)c->he_co, (const T *)c->he_gam,
+                       (typename V2<T>::type *)p.nrm, (typename V4<T>::type *)p.wgt,
+                       (typename V2<T>::type *)p.gam);
+}
+
+// The ranges of cells that become tiles: `tile` cells each, a range whose
+// halo is over the bound cut in two until it is not (where the numbering
+// jumps: the cells sent to several parts, ghost blocks).  More than an eighth
+// of the ranges cut says that the numbering has no locality at this size:
+// ok = false, and smaller tiles are taken.  rg: x first cell, y cells, z halo
+// cells, w edges.
+int plan_ranges(swe_ctx *c, int tile, std::vector<int4> &rg, bool &ok)
+{
+    const int n = c->n_total;
+    rg.clear();
+    ok = true;
+    std::vector<int4> todo, next;
+    for (int c0 = 0; c0 < n; c0 += tile) todo.push_back(make_int4(c0, std::min(tile, n - c0), 0, 0));
+    const size_t base = todo.size();
+    while (!todo.empty()) {
+        void *buf = nullptr;
+        const size_t bytes = sizeof(int4) * todo.size();
+        HIP_OK(c, dalloc(c, &buf, bytes));
+        hipError_t e = hipMemcpyAsync(buf, todo.data(), bytes, hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess) {
+            launch_plan_any(c, tile, (int)todo.size(), 0, 0, 0, buf, nullptr, nullptr);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipMemcpyAsync(todo.data(), buf, bytes, hipMemcpyDeviceToHost, c->stream);
+        const hipError_t es = hipStreamSynchronize(c->stream);
+        dfree(c, buf);
+        HIP_OK(c, e);
+        HIP_OK(c, es);
+        next.clear();
+        for (const int4 &r : todo) {
+            if (r.z <= halo_bound(tile)) { rg.push_back(r); continue; }
+            const int h = r.y / 2;
+            next.push_back(make_int4(r.x, h, 0, 0));
+            next.push_back(make_int4(r.x + h, r.y - h, 0, 0));
+        }
+        if (rg.size() + next.size() > base + base / 8 + 16) { ok = false; return SWE_OK; }
+        todo.swap(next);
+    }
+    std::sort(rg.begin(), rg.end(), [](const int4 &a, const int4 &b) { return a.x < b.x; });
+    return SWE_OK;
+}
+
+// The tile plan for tiles of B cells, or of a smaller size where their halos
+// do not fit.  Built on first use, on the context's stream; waits for it.
+int ensure_plan(swe_ctx *c, int B, TilePlan **out)
+{
+    for (int tile = B;; tile >>= 1) {
+        TilePlan &p = c->plans[tile == 64 ? 0 : (tile == 128 ? 1 : (tile == 256 ? 2 : 3))];
+        if (p.tile > 0) { *out = &p; return SWE_OK; }
+        if (p.tile < 0) continue;  // known not to fit
+        std::vector<int4> rg;
+        bool ok = false;
+        const int rc = plan_ranges(c, tile, rg, ok);
+        if (rc != SWE_OK) return rc;
+        if (!ok) { p.tile = -1; continue; }  // 64-cell tiles always fit
+        TilePlan q;
+        q.tile = tile;
+        q.ntiles = (int)rg.size();
+        for (int4 &r : rg) {
+            q.hs = std::max(q.hs, r.z);
+            q.es = std::max(q.es, r.w);
+        }
+        q.hs = std::max(4, (q.hs + 3) & ~3);
+        q.es = std::max(tile, (q.es + 15) & ~15);  // the kernel's first round loads `tile` places
+        const bool muscl = c->cfg.scheme == SWE_MUSCL;
+        const bool learned = muscl && c->cfg.limiter == SWE_LEARNED;
+        const size_t nt = q.ntiles, ne = nt * q.es, ts = c->tsize;
+        const size_t sz[6] = {16 * nt, 4 * nt * q.hs, 8 * ne, 2 * ts * ne, muscl ? 4 * ts * ne : 0,
+                              learned ? 2 * ts * ne : 0};
+        size_t off[7] = {0};
+        for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + ((sz[i] + 255) & ~(size_t)255);
+        HIP_OK(c, dalloc(c, &q.mem, off[6]));
+        p = q;  // owned by the context from here on
+        void **at[6] = {&p.desc, &p.halo, &p.ent, &p.nrm, &p.wgt, &p.gam};
+        for (int i = 0; i < 6; ++i) *at[i] = sz[i] ? (char *)p.mem + off[i] : nullptr;
+        hipError_t e = hipMemcpyAsync(p.desc, rg.data(), sz[0], hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess) {
+            launch_plan_any(c, tile, p.ntiles, 1, p.hs, p.es, p.desc, p.halo, p.ent);
+            if (c->tsize == 8) launch_plan_geometry<double>(c, p);
+            else launch_plan_geometry<float>(c, p);
+            e = hipGetLastError();
+        }
+        const hipError_t es = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess || es != hipSuccess) release_plan(c, p);
+        HIP_OK(c, e);
+        HIP_OK(c, es);
+        *out = &p;
+        return SWE_OK;
+    }
+}
+
+// The plan a step's launch uses, null for the kernels without one.
+inline bool uses_plan(const swe_ctx *c)
+{
+    return !c->cfg.cell_kernel && c->cfg.scheme != SWE_WAF;
+}
+
+// Tile and threads of the tiled kernel unless the configuration or the
+// autotuner chose them.  While the chip holds every tile at once a launch
+// costs its tiles' chain of latencies: tiles of 128 cells with a thread per
+// edge (per step: 12.3 us against 15.3 with a thread per cell on 20,160 cells
+// MUSCL FP32, 19.5 against 23.1 on 101,202 cells FP64), of 64 cells while
+// there is a compute unit for each (7.3 against 7.6 us on 16,000 cells
+// first-order FP64).  Larger meshes are bound by what the compute units keep
+// in flight: a thread per cell, 256 cells (49 against 60 us on a million
+// cells MUSCL FP32; learned limiter 37.3 against 39.0 on 250,000).
+inline Shape wanted_shape(const swe_ctx *c)
+{
+    const int n = c->n_total, ncu = c->ncu > 0 ? c->ncu : 256;
+    // blocks of 256 threads a compute unit holds: 7 (FP32, 72 registers) or
+    // 4 (FP64, 128 registers)
+    const int held = c->tsize == 8 ? 4 : 7;
+    const bool few = (long long)n <= 128LL * held * ncu;
+    Shape s{c->block, few, false};
+    if (s.tile == 0) s.tile = !few ? 256 : ((long long)n <= 64LL * ncu ? 64 : 128);
+    if (c->tsize == 8) s.tile = std::min(s.tile, 256);
+    if (c->wide >= 0) s.wide = c->wide != 0;
+    if (s.tile == 512) s.wide = false;
+    return s;
+}
+
+int current_plan(swe_ctx *c, TilePlan **out)
+{
+    *out = nullptr;
+    if (!uses_plan(c)) return SWE_OK;
+    return ensure_plan(c, wanted_shape(c).tile, out);
+}
+
+// The shape of a launch over this plan.  Eight waves per SIMD where a launch
+// spans eight or more rounds of tiles and runs as a persistent grid (589
+// against 604 us per step on the 13M-cell river); on a million cells they are
+// slower (54 against 49 us).
+inline Shape launch_shape(const swe_ctx *c, const TilePlan &p)
+{
+    Shape s = wanted_shape(c);
+    s.tile = p.tile;
+    s.eight = c->grid_persist >= 0 && p.ntiles >= 8LL * 7 * c->ncu;
+    if (c->cfg.waves) s.eight = c->cfg.waves == 7;
+    if (c->eight >= 0) s.eight = c->eight != 0;
+    return s;
+}
+
 int push_scenarios(swe_ctx *c)
 {
     // the buffers below are replaced: the stream must be done with them
@@ -1606,38 +1738,17 @@ int push_scenarios(swe_ctx *c)
 
 template <typename T> using KernelFn = void (*)(StageArgs<T>);
 
-template <typename T, int TILE, int OCC = SWE_TILED_WAVES> KernelFn<T> pick_tiled(int scheme, int lim)
+template <typename T, int TILE, int NT, int OCC> KernelFn<T> pick_tiled(int scheme, int lim)
 {
-    if (scheme == kHLLC1) return k_stage_tiled<T, false, kMinmod, TILE, OCC>;
+    if (scheme == kHLLC1) return k_stage_tiled<T, false, kMinmod, TILE, NT, OCC>;
     switch (lim) {
-    case kSuperbee: return k_stage_tiled<T, true, kSuperbee, TILE, OCC>;
-    case kVanAlbada: return k_stage_tiled<T, true, kVanAlbada, TILE, OCC>;
-    case kLearned: return k_stage_tiled<T, true, kLearned, TILE>;
-    case kLearnedNet: return k_stage_tiled<T, true, kLearnedNet, TILE>;
-    case kZeroSlope: return k_stage_tiled<T, true, kZeroSlope, TILE, OCC>;
-    default: return k_stage_tiled<T, true, kMinmod, TILE, OCC>;
+    case kSuperbee: return k_stage_tiled<T, true, kSuperbee, TILE, NT, OCC>;
+    case kVanAlbada: return k_stage_tiled<T, true, kVanAlbada, TILE, NT, OCC>;
+    case kLearned: return k_stage_tiled<T, true, kLearned, TILE, NT>;
+    case kLearnedNet: return k_stage_tiled<T, true, kLearnedNet, TILE, NT>;
+    case kZeroSlope: return k_stage_tiled<T, true, kZeroSlope, TILE, NT, OCC>;
+    default: return k_stage_tiled<T, true, kMinmod, TILE, NT, OCC>;
     }
-}
-
-// Seven waves per SIMD instead of six for the FP32 tiled kernel with
-// 256-cell tiles: each tile takes longer (72 registers instead of 80), but
-// the chip holds 7 instead of 6 tiles per compute unit.  Worth it when that
-// saves a round of tiles in a launch of at most two rounds (a sub-domain of
-// about 400k cells: one round instead of two), and on a launch of many
-// rounds (8 or more), which then runs as a persistent grid of 7 blocks per
-// compute unit (measured 6% faster on the 13M-cell river); on
-// config-2-sized meshes (a few rounds) six is faster.
-template <typename T> bool seven_waves(const swe_ctx *c, int B)
-{
-    if (sizeof(T) != 4 || B != 256 || c->cfg.scheme == SWE_WAF || c->cfg.cell_kernel ||
-        (c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED))
-        return false;
-    if (c->waves) return c->waves == 7;
-    const long long nt = (c->n_total + B - 1) / B, s6 = 6LL * c->ncu, s7 = 7LL * c->ncu;
-    if (s6 <= 0) return false;
-    const long long r6 = (nt + s6 - 1) / s6, r7 = (nt + s7 - 1) / s7;
-    if (r6 >= 8 && c->grid_persist >= 0) return true;  // persistent grid (see stage_grid)
-    return r7 < r6 && r6 <= 2;
 }
 
 template <typename T> KernelFn<T> pick_cell_kernel(int scheme, int lim, int wafm);
@@ -1651,20 +1762,32 @@ template <typename T, int TILE> KernelFn<T> pick_tiled_waf(int wafm)
     return k_stage_tiled_waf<T, kWafSuperbee, TILE>;
 }
 
-template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, int block, int cell,
-                                              bool w7, bool euler)
+template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, Shape sh, int cell, bool euler)
 {
     if (scheme == kWAF && !cell && euler) {  // tiled WAF: Euler only (as the paper's WAF)
-        if (block == 64) return pick_tiled_waf<T, 64>(wafm);
-        if (block == 128 || sizeof(T) == 8) return pick_tiled_waf<T, 128>(wafm);
+        if (sh.tile == 64) return pick_tiled_waf<T, 64>(wafm);
+        if (sh.tile == 128 || sizeof(T) == 8) return pick_tiled_waf<T, 128>(wafm);
         return pick_tiled_waf<T, 256>(wafm);
     }
     if (scheme != kWAF && !cell) {
-        if (block == 64) return pick_tiled<T, 64>(scheme, lim);
-        if (block == 128) return pick_tiled<T, 128>(scheme, lim);
-        if (block == 512 && sizeof(T) == 4) return pick_tiled<T, 512>(scheme, lim);
-        if (w7 && sizeof(T) == 4) return pick_tiled<T, 256, 7>(scheme, lim);
-        return pick_tiled<T, 256>(scheme, lim);
+        constexpr int W = SWE_TILED_WAVES;
+        switch (sh.tile) {
+        case 64:
+            return sh.wide ? pick_tiled<T, 64, tile_threads(64, true), W>(scheme, lim)
+                           : pick_tiled<T, 64, 64, W>(scheme, lim);
+        case 128:
+            return sh.wide ? pick_tiled<T, 128, tile_threads(128, true), W>(scheme, lim)
+                           : pick_tiled<T, 128, 128, W>(scheme, lim);
+        case 512:
+            if constexpr (sizeof(T) == 4) return pick_tiled<T, 512, 512, W>(scheme, lim);
+            [[fallthrough]];
+        default:
+            if (sh.wide) return pick_tiled<T, 256, tile_threads(256, true), W>(scheme, lim);
+            if constexpr (sizeof(T) == 4)
+                if (sh.eight && scheme == kMUSCL && lim != kLearned && lim != kLearnedNet)
+                    return pick_tiled<T, 256, 256, 8>(scheme, lim);
+            return pick_tiled<T, 256, 256, W>(scheme, lim);
+        }
     }
     return pick_cell_kernel<T>(scheme, lim, wafm);
 }
@@ -1688,10 +1811,10 @@ template <typename T> KernelFn<T> pick_cell_kernel(int scheme, int lim, int wafm
 
 // Blocks of `kernel` (block size B) the whole chip holds at once (0 if the
 // occupancy query fails).
-inline int resident_blocks(const swe_ctx *c, const void *kernel, int B)
+inline int resident_blocks(const swe_ctx *c, const void *kernel, int B, size_t lds)
 {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, B, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, B, lds) != hipSuccess) return 0;
     return per_cu * c->ncu;
 }
 
@@ -1700,11 +1823,11 @@ inline int resident_blocks(const swe_ctx *c, const void *kernel, int B)
 // persistent grid of the blocks the chip holds at once, each sweeping tiles
 // (measured: 2.7% faster on the 13M-cell river; on a mesh of a few rounds
 // the hardware's own dispatch of one tile per block balances better)
-inline int stage_grid(const swe_ctx *c, const void *kernel, int B, int ntiles)
+inline int stage_grid(const swe_ctx *c, const void *kernel, int B, int ntiles, size_t lds)
 {
     int gp = c->grid_persist;
     if (gp == 0) {
-        const int res = resident_blocks(c, kernel, B);
+        const int res = resident_blocks(c, kernel, B, lds);
         if (res > 0 && ntiles >= 8 * res) gp = res;
     }
     if (gp < 0) gp = 0;  // one tile per block, as asked
@@ -1723,6 +1846,7 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     using T4 = typename V4<T>::type;
     StageArgs<T> a{};
     a.n = c->n_total;
+    a.n_owned = c->n_owned;
     a.n_scen = c->n_scen;
     a.nbr = (const int4 *)c->nbr;
     a.cell = (const T4 *)c->cell;
@@ -1751,19 +1875,34 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     a.slot_cur = (int)(step % 3);
     a.slot_next = (int)((step + 1) % 3);
     a.slot_reset = (int)((step + 2) % 3);
-    // the one-thread-per-cell kernel is built for at most 256 threads, and
-    // FP64 tiles stop at 256 cells (LDS)
     const bool euler = c->cfg.integrator == SWE_EULER;
     const bool cell_kernel = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
-    // the cell kernel, FP64 and the WAF tiles stop at 256 cells (FP64 WAF
-    // tiles at 128: LDS)
-    int B = cell_kernel || sizeof(T) == 8 || c->cfg.scheme == SWE_WAF ? std::min(c->block, 256) : c->block;
-    if (c->cfg.scheme == SWE_WAF && !cell_kernel && sizeof(T) == 8) B = std::min(B, 128);
-    KernelFn<T> k = pick_kernel<T>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, B,
-                                   cell_kernel, seven_waves<T>(c, B), euler);
-    const int ntiles = (c->n_total + B - 1) / B;
-    dim3 grid(cell_kernel ? ntiles : stage_grid(c, (const void *)k, B, ntiles));
-    const dim3 blk(B);
+    const bool lrn = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
+    // the cell kernel and the WAF tiles stop at 256 cells (FP64 WAF tiles at
+    // 128: LDS)
+    Shape sh{std::min(c->block ? c->block : 256, 256), false, false};
+    if (c->cfg.scheme == SWE_WAF && !cell_kernel && sizeof(T) == 8) sh.tile = std::min(sh.tile, 128);
+    TilePlan *plan = nullptr;
+    const int prc = current_plan(c, &plan);  // built by the call that uploaded the mesh
+    if (prc != SWE_OK) return prc;
+    if (plan) {
+        sh = launch_shape(c, *plan);
+        a.tdesc = (const int4 *)plan->desc;
+        a.thalo = (const int *)plan->halo;
+        a.tent = (const uint2 *)plan->ent;
+        a.tnrm = (const typename V2<T>::type *)plan->nrm;
+        a.twgt = (const T4 *)plan->wgt;
+        a.tgam = (const typename V2<T>::type *)plan->gam;
+        a.hs = plan->hs;
+        a.es = plan->es;
+        a.ntiles = plan->ntiles;
+    }
+    const int ntiles = plan ? plan->ntiles : (c->n_total + sh.tile - 1) / sh.tile;
+    const int threads = plan ? tile_threads(sh.tile, sh.wide) : sh.tile;
+    const size_t lds = plan ? tiled_lds<T>(sh.tile, plan->hs, lrn, false) : 0;
+    KernelFn<T> k = pick_kernel<T>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell_kernel, euler);
+    dim3 grid(cell_kernel ? ntiles : stage_grid(c, (const void *)k, threads, ntiles, lds));
+    const dim3 blk(threads);
     T4 *Ucur = (T4 *)c->U[step & 1];
     // the learned limiter's phi is evaluated from U^n of the steps whose
     // index is a multiple of phi_every (every step by default; a step between
@@ -1779,19 +1918,23 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     if (phi_sep && launch_limiter_phi(c, Ucur, c->phi) != SWE_OK) return SWE_ERR_DEVICE;
     KernelFn<T> k1 = k;  // the step's first stage
     dim3 grid1 = grid;
+    size_t lds1 = lds;
     if (phi_now && !phi_sep) {
-        k1 = pick_kernel<T>(c->cfg.scheme, kLearnedNet, c->cfg.waf_limiter, B, 0, false, euler);
-        grid1 = dim3(stage_grid(c, (const void *)k1, B, ntiles));
+        k1 = pick_kernel<T>(c->cfg.scheme, kLearnedNet, c->cfg.waf_limiter, sh, 0, euler);
+        lds1 = tiled_lds<T>(sh.tile, plan->hs, true, true);
+        grid1 = dim3(stage_grid(c, (const void *)k1, threads, ntiles, lds1));
     }
+    size_t lds2 = lds;
     if (c->cfg.integrator == SWE_RK2) {
         // stage 1: U^n -> U1;  stage 2: U1 -> U^{n+1} = (U^n + E(U1)) / 2
         a.kind = 1; a.Uin = Ucur; a.U0 = Ucur; a.Uout = (T4 *)c->U1;
-        hipLaunchKernelGGL(k1, grid1, blk, 0, c->stream, a);
+        hipLaunchKernelGGL(k1, grid1, blk, lds1, c->stream, a);
         a.kind = 2; a.Uin = (T4 *)c->U1; a.U0 = Ucur; a.Uout = (T4 *)c->U[(step + 1) & 1];
     } else {
         a.kind = 0; a.Uin = Ucur; a.U0 = Ucur; a.Uout = (T4 *)c->U[(step + 1) & 1];
         k = k1;
         grid = grid1;
+        lds2 = lds1;
     }
     if (ov.sendbuf && c->n_send > 0) {  // the last stage also fills the send buffer
         a.pk_off = c->pk_off;
@@ -1800,7 +1943,7 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
         a.pk_ncell = c->send_prefix;
         a.pk_nsend = c->n_send;
     }
-    hipLaunchKernelGGL(k, grid, blk, 0, c->stream, a);
+    hipLaunchKernelGGL(k, grid, blk, lds2, c->stream, a);
     HIP_OK(c, hipGetLastError());
     return SWE_OK;
 }
@@ -1884,12 +2027,12 @@ int swe_create(const swe_config *cfg, swe_ctx **out)
     c->cfg = *cfg;
     c->dev = cfg->device;
     c->tsize = cfg->precision == SWE_F64 ? 8 : 4;
-    // default tile: 256 cells, 64 for the FP32 tiled WAF kernel (its LDS
-    // per cell is larger, and smaller tiles keep more of them in flight)
+    // default tile: chosen by size (wanted_shape), 64 for the FP32 tiled WAF
+    // kernel (its LDS per cell is larger, and smaller tiles keep more of them
+    // in flight)
     const bool waf_tiled32 = cfg->scheme == SWE_WAF && cfg->integrator == SWE_EULER &&
                              !cfg->cell_kernel && cfg->precision == SWE_F32;
-    c->block = cfg->block ? cfg->block : (waf_tiled32 ? 64 : 256);
-    c->waves = cfg->waves;
+    c->block = cfg->block ? cfg->block : (waf_tiled32 ? 64 : 0);
     c->own_stream = cfg->stream == nullptr;
     if (!c->own_stream) c->stream = (hipStream_t)cfg->stream;
     if (hipSetDevice(c->dev) != hipSuccess ||
@@ -2055,6 +2198,9 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
         sp.outflow_stage = ms[i].outflow_stage;
     }
     rc = push_scenarios(c);
+    if (rc != SWE_OK) return rc;
+    TilePlan *plan = nullptr;
+    rc = current_plan(c, &plan);
     if (rc != SWE_OK) return rc;
     c->has_mesh = true;
     c->has_state = false;
@@ -2378,29 +2524,37 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     const bool graphs = c->use_graphs;
     c->use_graphs = false;
     float best = 1e30f;
-    int best_b = c->block, best_g = c->grid_persist, best_w = c->waves;
+    int best_b = c->block, best_g = c->grid_persist, best_w = c->wide, best_e = c->eight;
     int rc = SWE_OK;
     // only launch shapes of the configured kernel: they give bitwise the same
     // results (the tiled kernel is tiling-independent), the two kernels do not
-    const int cell0 = c->cfg.cell_kernel;
-    const bool tiled = c->cfg.scheme != SWE_WAF && !cell0;
+    const bool euler = c->cfg.integrator == SWE_EULER;
+    const bool cell = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
+    const bool tiled = uses_plan(c);
     const bool f64 = c->cfg.precision == SWE_F64;
-    int best_cell = cell0;
     const bool learned = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
     for (int B : {64, 128, 256, 512})
-    for (int W : {6, 7}) {
+    for (int W = 0; W < 3; ++W) {  // a thread per cell, per edge, per cell with eight waves per SIMD
         if (B == 512 && (!tiled || f64)) continue;  // FP32 tiled kernel only
-        // a second register budget only for the FP32 tiled kernel with 256-cell tiles
-        if (W == 7 && (B != 256 || !tiled || f64 || learned)) continue;
+        if (W == 1 && (!tiled || B == 512)) continue;
+        if (W == 2 && (!tiled || B != 256 || f64 || learned || c->cfg.scheme != SWE_MUSCL)) continue;
         for (int persist = 0; persist < 2 && rc == SWE_OK; ++persist) {
             c->block = B;
-            c->waves = W;
+            c->wide = W == 1;
+            c->eight = W == 2;
             c->grid_persist = -1;  // one tile per block
+            TilePlan *plan = nullptr;
+            rc = current_plan(c, &plan);
+            if (rc != SWE_OK) break;
+            if (plan && plan->tile != B) continue;  // its tiles do not fit: a smaller size stands for it
             if (persist) {
-                const bool cell = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && c->cfg.integrator != SWE_EULER);
-                const int res = c->cfg.precision == SWE_F64
-                                    ? resident_blocks(c, (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, B, cell, false, c->cfg.integrator == SWE_EULER), B)
-                                    : resident_blocks(c, (const void *)pick_kernel<float>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, B, cell, W == 7, c->cfg.integrator == SWE_EULER), B);
+                const Shape sh{B, W == 1, W == 2};
+                const int threads = plan ? tile_threads(B, sh.wide) : B;
+                const size_t lds = !plan ? 0 : (f64 ? tiled_lds<double>(B, plan->hs, learned, false)
+                                                    : tiled_lds<float>(B, plan->hs, learned, false));
+                const void *k = f64 ? (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler)
+                                    : (const void *)pick_kernel<float>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler);
+                const int res = resident_blocks(c, k, threads, lds);
                 c->grid_persist = res > 0 ? res : ncu * (2048 / B);
             }
             (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
@@ -2414,16 +2568,22 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
             float ms = 0.f;
             rc = swe_last_step_ms(c, &ms);
             if (rc == SWE_OK && ms < best) {
-                best = ms; best_b = B; best_g = c->grid_persist; best_cell = c->cfg.cell_kernel;
-                best_w = W;
+                best = ms; best_b = B; best_g = c->grid_persist; best_w = c->wide; best_e = c->eight;
             }
         }
     }
     c->use_graphs = graphs;
     c->block = best_b;
     c->grid_persist = best_g;
-    c->waves = best_w;
-    c->cfg.cell_kernel = best_cell;
+    c->wide = best_w;
+    c->eight = best_e;
+    {   // the other sizes' plans go
+        TilePlan *plan = nullptr;
+        const int prc = current_plan(c, &plan);
+        if (rc == SWE_OK) rc = prc;
+        for (TilePlan &p : c->plans)
+            if (&p != plan) release_plan(c, p);
+    }
     (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
     (void)hipMemcpyAsync(c->clock, saveK, clock_bytes(c), hipMemcpyDeviceToDevice, c->stream);
     (void)hipStreamSynchronize(c->stream);

@@ -457,36 +457,25 @@ __device__ __forceinline__ T limit2(T sb, T sf)
     return p > T(0) ? copysign(m, sf) : T(0);
 }
 
-// Interface values of cell C across an interior edge with outward normal n
-// (Sec. 6.2.3 on the rotated states), K across the edge, A and B the upwind
-// cells, with the distances folded into weights: al = d_mid / d_up and
-// be = d_mid / d_fwd for the limited slope, ga = d_mid / d_central for the
-// learned limiter's scaled central slope.
-template <typename T, bool MUSCL_, int LIM>
-__device__ __forceinline__ Half<T> recon3(const Prim<T> &C, const Prim<T> &K, const Prim<T> &A,
-                                          bool ha, const Prim<T> &B, bool hb, T nx, T ny, T al,
-                                          T be, T ga, float phi, T eps)
+// Interface values of one side of an interior edge (Sec. 6.2.3), in the
+// edge's frame: qc the side's cell, qk the cell across (h, eta, normal and
+// tangential velocity), A and B the side's upwind cells (h, b, u, v; the same
+// one twice where one is missing).  The distances are folded into weights:
+// al = d_mid / d_up and be = d_mid / d_fwd for the limited slope, ga = d_mid /
+// d_central for the learned limiter's scaled central slope.  r comes in with
+// the first-order values and keeps them where a stencil cell is dry or the
+// reconstructed depth is negative.
+template <typename T, int LIM, typename T4>
+__device__ __forceinline__ void recon_side(Half<T> &r, const T qc[4], const T qk[4], const T4 &A,
+                                           const T4 &B, bool wet, T nx, T ny, T al, T be, T ga,
+                                           float phi, T eps)
 {
-    Half<T> r;
-    r.h = C.h;
-    r.b = C.b;
-    r.eta = C.h + C.b;
-    r.un = C.u * nx + C.v * ny;
-    r.ut = -C.u * ny + C.v * nx;
-    if (!MUSCL_) return r;
-    if (!(C.h > eps) || !(K.h > eps)) return r;
-    if ((ha && !(A.h > eps)) || (hb && !(B.h > eps)) || (!ha && !hb)) return r;
-    const T qc[4] = {C.h, C.h + C.b, r.un, r.ut};
-    const T qk[4] = {K.h, K.h + K.b, K.u * nx + K.v * ny, -K.u * ny + K.v * nx};
+    if (!(wet && A.x > eps && B.x > eps)) return;
     // upwind state: the mean of the upwind cells (rotation is linear, so the
-    // mean velocity is rotated once), or the one that exists
-    const bool both = ha && hb;
-    const Prim<T> &O = ha ? A : B;
-    const T uh = both ? T(0.5) * (A.h + B.h) : O.h;
-    const T ue = both ? T(0.5) * ((A.h + A.b) + (B.h + B.b)) : O.h + O.b;
-    const T uu = both ? T(0.5) * (A.u + B.u) : O.u;
-    const T uv = both ? T(0.5) * (A.v + B.v) : O.v;
-    const T qu[4] = {uh, ue, uu * nx + uv * ny, -uu * ny + uv * nx};
+    // mean velocity is rotated once)
+    const T uu = T(0.5) * (A.z + B.z), uv = T(0.5) * (A.w + B.w);
+    const T qu[4] = {T(0.5) * (A.x + B.x), T(0.5) * ((A.x + A.y) + (B.x + B.y)), uu * nx + uv * ny,
+                     -uu * ny + uv * nx};
     T out[4];
     bool done = false;
     if (LIM == kLearned) {
@@ -505,58 +494,15 @@ __device__ __forceinline__ Half<T> recon3(const Prim<T> &C, const Prim<T> &K, co
             out[i] = qc[i] + limit2<T, (LIM == kLearned ? kMinmod : LIM)>(al * (qc[i] - qu[i]),
                                                                           be * (qk[i] - qc[i]));
     }
-    if (out[0] < T(0)) return r;
+    if (out[0] < T(0)) return;
     r.h = out[0];
     r.b = out[1] - out[0];
     r.eta = out[1];
     r.un = out[2];
     r.ut = out[3];
-    return r;
 }
 
-// HLLC of Sec. 6.2.1 from depths and normal-frame velocities (the same
-// estimates as wave_fan / flux_hllc).
-template <typename T>
-__device__ __forceinline__ void hllc_prim(T g, T eps, T hL, T uL, T vL, T hR, T uR, T vR, T F[3])
-{
-    const bool wl = hL > eps, wr = hR > eps;
-    if (!wl && !wr) { F[0] = F[1] = F[2] = T(0); return; }
-    if (!wl) { uL = T(0); vL = T(0); }
-    if (!wr) { uR = T(0); vR = T(0); }
-    const T qL = wl ? hL * uL : T(0), qR = wr ? hR * uR : T(0);
-    const T aL = sqrt(g * hL), aR = sqrt(g * hR);
-    T SL, SR, Ss;
-    if (!wr) {
-        SL = uL - aL; SR = uL + T(2) * aL; Ss = SR;
-    } else if (!wl) {
-        SL = uR - T(2) * aR; SR = uR + aR; Ss = SL;
-    } else {
-        const T h0 = T(0.5) * (hL + hR) - T(0.25) * (uR - uL) * (hL + hR) * frcp(aR + aL);
-        T hs;
-        if (h0 <= tmin(hL, hR)) {
-            const T t = T(0.5) * (aR + aL) + T(0.25) * (uL - uR);
-            hs = t > T(0) ? t * t * frcp(g) : T(0);
-        } else {
-            const T gL = sqrt(g * (h0 + hL) * frcp(T(2) * h0 * hL));
-            const T gR = sqrt(g * (h0 + hR) * frcp(T(2) * h0 * hR));
-            hs = (hL * gL + hR * gR + uL - uR) * frcp(gL + gR);
-        }
-        const T pL = hs > hL ? sqrt((hs + hL) * hs * frcp(T(2) * hL * hL)) : T(1);
-        const T pR = hs > hR ? sqrt((hs + hR) * hs * frcp(T(2) * hR * hR)) : T(1);
-        SL = uL - aL * pL;
-        SR = uR + aR * pR;
-        Ss = (SL * hR * (uR - SR) - SR * hL * (uL - SL)) * frcp(hR * (uR - SR) - hL * (uL - SL));
-    }
-    const T GL1 = qL * uL + T(0.5) * g * hL * hL, GR1 = qR * uR + T(0.5) * g * hR * hR;
-    if (SL >= T(0)) { F[0] = qL; F[1] = GL1; F[2] = qL * vL; return; }
-    if (SR <= T(0)) { F[0] = qR; F[1] = GR1; F[2] = qR * vR; return; }
-    const T inv = frcp(SR - SL);
-    F[0] = (SR * qL - SL * qR + SR * SL * (hR - hL)) * inv;
-    F[1] = (SR * GL1 - SL * GR1 + SR * SL * (qR - qL)) * inv;
-    F[2] = F[0] * (Ss >= T(0) ? vL : vR);
-}
-
-// HLLC of Sec. 6.2.1 (the estimates of hllc_prim) in pressure-deviation
+// HLLC of Sec. 6.2.1 (the estimates of wave_fan) in pressure-deviation
 // form: the mass flux F0, the tangential flux F2 and, for the normal
 // momentum, the flux less either side's hydrostatic pressure,
 // DL = F1 - g hL^2 / 2 and DR = F1 - g hR^2 / 2.  The pressure difference

@@ -1,0 +1,248 @@
+// Tile plan of the tiled stage kernels: for every tile (at most TILE
+// consecutive cells), the cells its edges read and the edges themselves,
+// built once per mesh on the device.
+//
+// A tile's cells have the slots 0 .. TILE-1; the cells outside it that its
+// edges need (those across an edge and, for MUSCL and WAF, their other
+// neighbours) are its halo, slots TILE .. TILE + hs - 1, listed once each in
+// ascending order.  Every edge of the tile's cells is one entry in canonical
+// orientation (L the cell of smaller global id, L's outward normal): inside
+// edges first, then edges leaving the tile (each side's tile has its own
+// entry), then boundary edges.  The stage kernels then need no neighbour
+// table: all addresses are known before the first load returns, the states
+// are gathered once per tile, and everything an edge reads is in LDS or in
+// one contiguous stream.
+//
+// Entry (two words):
+//   x: L slot (10) | R slot (10) | mL (2) | mR (2) | low 8 bits of Rb
+//   y: La (10) | Lb (10) | Ra (10) | high 2 bits of Rb
+// mL, mR: the edge's local number in L and R; La, Lb (Ra, Rb): the two other
+// neighbours of L (R).  Where one of them is missing its place holds the
+// other, so their mean is the existing one; where both are, the cell itself
+// (a zero slope: first order).  A boundary edge has R = kNoCell, its cell as
+// L and minus its tag in the last byte of x.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "swe_internal.h"
+#include "swe_kernels.h"
+
+namespace swe {
+
+constexpr unsigned kNoCell = 1023u;
+constexpr int kMaxSlots = 1023;  // 10-bit slots, kNoCell excluded
+
+// One block per tile, threads = min(TILE, 256).  desc[tile] comes in with x:
+// the tile's first cell and y: its cells.  write == 0: z becomes the halo's
+// cells and w the tile's edges; otherwise z becomes the scenario (-1 when the
+// tile holds several), w the edges to other cells and, from bit 16, the
+// boundary edges, and the tile's halo list (-1 after its end) and entries are
+// written.  ring2: list the far cells' other neighbours too.
+template <int TILE>
+__global__ void __launch_bounds__(TILE < 256 ? TILE : 256)
+k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, int *halo, uint2 *ent)
+{
+    constexpr int NT = TILE < 256 ? TILE : 256, CPT = TILE / NT;
+    constexpr int CAP = TILE * 9 <= 1024 ? 1024 : (TILE * 9 <= 2048 ? 2048 : (TILE * 9 <= 4096 ? 4096 : 8192));
+    __shared__ int sC[CAP];
+    __shared__ int sScan[NT];
+    __shared__ unsigned long long sScan64[NT];
+    __shared__ int sCnt, sUniq;
+    const int t = threadIdx.x, tile = blockIdx.x, c0 = desc[tile].x, c1 = c0 + desc[tile].y;
+    if (t == 0) sCnt = 0;
+    __syncthreads();
+    const auto inside = [&](int k) { return k >= c0 && k < c1; };
+    const auto third = [](const int4 &v, int m) { return m == 0 ? v.x : (m == 1 ? v.y : v.z); };
+    for (int c = c0 + t; c < c1; c += NT) {
+        const int4 q = nbr[c];
+        for (int m = 0; m < 3; ++m) {
+            const int k = third(q, m);
+            if (k < 0 || inside(k)) continue;
+            sC[atomicAdd(&sCnt, 1)] = k;
+            if (!ring2) continue;
+            const int4 p = nbr[k];
+            const int jb = ((unsigned)q.w >> (2 * m)) & 3;
+            for (int j = 1; j < 3; ++j) {
+                const int kk = third(p, (jb + j) % 3);
+                if (kk >= 0 && !inside(kk)) sC[atomicAdd(&sCnt, 1)] = kk;
+            }
+        }
+    }
+    __syncthreads();
+    const int cnt = sCnt;
+    int P = NT;
+    while (P < cnt) P <<= 1;
+    for (int i = cnt + t; i < P; i += NT) sC[i] = 0x7fffffff;
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)  // bitonic sort, ascending
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int i = t; i < P; i += NT) {
+                const int l = i ^ j;
+                if (l > i) {
+                    const int x = sC[i], y = sC[l];
+                    if ((x > y) == ((i & k) == 0)) { sC[i] = y; sC[l] = x; }
+                }
+            }
+            __syncthreads();
+        }
+    // unique: every thread owns a contiguous run of P / NT values; a scan of
+    // the runs' counts gives the places
+    const int run = P / NT, r0 = t * run;
+    int heads = 0;
+    for (int i = r0; i < r0 + run; ++i)
+        heads += sC[i] != 0x7fffffff && (i == 0 || sC[i] != sC[i - 1]);
+    sScan[t] = heads;
+    __syncthreads();
+    for (int d = 1; d < NT; d <<= 1) {
+        const int v = t >= d ? sScan[t - d] : 0;
+        __syncthreads();
+        sScan[t] += v;
+        __syncthreads();
+    }
+    const int at0 = sScan[t] - heads;
+    if (t == NT - 1) sUniq = sScan[t];
+    int prev = r0 > 0 ? sC[r0 - 1] : -1;
+    __syncthreads();  // the run before is read before its owner moves values
+    // compaction in place moves values to the left only; runs are handled in
+    // thread order by going through registers first
+    {
+        int keep[CAP / NT];
+#pragma unroll 1
+        for (int i = 0; i < run; ++i) {
+            const int v = sC[r0 + i];
+            keep[i] = v != 0x7fffffff && v != prev ? v : -1;
+            prev = v;
+        }
+        __syncthreads();
+        int at = at0;
+#pragma unroll 1
+        for (int i = 0; i < run; ++i)
+            if (keep[i] >= 0) sC[at++] = keep[i];
+    }
+    __syncthreads();
+    const int nh = sUniq;
+    // edges: counts per cell (inside | outside | boundary, 21 bits each)
+    unsigned long long mine = 0;
+    int smin = 0x7fffffff, smax = -1;
+    for (int i = 0; i < CPT; ++i) {
+        const int c = c0 + t * CPT + i;
+        if (c >= c1) break;
+        const int4 q = nbr[c];
+        const int s = (int)((unsigned)q.w >> kScenShift);
+        smin = s < smin ? s : smin;
+        smax = s > smax ? s : smax;
+        for (int m = 0; m < 3; ++m) {
+            const int k = third(q, m);
+            if (k < 0) mine += 1ull << 42;
+            else if (!inside(k)) mine += 1ull << 21;
+            else if (((unsigned)q.w >> (6 + m)) & 1u) mine += 1ull;
+        }
+    }
+    sScan64[t] = mine;
+    sScan[t] = smin;
+    __syncthreads();
+    for (int d = 1; d < NT; d <<= 1) {
+        const unsigned long long v = t >= d ? sScan64[t - d] : 0ull;
+        __syncthreads();
+        sScan64[t] += v;
+        __syncthreads();
+    }
+    const unsigned long long all = sScan64[NT - 1], before = sScan64[t] - mine;
+    const int ni = (int)(all & 0x1fffff), no = (int)((all >> 21) & 0x1fffff), nb = (int)(all >> 42);
+    if (!write) {
+        if (t == 0) {
+            desc[tile].z = nh;
+            desc[tile].w = ni + no + nb;
+        }
+        return;
+    }
+    // one scenario in the whole tile?  (sScan holds the threads' minima)
+    const int first = sScan[0];
+    const int mixed = __syncthreads_or(smax >= 0 && (smin != first || smax != first));
+    if (t == 0) desc[tile] = make_int4(c0, c1 - c0, mixed ? -1 : first, (ni + no) | (nb << 16));
+    for (int i = t; i < hs; i += NT) halo[(size_t)tile * hs + i] = i < nh ? sC[i] : -1;
+    const auto slot = [&](int k) -> unsigned {
+        if (inside(k)) return (unsigned)(k - c0);
+        int lo = 0, hi = nh - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (sC[mid] < k) lo = mid + 1;
+            else hi = mid;
+        }
+        return (unsigned)(TILE + lo);
+    };
+    uint2 *e = ent + (size_t)tile * es;
+    int ai = (int)(before & 0x1fffff), ao = ni + (int)((before >> 21) & 0x1fffff),
+        ab = ni + no + (int)(before >> 42);
+    for (int i = 0; i < CPT; ++i) {
+        const int c = c0 + t * CPT + i;
+        if (c >= c1) break;
+        const int4 q = nbr[c];
+        for (int m = 0; m < 3; ++m) {
+            const int k = third(q, m);
+            if (k < 0) {
+                e[ab++] = make_uint2((unsigned)(c - c0) | (kNoCell << 10) | ((unsigned)m << 20) |
+                                         ((unsigned)(-k) << 24), 0u);
+                continue;
+            }
+            const bool in = inside(k), isL = ((unsigned)q.w >> (6 + m)) & 1u;
+            if (in && !isL) continue;
+            const int4 p = nbr[k];
+            const int jb = ((unsigned)q.w >> (2 * m)) & 3;
+            int ca = third(q, (m + 1) % 3), cb = third(q, (m + 2) % 3);
+            int ka = third(p, (jb + 1) % 3), kb = third(p, (jb + 2) % 3);
+            if (ca < 0) ca = cb;
+            if (cb < 0) cb = ca;
+            if (ca < 0) ca = cb = c;
+            if (ka < 0) ka = kb;
+            if (kb < 0) kb = ka;
+            if (ka < 0) ka = kb = k;
+            const unsigned sc = (unsigned)(c - c0), sk = slot(k);
+            unsigned xa = sc, xb = sc, ya = sk, yb = sk;
+            if (ring2) { xa = slot(ca); xb = slot(cb); ya = slot(ka); yb = slot(kb); }
+            const unsigned L = isL ? sc : sk, R = isL ? sk : sc, mL = isL ? m : jb, mR = isL ? jb : m;
+            const unsigned La = isL ? xa : ya, Lb = isL ? xb : yb, Ra = isL ? ya : xa, Rb = isL ? yb : xb;
+            e[in ? ai++ : ao++] = make_uint2(L | (R << 10) | (mL << 20) | (mR << 22) | ((Rb & 255u) << 24),
+                                             La | (Lb << 10) | (Ra << 20) | ((Rb >> 8) << 30));
+        }
+    }
+}
+
+// Geometry of the entries, from the per-half-edge arrays of the mesh
+// (edge-major): the unit normal of L and, where asked for, the MUSCL weights
+// (L's backward and forward, R's backward and forward) and the learned
+// limiter's central weights of L and R.  One block per tile.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_plan_geometry(int n, int TILE, const int4 *desc, const int *halo, const uint2 *ent, int hs, int es,
+                const typename V4<T>::type *he_co, const T *he_gam, typename V2<T>::type *nrm,
+                typename V4<T>::type *wgt, typename V2<T>::type *gam)
+{
+    const int tile = blockIdx.x, c0 = desc[tile].x, nt = (desc[tile].w & 0xffff) + (desc[tile].w >> 16);
+    for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        const size_t at = (size_t)tile * es + i;
+        const unsigned x = ent[at].x;
+        const int L = x & 1023u, R = (x >> 10) & 1023u, mL = (x >> 20) & 3u, mR = (x >> 22) & 3u;
+        const int cL = L < TILE ? c0 + L : halo[(size_t)tile * hs + (L - TILE)];
+        const auto a = he_co[(size_t)mL * n + cL];
+        typename V2<T>::type v;
+        v.x = a.x; v.y = a.y;
+        nrm[at] = v;
+        if (R == (int)kNoCell) continue;
+        const int cR = R < TILE ? c0 + R : halo[(size_t)tile * hs + (R - TILE)];
+        if (wgt) {
+            const auto b = he_co[(size_t)mR * n + cR];
+            typename V4<T>::type w;
+            w.x = a.z; w.y = a.w; w.z = b.z; w.w = b.w;
+            wgt[at] = w;
+        }
+        if (gam) {
+            v.x = he_gam[(size_t)mL * n + cL];
+            v.y = he_gam[(size_t)mR * n + cR];
+            gam[at] = v;
+        }
+    }
+}
+
+}  // namespace swe
