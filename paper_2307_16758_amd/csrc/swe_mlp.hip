@@ -16,7 +16,7 @@
 //    stencils; the target of a half-edge is the mean of the two children of
 //    the coarse cell that touch that edge.
 //  * Training (k_train_partial, k_train_reduce, k_adam): FP32 forward and
-//    backward, per-block gradient partials reduced in a fixed order
+//    backward on the matrix cores, per-block gradient partials reduced in a fixed order
 //    (deterministic), Adam on FP32 master weights, BF16 copies for inference.
 #include <hip/hip_runtime.h>
 
@@ -234,7 +234,24 @@ __global__ void k_pairs(PairArgs<T> a)
 }
 
 // -------------------------------------------------------------- training
-constexpr int kChunk = 64;
+// Forward, backward and gradient sums run on the FP32 matrix cores
+// (v_mfma_f32_16x16x4_f32: FP32 operands, products and sums, as the scalar
+// code this replaced).  A wave takes 16 records at a time.  Layers are computed transposed
+// (units x records): lane (r, q) = (lane & 15, lane >> 4) holds units
+// 16 t + 4 q .. + 3 of record r after each layer, which is the next layer's B
+// operand as it stands when its K steps take the units in that order (step
+// s: unit 4 q + s of lane group q; the weights' A operand is loaded in the
+// same order).  The weight gradients sum over records, so activations and
+// deltas go through the wave's own LDS rows once ([record][unit]) to become
+// operands with K = record.  The lanes of group q evaluate the loss of
+// variable q of their record.  Sums run in a fixed order (records of a wave
+// in order, the waves of a block, then the blocks in k_train_reduce), so
+// results are deterministic.
+// 65,536 records: 136 us with one thread per record in 64 of a block's 256
+// threads, 17 us this way; the matrix work alone is 4 us.
+constexpr int kChunk = 64;  // records of a block at a time: 16 per wave
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // any float address
 
 struct TrainArgs {
     const float *rec;
@@ -245,121 +262,199 @@ struct TrainArgs {
     float *partial;        // [gridDim.x][kMlpParams + 1]
 };
 
-__global__ void __launch_bounds__(256) k_train_partial(TrainArgs a)
+// sum over the 16 lanes with the same lane >> 4, in every one of them
+__device__ __forceinline__ float row_sum(float x)
 {
-    __shared__ float P[kMlpParams];
-    __shared__ float sx[kChunk][kMlpIn], sa1[kChunk][kMlpH], sa2[kChunk][kMlpH];
-    __shared__ float sd1[kChunk][kMlpH], sd2[kChunk][kMlpH], sdz[kChunk], sloss[kChunk];
-    for (int i = threadIdx.x; i < kMlpParams; i += blockDim.x) P[i] = a.params[i];
-    const float *W1 = P, *b1 = P + kMlpH * kMlpIn, *W2 = b1 + kMlpH, *b2 = W2 + kMlpH * kMlpH;
-    const float *W3 = b2 + kMlpH, *b3 = W3 + kMlpH;
-    constexpr int kSlots = (kMlpParams + 255) / 256;
-    float acc[kSlots];
-    for (int i = 0; i < kSlots; ++i) acc[i] = 0.f;
-    float lacc = 0.f;
-    __syncthreads();
-    const int nchunks = (a.n + kChunk - 1) / kChunk;
-    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const int t = threadIdx.x;
-        if (t < kChunk) {
-            const int si = ch * kChunk + t;
-            float a1[kMlpH], a2[kMlpH];
-            const int ri = si < a.n ? a.idx[si] : -1;
-            if (ri >= 0 && ri < a.n_rec) {
-                const float *r = a.rec + (size_t)kRec * ri;
-                float x[kMlpIn];
-                for (int i = 0; i < kMlpIn; ++i) { x[i] = r[i]; sx[t][i] = x[i]; }
-                for (int j = 0; j < kMlpH; ++j) {
-                    float s = b1[j];
-                    for (int i = 0; i < kMlpIn; ++i) s += W1[j * kMlpIn + i] * x[i];
-                    a1[j] = fmaxf(s, 0.f);
-                }
-                for (int j = 0; j < kMlpH; ++j) {
-                    float s = b2[j];
-                    for (int i = 0; i < kMlpH; ++i) s += W2[j * kMlpH + i] * a1[i];
-                    a2[j] = fmaxf(s, 0.f);
-                }
-                float z = b3[0];
-                for (int i = 0; i < kMlpH; ++i) z += W3[i] * a2[i];
-                const float phi = 1.0f / (1.0f + expf(-z));
-                // the value the solver reconstructs with this phi: the
-                // scaled central slope kept in the TVD region of the
-                // backward and forward slopes (no dependence on phi where
-                // the bound or the sign test decides)
-                float dphi = 0.f, loss = 0.f;
-                for (int k = 0; k < 4; ++k) {
-                    const float sc = r[18 + k], sb = r[32 + k], sf = r[36 + k];
-                    const float sp = phi * sc;
-                    const bool pass = sb * sf > 0.f && fabsf(sp) < 2.f * fminf(fabsf(sb), fabsf(sf));
-                    const float cl = sb * sf > 0.f ? copysignf(fminf(fabsf(sp), 2.f * fminf(fabsf(sb), fabsf(sf))), sf)
-                                                   : 0.f;
-                    const float res = r[14 + k] + r[22] * cl - r[23 + k];
-                    loss += a.wv[k] * res * res;
-                    if (pass) dphi += 2.0f * a.wv[k] * res * r[22] * copysignf(fabsf(sc), sf);
-                }
-                const float dz = dphi * phi * (1.0f - phi) / (float)a.n;
-                sdz[t] = dz;
-                sloss[t] = loss;
-                float d2[kMlpH];
-                for (int i = 0; i < kMlpH; ++i) d2[i] = a2[i] > 0.f ? dz * W3[i] : 0.f;
-                for (int i = 0; i < kMlpH; ++i) {
-                    float s = 0.f;
-                    for (int j = 0; j < kMlpH; ++j) s += d2[j] * W2[j * kMlpH + i];
-                    sd1[t][i] = a1[i] > 0.f ? s : 0.f;
-                }
-                for (int i = 0; i < kMlpH; ++i) { sa1[t][i] = a1[i]; sa2[t][i] = a2[i]; sd2[t][i] = d2[i]; }
-            } else {
-                for (int i = 0; i < kMlpIn; ++i) sx[t][i] = 0.f;
-                for (int i = 0; i < kMlpH; ++i) { sa1[t][i] = 0.f; sa2[t][i] = 0.f; sd1[t][i] = 0.f; sd2[t][i] = 0.f; }
-                sdz[t] = 0.f;
-                sloss[t] = 0.f;
-            }
-        }
-        __syncthreads();
-        for (int sl = 0; sl < kSlots; ++sl) {
-            const int p = threadIdx.x + 256 * sl;
-            if (p >= kMlpParams) break;
-            float g = 0.f;
-            if (p < kMlpH * kMlpIn) {
-                const int j = p / kMlpIn, i = p % kMlpIn;
-                for (int s = 0; s < kChunk; ++s) g += sd1[s][j] * sx[s][i];
-            } else if (p < kMlpH * kMlpIn + kMlpH) {
-                const int j = p - kMlpH * kMlpIn;
-                for (int s = 0; s < kChunk; ++s) g += sd1[s][j];
-            } else if (p < kMlpH * kMlpIn + kMlpH + kMlpH * kMlpH) {
-                const int q = p - (kMlpH * kMlpIn + kMlpH), j = q / kMlpH, i = q % kMlpH;
-                for (int s = 0; s < kChunk; ++s) g += sd2[s][j] * sa1[s][i];
-            } else if (p < kMlpH * kMlpIn + 2 * kMlpH + kMlpH * kMlpH) {
-                const int j = p - (kMlpH * kMlpIn + kMlpH + kMlpH * kMlpH);
-                for (int s = 0; s < kChunk; ++s) g += sd2[s][j];
-            } else if (p < kMlpParams - 1) {
-                const int i = p - (kMlpH * kMlpIn + 2 * kMlpH + kMlpH * kMlpH);
-                for (int s = 0; s < kChunk; ++s) g += sdz[s] * sa2[s][i];
-            } else {
-                for (int s = 0; s < kChunk; ++s) g += sdz[s];
-            }
-            acc[sl] += g;
-        }
-        if (threadIdx.x == 0)
-            for (int s = 0; s < kChunk; ++s) lacc += sloss[s];
-        __syncthreads();
-    }
-    float *out = a.partial + (size_t)blockIdx.x * (kMlpParams + 1);
-    for (int sl = 0; sl < kSlots; ++sl) {
-        const int p = threadIdx.x + 256 * sl;
-        if (p < kMlpParams) out[p] = acc[sl];
-    }
-    if (threadIdx.x == 0) out[kMlpParams] = lacc;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) x += __shfl_xor(x, d);
+    return x;
 }
 
-// fixed-order sum of the block partials: grad[p], loss (mean over n)
-__global__ void k_train_reduce(const float *partial, int nblocks, int n, float *grad_loss)
+__global__ void __launch_bounds__(256) k_train_partial(TrainArgs a)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kMlpParams) return;
+    constexpr int kU = 36, kX = 20;              // row strides: unit rows, input rows
+    constexpr int kWave = 16 * (3 * kU + kX);    // floats of one wave's rows
+    static_assert(kWave >= kMlpParams + 1, "the waves' sums reuse the rows");
+    __shared__ __align__(16) float lds[4 * kWave];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
+    float *sA1 = lds + wave * kWave, *sD2 = sA1 + 16 * kU, *sD1 = sD2 + 16 * kU, *sX = sD1 + 16 * kU;
+    const float *W1 = a.params, *b1 = W1 + kMlpH * kMlpIn, *W2 = b1 + kMlpH, *b2 = W2 + kMlpH * kMlpH;
+    const float *W3 = b2 + kMlpH, *b3 = W3 + kMlpH;
+    // weights as operands: w1[t][s] = W1[16 t + r][4 q + s] (inputs 14 and 15
+    // do not exist), w2[t][k][s] = W2[16 t + r][16 k + 4 q + s], and its
+    // transpose w2t[t][k][s] = W2[16 k + 4 q + s][16 t + r]
+    float w1[2][4], w2[2][2][4], w2t[2][2][4], w3[2][4], c1[2][4], c2[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            w1[t][s] = 4 * q + s < kMlpIn ? W1[(16 * t + r) * kMlpIn + 4 * q + s] : 0.f;
+            w3[t][s] = W3[16 * t + 4 * q + s];
+            c1[t][s] = b1[16 * t + 4 * q + s];
+            c2[t][s] = b2[16 * t + 4 * q + s];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                w2[t][k][s] = W2[(16 * t + r) * kMlpH + 16 * k + 4 * q + s];
+                w2t[t][k][s] = W2[(16 * k + 4 * q + s) * kMlpH + 16 * t + r];
+            }
+        }
+    }
+    const float z0 = b3[0], wq = a.wv[q], inv_n = 1.0f / (float)a.n;
+    f4v g2[2][2] = {}, g1[2] = {};           // gradients of W2, of W1 and (input 14) of b1
+    float gb2[2][4] = {}, gw3[2][4] = {}, gb3 = 0.f, loss = 0.f;
+    const int nchunks = (a.n + kChunk - 1) / kChunk;
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        const int si = ch * kChunk + wave * 16 + r;
+        const int ri = si < a.n ? a.idx[si] : -1;
+        const bool have = ri >= 0 && ri < a.n_rec;
+        f4u x = {0.f, 0.f, 0.f, 0.f};
+        float qc = 0.f, sc = 0.f, d = 0.f, tg = 0.f, sb = 0.f, sf = 0.f;
+        if (have) {
+            const float *p = a.rec + (size_t)kRec * ri;
+            x = *(const f4u *)(p + 4 * q);
+            if (q == 3) { x[2] = 1.f; x[3] = 0.f; }  // input 14: one (for b1's gradient); no weight
+            qc = p[14 + q]; sc = p[18 + q]; d = p[22]; tg = p[23 + q]; sb = p[32 + q]; sf = p[36 + q];
+        }
+        *(f4v *)&sX[r * kX + 4 * q] = (f4v){x[0], x[1], x[2], x[3]};
+        // forward
+        f4v a1[2], a2[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f4v acc = {c1[t][0], c1[t][1], c1[t][2], c1[t][3]};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][s], x[s], acc, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) a1[t][s] = fmaxf(acc[s], 0.f);
+            *(f4v *)&sA1[r * kU + 16 * t + 4 * q] = a1[t];
+        }
+        float zp = 0.f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f4v acc = {c2[t][0], c2[t][1], c2[t][2], c2[t][3]};
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[t][k][s], a1[k][s], acc, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                a2[t][s] = fmaxf(acc[s], 0.f);
+                zp += w3[t][s] * a2[t][s];
+            }
+        }
+        zp += __shfl_xor(zp, 16);
+        zp += __shfl_xor(zp, 32);
+        const float phi = 1.0f / (1.0f + expf(-(z0 + zp)));
+        // the value the solver reconstructs with this phi: the scaled central
+        // slope kept in the TVD region of the backward and forward slopes (no
+        // dependence on phi where the bound or the sign test decides)
+        float dphi = 0.f;
+        if (have) {
+            const float sp = phi * sc, lim = 2.f * fminf(fabsf(sb), fabsf(sf));
+            const bool same = sb * sf > 0.f, pass = same && fabsf(sp) < lim;
+            const float cl = same ? copysignf(fminf(fabsf(sp), lim), sf) : 0.f;
+            const float res = qc + d * cl - tg;
+            loss += wq * res * res;
+            if (pass) dphi = 2.0f * wq * res * d * copysignf(fabsf(sc), sf);
+        }
+        dphi += __shfl_xor(dphi, 16);
+        dphi += __shfl_xor(dphi, 32);
+        const float dz = have ? dphi * phi * (1.0f - phi) * inv_n : 0.f;
+        if (q == 0) gb3 += dz;
+        // backward
+        f4v d2[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                d2[t][s] = a2[t][s] > 0.f ? dz * w3[t][s] : 0.f;
+                gb2[t][s] += d2[t][s];
+                gw3[t][s] += dz * a2[t][s];
+            }
+            *(f4v *)&sD2[r * kU + 16 * t + 4 * q] = d2[t];
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f4v acc = {0.f, 0.f, 0.f, 0.f}, d1;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w2t[t][k][s], d2[k][s], acc, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) d1[s] = a1[t][s] > 0.f ? acc[s] : 0.f;
+            *(f4v *)&sD1[r * kU + 16 * t + 4 * q] = d1;
+        }
+        wave_lds_sync();
+        // gradient sums: K = record 4 s + q, lane r: row (unit) or column
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = 4 * s + q;
+            const float xs = sX[k * kX + r];
+            float v2[2], v1[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                v2[t] = sD2[k * kU + 16 * t + r];
+                v1[t] = sA1[k * kU + 16 * t + r];
+                g1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sD1[k * kU + 16 * t + r], xs, g1[t], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    g2[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(v2[t], v1[u], g2[t][u], 0, 0, 0);
+        }
+        wave_lds_sync();  // the rows are rewritten by the next 16 records
+    }
+    // the wave's sums, in parameter order, over its rows
+    __syncthreads();
+    float *out = lds + wave * kWave;
+    const int oB1 = kMlpH * kMlpIn, oW2 = oB1 + kMlpH, oB2 = oW2 + kMlpH * kMlpH, oW3 = oB2 + kMlpH;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int j = 16 * t + 4 * q + s;
+            if (r < kMlpIn) out[j * kMlpIn + r] = g1[t][s];
+            else if (r == kMlpIn) out[oB1 + j] = g1[t][s];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) out[oW2 + j * kMlpH + 16 * u + r] = g2[t][u][s];
+            const float b = row_sum(gb2[t][s]), w = row_sum(gw3[t][s]);
+            if (r == 0) { out[oB2 + j] = b; out[oW3 + j] = w; }
+        }
+    gb3 = row_sum(gb3);
+    loss = row_sum(loss);
+    loss += __shfl_xor(loss, 16);
+    loss += __shfl_xor(loss, 32);
+    if (lane == 0) { out[kMlpParams - 1] = gb3; out[kMlpParams] = loss; }
+    __syncthreads();
+    float *part = a.partial + (size_t)blockIdx.x * (kMlpParams + 1);
+    for (int p = threadIdx.x; p <= kMlpParams; p += 256)
+        part[p] = (lds[p] + lds[kWave + p]) + (lds[2 * kWave + p] + lds[3 * kWave + p]);
+}
+
+// Fixed-order sum of the block partials: grad[p], loss (mean over n).  A
+// block takes 64 parameters; each of its 16 waves sums every 16th partial in
+// double, and the waves' sums are added in order (121 us with one thread per
+// parameter over 512 partials, 4 us this way).  host: page-locked
+// memory of the caller, null if the result stays on the device.
+__global__ void __launch_bounds__(1024) k_train_reduce(const float *partial, int nblocks, int n,
+                                                       float *grad_loss, float *host)
+{
+    __shared__ double sum[16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += partial[(size_t)b * (kMlpParams + 1) + p];
-    grad_loss[p] = p == kMlpParams ? float(s / n) : float(s);
+    if (p <= kMlpParams) {
+#pragma unroll 8
+        for (int b = w; b < nblocks; b += 16) s += partial[(size_t)b * (kMlpParams + 1) + p];
+    }
+    sum[w][lane] = s;
+    __syncthreads();
+    if (w != 0 || p > kMlpParams) return;
+    for (int i = 1; i < 16; ++i) s += sum[i][lane];
+    const float v = p == kMlpParams ? float(s / n) : float(s);
+    grad_loss[p] = v;
+    if (host) host[p] = v;
 }
 
 __global__ void k_adam(float *w, float *m, float *v, const float *grad, int t, float lr, MlpDev *inf)
@@ -407,6 +502,7 @@ struct swe_trainer {
     int dev = 0;
     hipStream_t stream = nullptr;
     float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *partial = nullptr;
+    float *host = nullptr;  // page-locked [kMlpParams + 1]: the last gradient and loss
     MlpDev *inf = nullptr;
     int t = 0, nblocks = kTrainBlocks;
     std::string err;
@@ -518,6 +614,7 @@ int swe_trainer_create(int device, const float *init, swe_trainer **out)
         hipMalloc(&T->w, 4 * P) != hipSuccess || hipMalloc(&T->m, 4 * P) != hipSuccess ||
         hipMalloc(&T->v, 4 * P) != hipSuccess || hipMalloc(&T->grad, 4 * (P + 1)) != hipSuccess ||
         hipMalloc(&T->partial, 4 * (P + 1) * (size_t)T->nblocks) != hipSuccess ||
+        hipHostMalloc((void **)&T->host, 4 * (P + 1), hipHostMallocDefault) != hipSuccess ||
         hipMalloc(&T->inf, sizeof(MlpDev)) != hipSuccess) {
         swe_trainer_destroy(T);
         return SWE_ERR_DEVICE;
@@ -543,6 +640,7 @@ void swe_trainer_destroy(swe_trainer *T)
     if (T->stream) (void)hipStreamSynchronize(T->stream);
     for (float *p : {T->w, T->m, T->v, T->grad, T->partial})
         if (p) (void)hipFree(p);
+    if (T->host) (void)hipHostFree(T->host);
     if (T->inf) (void)hipFree(T->inf);
     if (T->stream) (void)hipStreamDestroy(T->stream);
     delete T;
@@ -553,7 +651,7 @@ void swe_trainer_destroy(swe_trainer *T)
 // it is read, so nothing needs clearing), then a fixed-order reduction
 static int launch_grad(const float *params, const float *rec, int32_t n_rec, const int32_t *idx,
                        int32_t n, const float *wv, float *partial, int nblocks, float *grad_loss,
-                       hipStream_t stream)
+                       float *host, hipStream_t stream)
 {
     TrainArgs a;
     a.rec = rec; a.idx = idx; a.n = n; a.n_rec = n_rec; a.params = params; a.partial = partial;
@@ -561,15 +659,15 @@ static int launch_grad(const float *params, const float *rec, int32_t n_rec, con
     const int nchunks = (n + kChunk - 1) / kChunk;
     const int G = nchunks < nblocks ? nchunks : nblocks;
     hipLaunchKernelGGL(k_train_partial, dim3(G), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(k_train_reduce, dim3((kMlpParams + 1 + 255) / 256), dim3(256), 0, stream,
-                       partial, G, n, grad_loss);
+    hipLaunchKernelGGL(k_train_reduce, dim3((kMlpParams + 1 + 63) / 64), dim3(1024), 0, stream,
+                       partial, G, n, grad_loss, host);
     return hipGetLastError() == hipSuccess ? SWE_OK : SWE_ERR_DEVICE;
 }
 
 static int trainer_grad(swe_trainer *T, const float *rec, int32_t n_rec, const int32_t *idx,
                         int32_t n, const float *wv)
 {
-    return launch_grad(T->w, rec, n_rec, idx, n, wv, T->partial, T->nblocks, T->grad, T->stream);
+    return launch_grad(T->w, rec, n_rec, idx, n, wv, T->partial, T->nblocks, T->grad, T->host, T->stream);
 }
 
 // Device address of `scratch` on the current device, looked up once per
@@ -597,12 +695,9 @@ int swe_trainer_loss_grad(swe_trainer *T, const float *rec, int32_t n_rec, const
     if (hipSetDevice(T->dev) != hipSuccess) return SWE_ERR_DEVICE;
     int rc = trainer_grad(T, rec, n_rec, idx, n, wv);
     if (rc != SWE_OK) return rc;
-    std::vector<float> g(kMlpParams + 1);
-    if (hipMemcpyAsync(g.data(), T->grad, 4 * (kMlpParams + 1), hipMemcpyDeviceToHost, T->stream) != hipSuccess ||
-        hipStreamSynchronize(T->stream) != hipSuccess)
-        return SWE_ERR_DEVICE;
-    *loss = g[kMlpParams];
-    if (grad_host) std::memcpy(grad_host, g.data(), 4 * kMlpParams);
+    if (hipStreamSynchronize(T->stream) != hipSuccess) return SWE_ERR_DEVICE;
+    *loss = T->host[kMlpParams];
+    if (grad_host) std::memcpy(grad_host, T->host, 4 * kMlpParams);
     return SWE_OK;
 }
 
@@ -618,9 +713,8 @@ int swe_trainer_step(swe_trainer *T, const float *rec, int32_t n_rec, const int3
                        T->v, T->grad, T->t, lr, T->inf);
     if (hipGetLastError() != hipSuccess) return SWE_ERR_DEVICE;
     if (loss) {
-        if (hipMemcpyAsync(loss, T->grad + kMlpParams, 4, hipMemcpyDeviceToHost, T->stream) != hipSuccess ||
-            hipStreamSynchronize(T->stream) != hipSuccess)
-            return SWE_ERR_DEVICE;
+        if (hipStreamSynchronize(T->stream) != hipSuccess) return SWE_ERR_DEVICE;
+        *loss = T->host[kMlpParams];
     }
     return SWE_OK;
 }
@@ -637,7 +731,7 @@ int swe_trainer_loss_grad_static(const float *dev_params, const float *dev_rec, 
     int rc = static_scratch_ptr(dev, &partial);
     if (rc != SWE_OK) return rc;
     return launch_grad(dev_params, dev_rec, n_rec, dev_idx, n, wv, partial, kTrainBlocks,
-                       dev_grad_loss, (hipStream_t)stream);
+                       dev_grad_loss, nullptr, (hipStream_t)stream);
 }
 
 int swe_trainer_get_params(swe_trainer *T, float *host_params)
