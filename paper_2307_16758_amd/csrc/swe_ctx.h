@@ -32,7 +32,7 @@ struct swe_ctx {
     int send_prefix = 0;  // the send cells are local cells [0, send_prefix)
     size_t tsize = 4;
     // device buffers
-    void *nbr = nullptr, *cell = nullptr, *man2 = nullptr, *he_geo = nullptr, *he_dist = nullptr;
+    void *nbr = nullptr, *cell = nullptr, *man2 = nullptr, *rad = nullptr, *he_geo = nullptr, *he_dist = nullptr;
     void *he_co = nullptr, *he_lam = nullptr, *he_gam = nullptr;  // tiled kernel's half-edge set
     void *he_dfw = nullptr;     // tiled WAF kernel: centroid distance per half-edge (WAF contexts)
     void *he_nrm = nullptr;     // tiled WAF kernel: unit normal per half-edge (WAF contexts)
@@ -41,17 +41,19 @@ struct swe_ctx {
     void *mlp = nullptr;        // learned-limiter weights (MlpDev, BF16)
     bool has_mlp = false;
     bool phi_stale = false;  // learned limiter: the next step evaluates phi whatever its index
-    unsigned long long *clock = nullptr;  // 3 slots x (1 + ncopy) lines per scenario
+    unsigned long long *clock = nullptr;  // 4 slots x (1 + ncopy) lines per scenario
     int ncopy = 64;
     swe::ScenParams *scen = nullptr;
-    double *ser_t = nullptr, *ser_q = nullptr, *t0 = nullptr;
+    double *ser_t = nullptr, *ser_q = nullptr;
     swe::TilePlan plans[4];  // 64, 128, 256 and 512 cells per tile, built when first needed
     int *health = nullptr, *flag = nullptr, *send_idx = nullptr;
     int *pk_off = nullptr, *pk_ent = nullptr;  // send entries per send cell (CSR)
+    int *host = nullptr;  // page-locked: call number of a refused state, health bits
+    int calls = 1;        // number of the last state set (k_begin_state); 0 and 1 are none's
     // host mirrors
     std::vector<swe::ScenParams> h_scen;
     std::vector<std::pair<std::vector<double>, std::vector<double>>> series;  // per scenario
-    std::vector<double> h_ser_t, h_ser_q, h_t0;
+    std::vector<double> h_ser_t, h_ser_q;
     std::vector<int> scen_off;  // first cell of each scenario, n_scen + 1 entries
     // launch shape: threads per block and blocks of a persistent launch (0:
     // one tile per block); picked by swe_autotune when tuned

@@ -126,10 +126,12 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb)
 using ClockWord = unsigned long long;
 
 // First word of clock slot `slot` of scenario s (the time); copy j of the
-// CFL partials starts kClockLine * (1 + j) words further.
+// CFL partials starts kClockLine * (1 + j) words further.  Slot 3 collects
+// the partials of a state that is being set until it is known to be valid.
+constexpr int kStagingSlot = 3;
 __host__ __device__ inline size_t clock_off(int ncopy, int s, int slot)
 {
-    return (size_t)(3 * s + slot) * (size_t)(ncopy + 1) * kClockLine;
+    return (size_t)(4 * s + slot) * (size_t)(ncopy + 1) * kClockLine;
 }
 
 // The CFL step (Sec. 6.2) from the reduced quantities; dt_max when nothing
@@ -1312,60 +1314,85 @@ __global__ void __launch_bounds__(TILE) k_stage_tiled_waf(StageArgs<T> a)
     }
 }
 
-// CFL minima of the current state into one clock slot (after set_state).
+// A new state: the caller's values into U (null: U holds them already) and
+// its CFL partials into the staging slot, in one pass (the copies, the pack
+// and the CFL pass of a 13M-cell state took 260 us apart; 36 B per cell now,
+// about 100 us).  A negative or non-finite value sets *flag and *host_flag to
+// this call's number.
 template <typename T>
-__global__ void __launch_bounds__(256) k_cfl_init(int n, const int4 *nbr,
-                                                  const typename V4<T>::type *cell,
-                                                  const typename V4<T>::type *U, ClockWord *clock,
-                                                  int ncopy, int slot, int rule, T g, T eps)
+__global__ void __launch_bounds__(256)
+k_begin_state(int n, int n_owned, int n_scen, const int4 *nbr, const T *rad, const T *h, const T *hu,
+              const T *hv, const T *b, typename V4<T>::type *U, ClockWord *clock, int ncopy, int rule,
+              T g, T eps, int *flag, int *host_flag, int call, int *health)
 {
     __shared__ CflVal<T> part[4];
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *health = 0;
     CflVal<T> v = cfl_none<T>();
-    if (c < n) {
-        const unsigned word = (unsigned)nbr[c].w;
-        const T h = U[c].x;
-        if (((word >> kOwnedBit) & 1u) && h > eps) {
-            const T u = fdiv(U[c].y, h), w = fdiv(U[c].z, h);
-            const T lm = sqrt(u * u + w * w) + sqrt(g * h);
-            v = cfl_cell<T>(rule, (int)(word >> kScenShift), cell[c].y, lm);
+    // one scenario: the grid may be smaller than the mesh
+    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
+        typename V4<T>::type u;
+        if (h) {
+            u.x = h[c]; u.y = hu[c]; u.z = hv[c]; u.w = b[c];
+            if (!(isfinite(u.x) && isfinite(u.y) && isfinite(u.z)) || u.x < T(0)) {
+                *flag = call;
+                *host_flag = call;
+            }
+            U[c] = u;
+        } else {
+            u = U[c];
         }
-        v.scen = (int)(word >> kScenShift);
+        v.scen = n_scen == 1 ? 0 : (int)((unsigned)nbr[c].w >> kScenShift);
+        if (c < n_owned && u.x > eps) {
+            const T x = fdiv(u.y, u.x), y = fdiv(u.z, u.x);
+            const CflVal<T> w = cfl_cell<T>(rule, v.scen, rad[c], sqrt(x * x + y * y) + sqrt(g * u.x));
+            v.mn = tmin(v.mn, w.mn);
+            v.mx = tmax(v.mx, w.mx);
+        }
     }
-    cfl_commit(clock, ncopy, slot, rule, v, part);
+    cfl_commit(clock, ncopy, kStagingSlot, rule, v, part);
 }
 
-// Clock slot `slot` of every scenario: partials cleared, time set from t0
-// when set_t.  One thread per (scenario, copy).
-__global__ void k_clock_reset(ClockWord *clock, int ncopy, int n_scen, int slot, const double *t0,
-                              int set_t)
+// The clock of a state that k_begin_state found valid: slot 0 takes the
+// staged partials and the time t, slot 1 is cleared; the staging slot is
+// cleared for the next call either way.  One thread per (scenario, copy).
+__global__ void k_begin_clock(ClockWord *clock, int ncopy, int n_scen, double t, const int *flag, int call)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n_scen * ncopy) return;
     const int s = e / ncopy, j = e % ncopy;
-    ClockWord *q = clock + clock_off(ncopy, s, slot);
-    if (set_t && j == 0) q[0] = dbits(t0[s]);
-    q += (size_t)(1 + j) * kClockLine;
+    const auto at = [&](int slot) { return clock + clock_off(ncopy, s, slot) + (size_t)(1 + j) * kClockLine; };
+    ClockWord *q = at(kStagingSlot);
+    if (*flag != call) {
+        ClockWord *z = at(0), *o = at(1);
+        z[kCfqMin] = q[kCfqMin];
+        z[kCfqMax] = q[kCfqMax];
+        o[kCfqMin] = kInfBits;
+        o[kCfqMax] = 0ull;
+        if (j == 0) clock[clock_off(ncopy, s, 0)] = dbits(t);
+    }
     q[kCfqMin] = kInfBits;
     q[kCfqMax] = 0ull;
 }
 
+// Per-cell values read on their own: inscribed radius and Manning n^2.
 template <typename T>
-__global__ void k_pack_state(int n, const T *h, const T *hu, const T *hv, const T *b,
-                             typename V4<T>::type *U, int *bad, T eps)
+__global__ void k_cell_columns(int n, const typename V4<T>::type *cell, T *rad, T *man2)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
-    typename V4<T>::type u;
-    u.x = h[c]; u.y = hu[c]; u.z = hv[c]; u.w = b[c];
-    if (!(isfinite(u.x) && isfinite(u.y) && isfinite(u.z)) || u.x < T(0)) atomicOr(bad, 1);
-    U[c] = u;
+    const typename V4<T>::type g = cell[c];
+    rad[c] = g.y;
+    man2[c] = g.z;
 }
 
+// The state as three arrays; host (may be null): page-locked, takes the
+// health bits.
 template <typename T>
-__global__ void k_unpack_state(int n, const typename V4<T>::type *U, T *h, T *hu, T *hv)
+__global__ void k_unpack_state(int n, const typename V4<T>::type *U, T *h, T *hu, T *hv,
+                               const int *health, int *host)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c == 0 && host) *host = *health;
     if (c >= n) return;
     const typename V4<T>::type u = U[c];
     h[c] = u.x; hu[c] = u.y; hv[c] = u.z;
@@ -1393,12 +1420,6 @@ __global__ void k_unpack_ghosts(int n_owned, int n_ghost, const T *buf, typename
     typename V4<T>::type u = U[n_owned + i];
     u.x = buf[i]; u.y = buf[n_ghost + i]; u.z = buf[2 * n_ghost + i];
     U[n_owned + i] = u;
-}
-
-__global__ void k_fill_int(int *p, int v, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
 }
 
 }  // namespace
@@ -1438,11 +1459,11 @@ void release_mesh(swe_ctx *c)
 {
     for (TilePlan &p : c->plans) release_plan(c, p);
     if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
-    dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->he_geo); dfree(c, c->he_dist);
+    dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->rad); dfree(c, c->he_geo); dfree(c, c->he_dist);
     dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw); dfree(c, c->he_nrm);
     dfree(c, c->U[0]); dfree(c, c->U[1]); dfree(c, c->U1); dfree(c, c->tmp3); dfree(c, c->bed);
     dfree_t(c, c->phi); dfree_t(c, c->clock); dfree_t(c, c->scen); dfree_t(c, c->ser_t); dfree_t(c, c->ser_q);
-    dfree_t(c, c->t0); dfree_t(c, c->send_idx); dfree_t(c, c->pk_off); dfree_t(c, c->pk_ent);
+    dfree_t(c, c->send_idx); dfree_t(c, c->pk_off); dfree_t(c, c->pk_ent);
     c->has_mesh = c->has_state = false;
 }
 
@@ -1468,12 +1489,11 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
     to_t(g.cell, tmp);
     HIP_OK(c, dalloc(c, (void **)&c->cell, 4 * sizeof(T) * n));
     HIP_OK(c, hipMemcpy(c->cell, tmp.data(), 4 * sizeof(T) * n, hipMemcpyHostToDevice));
-    {
-        std::vector<T> m2(n);
-        for (size_t i = 0; i < n; ++i) m2[i] = tmp[4 * i + 2];
-        HIP_OK(c, dalloc(c, (void **)&c->man2, sizeof(T) * n));
-        HIP_OK(c, hipMemcpy(c->man2, m2.data(), sizeof(T) * n, hipMemcpyHostToDevice));
-    }
+    HIP_OK(c, dalloc(c, &c->man2, sizeof(T) * n));
+    HIP_OK(c, dalloc(c, &c->rad, sizeof(T) * n));
+    hipLaunchKernelGGL(k_cell_columns<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, (int)n,
+                       (const typename V4<T>::type *)c->cell, (T *)c->rad, (T *)c->man2);
+    HIP_OK(c, hipGetLastError());
     to_t(g.he_geo, tmp);
     HIP_OK(c, dalloc(c, (void **)&c->he_geo, 12 * sizeof(T) * n));
     HIP_OK(c, hipMemcpy(c->he_geo, tmp.data(), 12 * sizeof(T) * n, hipMemcpyHostToDevice));
@@ -1954,16 +1974,27 @@ int launch_step_any(swe_ctx *c, long long step, double dt_fixed, bool phi_force 
                                        : launch_step<float>(c, step, dt_fixed, phi_force);
 }
 
+int health_result(swe_ctx *c, int bits);
+
 int health_status(swe_ctx *c)
 {
-    int bits = 0;
-    HIP_OK(c, hipMemcpy(&bits, c->health, sizeof(int), hipMemcpyDeviceToHost));
+    HIP_OK(c, hipMemcpyAsync(c->host + 1, c->health, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_OK(c, hipStreamSynchronize(c->stream));
+    return health_result(c, c->host[1]);
+}
+
+int health_result(swe_ctx *c, int bits)
+{
     if (bits & kHealthNonfinite) return set_err(c, SWE_ERR_NONFINITE, "non-finite value in the state");
     if (bits & kHealthNegDepth) return set_err(c, SWE_ERR_NEGATIVE_DEPTH, "depth below -eps in the state");
     return SWE_OK;
 }
 
 }  // namespace
+
+namespace {
+int begin_state(swe_ctx *c, const void *h, const void *hu, const void *hv, double t, int &bad);
+}
 
 extern "C" {
 
@@ -2040,11 +2071,13 @@ int swe_create(const swe_config *cfg, swe_ctx **out)
         hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
         dalloc(c, (void **)&c->health, sizeof(int)) != hipSuccess ||
         dalloc(c, (void **)&c->flag, sizeof(int)) != hipSuccess ||
+        hipHostMalloc((void **)&c->host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
         hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->dev) != hipSuccess) {
         swe_destroy(c);
         return SWE_ERR_DEVICE;
     }
     (void)hipMemset(c->health, 0, sizeof(int));
+    c->host[0] = c->host[1] = 0;
     *out = c;
     return SWE_OK;
 }
@@ -2058,6 +2091,7 @@ void swe_destroy(swe_ctx *c)
     dfree(c, c->mlp);
     dfree_t(c, c->health);
     dfree_t(c, c->flag);
+    if (c->host) (void)hipHostFree(c->host);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->stream && c->own_stream) (void)hipStreamDestroy(c->stream);
@@ -2161,7 +2195,11 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
     // meet on one, few enough that large batches stay small
     c->ncopy = nm <= 64 ? 16 : (nm <= 1024 ? 8 : 4);
     HIP_OK(c, dalloc(c, (void **)&c->clock, clock_bytes(c)));
-    HIP_OK(c, dalloc(c, (void **)&c->t0, sizeof(double) * (size_t)nm));
+    // the staging slots start cleared (call -1 is no state's)
+    HIP_OK(c, hipMemsetAsync(c->flag, 0xff, sizeof(int), c->stream));
+    hipLaunchKernelGGL(k_begin_clock, dim3((unsigned)((nm * c->ncopy + 255) / 256)), dim3(256), 0, c->stream,
+                       c->clock, c->ncopy, nm, 0.0, c->flag, -1);
+    HIP_OK(c, hipGetLastError());
     {
         std::vector<double> bd(n);
         for (int i = 0; i < nm; ++i) std::copy(ms[i].cell_b, ms[i].cell_b + ms[i].n_total, bd.begin() + off[i]);
@@ -2259,6 +2297,25 @@ int swe_scenario_times(swe_ctx *c, double *t)
     return health_status(c);
 }
 
+// true if p is device (or managed) memory of the context's device; a failed
+// query leaves HIP's last error set, which is cleared here so that the next
+// launch check does not report it
+static bool device_buffer(const swe_ctx *c, const void *p)
+{
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged) && a.device == c->dev;
+}
+
+// ... that a kernel can read or write as the context's values
+static bool kernel_buffer(const swe_ctx *c, const void *p)
+{
+    return (uintptr_t)p % c->tsize == 0 && device_buffer(c, p);
+}
+
 int swe_set_state(swe_ctx *c, const void *h, const void *hu, const void *hv, int where, double t)
 {
     if (!c || !h || !hu || !hv || (where != SWE_HOST && where != SWE_DEVICE))
@@ -2266,67 +2323,66 @@ int swe_set_state(swe_ctx *c, const void *h, const void *hu, const void *hv, int
     if (!c->has_mesh) return set_err(c, SWE_ERR_STATE, "no mesh uploaded");
     HIP_OK(c, hipSetDevice(c->dev));
     const size_t n = c->n_total, ts = c->tsize;
+    const void *src[3] = {h, hu, hv};
     char *tmp = (char *)c->tmp3;
+    // device buffers are read in place; host memory (and whatever else a copy
+    // can read) through the staging buffer
     const hipMemcpyKind kind = where == SWE_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-    HIP_OK(c, hipMemcpyAsync(tmp, h, ts * n, kind, c->stream));
-    HIP_OK(c, hipMemcpyAsync(tmp + ts * n, hu, ts * n, kind, c->stream));
-    HIP_OK(c, hipMemcpyAsync(tmp + 2 * ts * n, hv, ts * n, kind, c->stream));
-    HIP_OK(c, hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-    HIP_OK(c, hipMemsetAsync(c->health, 0, sizeof(int), c->stream));
-    const int B = 256, G = (int)((n + B - 1) / B);
-    if (ts == 8)
-        hipLaunchKernelGGL(k_pack_state<double>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const double *)tmp, (const double *)(tmp + 8 * n),
-                           (const double *)(tmp + 16 * n), (const double *)c->bed,
-                           (double4 *)c->U[0], c->flag, c->cfg.eps);
-    else
-        hipLaunchKernelGGL(k_pack_state<float>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const float *)tmp, (const float *)(tmp + 4 * n),
-                           (const float *)(tmp + 8 * n), (const float *)c->bed, (float4 *)c->U[0],
-                           c->flag, (float)c->cfg.eps);
-    HIP_OK(c, hipGetLastError());
+    for (int i = 0; i < 3; ++i) {
+        if (where == SWE_DEVICE && kernel_buffer(c, src[i])) continue;
+        HIP_OK(c, hipMemcpyAsync(tmp + i * ts * n, src[i], ts * n, kind, c->stream));
+        src[i] = tmp + i * ts * n;
+    }
     int bad = 0;
-    HIP_OK(c, hipMemcpyAsync(&bad, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_OK(c, hipStreamSynchronize(c->stream));
+    const int rc = begin_state(c, src[0], src[1], src[2], t, bad);
+    if (rc != SWE_OK) return rc;
     if (bad) return set_err(c, SWE_ERR_STATE, "state has a negative or non-finite value");
     c->step_count = 0;
-    int rc = init_clock(c, t);
-    if (rc != SWE_OK) return rc;
     c->has_state = true;
     return SWE_OK;
 }
 
 }  // extern "C"
 
+namespace {
+
+// Queue a new state (h null: the state in U[0]) and its clock, and wait.
+int begin_state(swe_ctx *c, const void *h, const void *hu, const void *hv, double t, int &bad)
+{
+    const int n = c->n_total, B = 256;
+    int G = (n + B - 1) / B;
+    if (c->n_scen == 1) G = std::min(G, 8 * std::max(1, c->ncu));  // a block's partials are committed once
+    const int call = ++c->calls;
+    if (c->tsize == 8)
+        hipLaunchKernelGGL(k_begin_state<double>, dim3(G), dim3(B), 0, c->stream, n, c->n_owned, c->n_scen,
+                           (const int4 *)c->nbr, (const double *)c->rad, (const double *)h,
+                           (const double *)hu, (const double *)hv, (const double *)c->bed,
+                           (double4 *)c->U[0], c->clock, c->ncopy, c->cfg.cfl_rule, c->cfg.g, c->cfg.eps,
+                           c->flag, c->host, call, c->health);
+    else
+        hipLaunchKernelGGL(k_begin_state<float>, dim3(G), dim3(B), 0, c->stream, n, c->n_owned, c->n_scen,
+                           (const int4 *)c->nbr, (const float *)c->rad, (const float *)h,
+                           (const float *)hu, (const float *)hv, (const float *)c->bed,
+                           (float4 *)c->U[0], c->clock, c->ncopy, c->cfg.cfl_rule, (float)c->cfg.g,
+                           (float)c->cfg.eps, c->flag, c->host, call, c->health);
+    hipLaunchKernelGGL(k_begin_clock, dim3((c->n_scen * c->ncopy + 255) / 256), dim3(256), 0, c->stream,
+                       c->clock, c->ncopy, c->n_scen, t, c->flag, call);
+    HIP_OK(c, hipGetLastError());
+    HIP_OK(c, hipStreamSynchronize(c->stream));
+    bad = c->host[0] == call;
+    return SWE_OK;
+}
+
+}  // namespace
+
 namespace swe {
 
 int init_clock(swe_ctx *c, double t)
 {
-    const size_t n = c->n_total, ts = c->tsize;
-    const int B = 256, G = (int)((n + B - 1) / B);
-    c->h_t0.assign(c->n_scen, t);
-    HIP_OK(c, hipMemcpyAsync(c->t0, c->h_t0.data(), sizeof(double) * c->n_scen,
-                             hipMemcpyHostToDevice, c->stream));
-    // slot 0: time and CFL minima of the initial state; slot 1 cleared
-    const int gs = (c->n_scen * c->ncopy + 255) / 256;
-    hipLaunchKernelGGL(k_clock_reset, dim3(gs), dim3(256), 0, c->stream, c->clock, c->ncopy, c->n_scen,
-                       0, c->t0, 1);
-    hipLaunchKernelGGL(k_clock_reset, dim3(gs), dim3(256), 0, c->stream, c->clock, c->ncopy, c->n_scen,
-                       1, c->t0, 0);
-    if (ts == 8)
-        hipLaunchKernelGGL(k_cfl_init<double>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const int4 *)c->nbr, (const double4 *)c->cell,
-                           (const double4 *)c->U[0], c->clock, c->ncopy, 0, c->cfg.cfl_rule,
-                           c->cfg.g, c->cfg.eps);
-    else
-        hipLaunchKernelGGL(k_cfl_init<float>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const int4 *)c->nbr, (const float4 *)c->cell, (const float4 *)c->U[0],
-                           c->clock, c->ncopy, 0, c->cfg.cfl_rule, (float)c->cfg.g,
-                           (float)c->cfg.eps);
-    HIP_OK(c, hipGetLastError());
-    HIP_OK(c, hipStreamSynchronize(c->stream));
-    c->has_state = true;
-    return SWE_OK;
+    int bad = 0;
+    const int rc = begin_state(c, nullptr, nullptr, nullptr, t, bad);
+    if (rc == SWE_OK) c->has_state = true;
+    return rc;
 }
 
 }  // namespace swe
@@ -2340,37 +2396,27 @@ int swe_read_state(swe_ctx *c, void *h, void *hu, void *hv, int where)
     if (!c->has_state) return set_err(c, SWE_ERR_STATE, "no state");
     HIP_OK(c, hipSetDevice(c->dev));
     const size_t n = c->n_total, ts = c->tsize;
+    void *dst[3] = {h, hu, hv};
     char *tmp = (char *)c->tmp3;
+    for (int i = 0; i < 3; ++i)  // device buffers are written in place
+        if (where != SWE_DEVICE || !kernel_buffer(c, dst[i])) dst[i] = tmp + i * ts * n;
     const int B = 256, G = (int)((n + B - 1) / B);
     void *Ucur = c->U[c->step_count & 1];
     if (ts == 8)
         hipLaunchKernelGGL(k_unpack_state<double>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const double4 *)Ucur, (double *)tmp, (double *)(tmp + 8 * n),
-                           (double *)(tmp + 16 * n));
+                           (const double4 *)Ucur, (double *)dst[0], (double *)dst[1], (double *)dst[2],
+                           c->health, c->host + 1);
     else
         hipLaunchKernelGGL(k_unpack_state<float>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const float4 *)Ucur, (float *)tmp, (float *)(tmp + 4 * n),
-                           (float *)(tmp + 8 * n));
+                           (const float4 *)Ucur, (float *)dst[0], (float *)dst[1], (float *)dst[2],
+                           c->health, c->host + 1);
     HIP_OK(c, hipGetLastError());
     const hipMemcpyKind kind = where == SWE_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
-    HIP_OK(c, hipMemcpyAsync(h, tmp, ts * n, kind, c->stream));
-    HIP_OK(c, hipMemcpyAsync(hu, tmp + ts * n, ts * n, kind, c->stream));
-    HIP_OK(c, hipMemcpyAsync(hv, tmp + 2 * ts * n, ts * n, kind, c->stream));
+    void *out[3] = {h, hu, hv};
+    for (int i = 0; i < 3; ++i)
+        if (dst[i] != out[i]) HIP_OK(c, hipMemcpyAsync(out[i], dst[i], ts * n, kind, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    return health_status(c);
-}
-
-// true if p is device (or managed) memory of the context's device; a failed
-// query leaves HIP's last error set, which is cleared here so that the next
-// launch check does not report it
-static bool device_buffer(const swe_ctx *c, const void *p)
-{
-    hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged) && a.device == c->dev;
+    return health_result(c, c->host[1]);
 }
 
 int swe_snapshot(swe_ctx *c, void *h, void *hu, void *hv, void *done_event)
@@ -2385,10 +2431,10 @@ int swe_snapshot(swe_ctx *c, void *h, void *hu, void *hv, void *done_event)
     void *Ucur = c->U[c->step_count & 1];
     if (c->tsize == 8)
         hipLaunchKernelGGL(k_unpack_state<double>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const double4 *)Ucur, (double *)h, (double *)hu, (double *)hv);
+                           (const double4 *)Ucur, (double *)h, (double *)hu, (double *)hv, c->health, nullptr);
     else
         hipLaunchKernelGGL(k_unpack_state<float>, dim3(G), dim3(B), 0, c->stream, (int)n,
-                           (const float4 *)Ucur, (float *)h, (float *)hu, (float *)hv);
+                           (const float4 *)Ucur, (float *)h, (float *)hu, (float *)hv, c->health, nullptr);
     HIP_OK(c, hipGetLastError());
     if (done_event) HIP_OK(c, hipEventRecord((hipEvent_t)done_event, c->stream));
     return SWE_OK;
