@@ -332,8 +332,7 @@ template <typename T> struct StageArgs {
     // L / area; d_mid / d_central
     const T4 *he_co;
     const T *he_lam, *he_gam;
-    const T *he_dfw;  // tiled WAF: centroid distance d_fwd per half-edge (edge-major)
-    const typename V2<T>::type *he_nrm;  // tiled WAF: unit normal per half-edge (edge-major)
+    const T *rad;  // inscribed radius per cell (tiled WAF)
     const T4 *Uin, *U0;
     T4 *Uout;
     // tile plan of the tiled kernels (see PlanView)
@@ -343,6 +342,7 @@ template <typename T> struct StageArgs {
     const typename V2<T>::type *tnrm;
     const T4 *twgt;
     const typename V2<T>::type *tgam;
+    const T *tdfw;
     int hs, es, ntiles;
     int n_owned;
     ClockWord *clock;
@@ -737,6 +737,9 @@ constexpr int kLearnedNet = 5;
 #ifndef SWE_TILED_WAVES
 #define SWE_TILED_WAVES 7  // FP32: waves per SIMD the register budget is sized for
 #endif
+#ifndef SWE_WAF_WAVES
+#define SWE_WAF_WAVES 6
+#endif
 #ifndef SWE_TILED_WAVES_LEARNED
 #define SWE_TILED_WAVES_LEARNED 5
 #endif
@@ -1070,212 +1073,187 @@ k_stage_tiled(StageArgs<T> args)
     }
 }
 
-// Tiled WAF stage (Euler).  The tiling of k_stage_tiled with WAF's data:
-//  1. every thread stores, per interior half-edge of its cell, the
-//     first-order interface values (h, b, u_n, u_t in its own edge frame),
-//     the cell's eta and tangential velocity and the mean eta and
-//     tangential velocity of its two upwind cells (WAF's ratios,
-//     Sec. 6.2.2), and files the edge tasks as k_stage_tiled does; the
-//     cell's step goes to LDS too (the Courant numbers need it);
-//  2. one dense sweep over the tasks: hydrostatic reconstruction, WAF in the
-//     canonical orientation (operands selected, one evaluation; an edge
-//     leaving the tile recomputes the far side from its 2-ring), rotation
-//     back, each side's share with its side correction (printed form);
+// Tiled WAF stage (Euler) on the same tile plan:
+//  1. the states and inscribed radii of the tile's cells and of its halo go
+//     to LDS;
+//  2. one thread per edge, in canonical orientation: the first-order states,
+//     hydrostatic reconstruction, WAF with the ratios of Sec. 6.2.2 (eta and
+//     tangential velocity of L, R and of their wet upwind cells' means), the
+//     positivity blend, both cells' shares with their side corrections
+//     (printed form) into LDS;
 //  3. cell sums, update, Manning, cleanup, CFL commit.
-// Tangential velocities taken in a cell's own frame are negated when that
-// frame is opposite to the canonical one (exact), so an edge gets the same
-// operands, and the same flux bits, wherever it is evaluated.
-template <typename T, int WAFM, int TILE>
-__global__ void __launch_bounds__(TILE) k_stage_tiled_waf(StageArgs<T> a)
+// The operands of an edge are the same in whichever tile it is evaluated.
+template <typename T> size_t waf_lds(int tile, int hs)
+{
+    return 5 * sizeof(T) * (size_t)(tile + hs) + 10 * sizeof(T) * (size_t)tile;
+}
+
+template <typename T, int WAFM, int TILE, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? SWE_WAF_WAVES : 2)))
+k_stage_tiled_waf(StageArgs<T> args)
 {
     using T4 = typename V4<T>::type;
-    static_assert(TILE <= 1024, "10-bit tile-local indices in task entries");
-    __shared__ T4 sR[3 * TILE];        // own-frame h, b, u_n, u_t
-    __shared__ T4 sQ[3 * TILE];        // eta, u_t (tangential form) of the cell; same of its upwind mean
-    __shared__ unsigned char sH[3 * TILE];  // the half-edge has an upwind cell
-    __shared__ unsigned sTask[3 * TILE];
-    __shared__ int sK[3 * TILE];
-    __shared__ T sRad[TILE];           // inscribed radius of each cell (positivity)
-    __shared__ T sDt[TILE];
-    __shared__ int sCount[2];
-    __shared__ CflVal<T> sCfl[TILE / 64];
-    clock_upkeep(a);
-    const T g = a.g, eps = a.eps;
-    const int ntiles = (a.n + TILE - 1) / TILE;
-    for (int tile = xcd_tile(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
-        const int c0 = tile * TILE, cl = threadIdx.x, c = c0 + cl;
-        const bool active = c < a.n;
-        if (threadIdx.x < 2) sCount[threadIdx.x] = 0;
-        __syncthreads();
+    using T2 = typename V2<T>::type;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ CflVal<T> sCfl[NT / 64];
+    constexpr bool kWide = NT > TILE;
+    const int hs = args.hs;
+    T4 *const sU = reinterpret_cast<T4 *>(smem);         // h, hu, hv, b per slot
+    T *const sF = reinterpret_cast<T *>(sU + TILE + hs);  // shares, as in k_stage_tiled
+    T *const sRad = sF + 9 * TILE;                        // inscribed radius per slot
+    T *const sDt = sRad + TILE + hs;                      // step per cell where a tile holds several scenarios
+    clock_upkeep(args_again<T>());
+    const T g = args.g, eps = args.eps;
+    const int ntiles = args.ntiles;
+    for (int tv = xcd_tile(blockIdx.x, gridDim.x); tv < ntiles; tv += gridDim.x) {
+        const int tile = __builtin_amdgcn_readfirstlane(tv);
+        const int cl = threadIdx.x;
+        const StageArgs<T> &a = args_again<T>();
         // ---- 1
-        int4 nb4 = make_int4(-1, -1, -1, 0);
-        if (active) nb4 = ldx(a.nbr, c);
-        const DtPrefetch dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur,
-                                           active ? (int)((unsigned)nb4.w >> kScenShift) : -1, a.dt_fixed);
-        T4 Ukeep;
-        T man2 = T(0);
-        const unsigned word = (unsigned)nb4.w;
-        if (active) {
-            const T4 Uc = ldx(a.Uin, c);
-            Ukeep = Uc;
-            const T4 cg = ldx(a.cell, c);
-            sRad[cl] = cg.y;
-            man2 = cg.z;
-            const bool hn0 = nb4.x >= 0, hn1 = nb4.y >= 0, hn2 = nb4.z >= 0;
-            const T4 Un0 = a.Uin[hn0 ? nb4.x : c], Un1 = a.Uin[hn1 ? nb4.y : c], Un2 = a.Uin[hn2 ? nb4.z : c];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int k = m == 0 ? nb4.x : (m == 1 ? nb4.y : nb4.z);
-                sK[m * TILE + cl] = k;
-                const unsigned jb = (word >> (2 * m)) & 3u, isL = (word >> (6 + m)) & 1u;
-                const unsigned ent = (unsigned)m | ((unsigned)cl << 2) | (jb << 12) | (isL << 14);
-                if (k < 0) {
-                    sTask[atomicAdd(&sCount[0], 1)] = ent;
-                    continue;
-                }
-                const int ma = (m + 1) % 3, mb = (m + 2) % 3;
-                const T4 Ua = ma == 0 ? Un0 : (ma == 1 ? Un1 : Un2);
-                const T4 Ub = mb == 0 ? Un0 : (mb == 1 ? Un1 : Un2);
-                const bool ha = ma == 0 ? hn0 : (ma == 1 ? hn1 : hn2);
-                const bool hb = mb == 0 ? hn0 : (mb == 1 ? hn1 : hn2);
-                const auto ge = ldx(a.he_nrm, m * a.n + c);  // unit normal
-                T4 rv;
-                rv.x = Uc.x;
-                rv.y = Uc.w;
-                frame_vel(Uc, ge.x, ge.y, eps, rv.z, rv.w);
-                sR[m * TILE + cl] = rv;
-                T eu, vu;
-                const bool hu = waf_upwind(Ua, ha, Ub, hb, ge.x, ge.y, eps, eu, vu);
-                T4 q;
-                q.x = Uc.x + Uc.w;
-                q.y = tangential(Uc, ge.x, ge.y, eps);
-                q.z = eu;
-                q.w = vu;
-                sQ[m * TILE + cl] = q;
-                sH[m * TILE + cl] = hu ? 1 : 0;
-                const int kl = k - c0;
-                if (kl >= 0 && kl < TILE) {
-                    if (isL) sTask[3 * TILE - 1 - atomicAdd(&sCount[1], 1)] = ent | ((unsigned)kl << 15);
-                } else {
-                    sTask[atomicAdd(&sCount[0], 1)] = ent;
-                }
+        const int *halo = a.thalo + (size_t)tile * a.hs;
+        const uint2 *const ent = a.tent + (size_t)tile * a.es;
+        const T2 *nrm = a.tnrm + (size_t)tile * a.es;
+        const T *dfw = a.tdfw + (size_t)tile * a.es;
+        const int4 d = a.tdesc[tile];
+        const int hj = kWide ? cl - TILE : cl;
+        int hid = -1;
+        if (hj >= 0 && hj < a.hs) hid = ldx(halo, hj);
+        uint2 en = make_uint2(0u, 0u);
+        T2 nn{};
+        T df = T(0);
+        if (cl < a.es) {
+            en = ldx(ent, cl);
+            nn = ldx(nrm, cl);
+            df = ldx(dfw, cl);
+        }
+        const int c0 = d.x, c = c0 + cl, nt = d.w & 0xffff;
+        const bool active = cl < d.y, mixed = a.n_scen > 1 && d.z < 0;
+        int s = -1;
+        if (active) s = a.n_scen == 1 ? 0 : d.z;
+        if (mixed && active) s = (int)((unsigned)a.nbr[c].w >> kScenShift);
+        const DtPrefetch dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur, s, a.dt_fixed);
+        const auto put = [&](int slot, int cell) {
+            sU[slot] = ldx(a.Uin, cell);
+            sRad[slot] = ldx(a.rad, cell);
+        };
+        if (active) put(cl, c);
+        if (hid >= 0) put(TILE + hj, hid);
+        for (int j = hj + NT; j < a.hs; j += NT) {
+            hid = ldx(halo, j);
+            if (hid < 0) break;
+            put(TILE + j, hid);
+        }
+        T lam0 = T(0), lam1 = T(0), lam2 = T(0), man2 = T(0);
+        if (kWide && active) {
+            lam0 = ldx(a.he_lam, c);
+            lam1 = ldx(a.he_lam, a.n + c);
+            lam2 = ldx(a.he_lam, 2 * a.n + c);
+            man2 = ldx(a.man2, c);
+        }
+        double dtd;
+        if (!mixed) {
+            const StageArgs<T> &a = args_again<T>();
+            dtd = lane_value(dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max,
+                                       a.dt_fixed), 0);
+            if (cl == 0) sDt[0] = T(dtd);  // (a wave without cells has read no step)
+        } else {
+            dtd = wave_step_dt(a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
+            if (cl < TILE) sDt[cl] = T(dtd);
+        }
+        __syncthreads();
+        const T dt0 = lane_value(sDt[0], 0);
+        // ---- 2
+        for (int i = cl; i < nt; i += NT) {
+            if (i >= NT) {
+                en = ldx(ent, i);
+                nn = ldx(nrm, i);
+                df = ldx(dfw, i);
+            }
+            const T nx = nn.x, ny = nn.y;
+            const int iL = en.x & 1023u, iR = (en.x >> 10) & 1023u, mL = (en.x >> 20) & 3u,
+                      mR = (en.x >> 22) & 3u;
+            const int iLa = en.y & 1023u, iLb = (en.y >> 10) & 1023u, iRa = (en.y >> 20) & 1023u,
+                      iRb = (en.y >> 30 << 8) | (en.x >> 24);
+            const T4 L = sU[iL], R = sU[iR];
+            const T dtt = mixed ? sDt[iL < TILE ? iL : iR] : dt0;
+            // in L's frame, for both sides
+            T unL, utL, unR, utR;
+            frame_vel(L, nx, ny, eps, unL, utL);
+            frame_vel(R, nx, ny, eps, unR, utR);
+            WafIn<T> w;
+            w.eL = L.x + L.w; w.eR = R.x + R.w;
+            w.vL = tangential(L, nx, ny, eps); w.vR = tangential(R, nx, ny, eps);
+            // a missing upwind cell's place holds the other one, or the cell
+            // itself where both are missing
+            const bool uL = iLa != iL, uR = iRa != iR;
+            w.hasLu = waf_upwind(sU[iLa], uL, sU[iLb], uL, nx, ny, eps, w.eLu, w.vLu);
+            w.hasRu = waf_upwind(sU[iRa], uR, sU[iRb], uR, nx, ny, eps, w.eRu, w.vRu);
+            // hydrostatic reconstruction (first-order states)
+            const T be = tmax(L.w, R.w);
+            const T hL = tmax(T(0), L.x + L.w - be);
+            const T hR = tmax(T(0), R.x + R.w - be);
+            T UL[3], UR[3];
+            UL[0] = hL; UL[1] = hL * unL; UL[2] = hL * utL;
+            UR[0] = hR; UR[1] = hR * unR; UR[2] = hR * utR;
+            T F[3];
+            flux_waf<T, WAFM>(g, eps, fdiv(dtt, df), UL, UR, w, F);
+            if (args_again<T>().waf_pos)
+                waf_positivity(g, eps, UL, UR, L.x, sRad[iL], R.x, sRad[iR], dtt, F);
+            const T G0 = F[0], G1 = F[1] * nx - F[2] * ny, G2 = F[1] * ny + F[2] * nx;
+            if (iL < TILE) {
+                T f0, f1, f2;
+                half_edge_flux(T(1), G0, G1, G2, T(0.5) * g * (L.x * L.x - hL * hL), nx, ny, f0, f1, f2);
+                sF[mL * TILE + iL] = f0;
+                sF[(3 + mL) * TILE + iL] = f1;
+                sF[(6 + mL) * TILE + iL] = f2;
+            }
+            if (iR < TILE) {
+                T f0, f1, f2;
+                half_edge_flux(T(-1), G0, G1, G2, T(0.5) * g * (R.x * R.x - hR * hR), -nx, -ny, f0, f1, f2);
+                sF[mR * TILE + iR] = f0;
+                sF[(3 + mR) * TILE + iR] = f1;
+                sF[(6 + mR) * TILE + iR] = f2;
             }
         }
-        const int s = active ? (int)(word >> kScenShift) : -1;
-        const double dtd = dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl,
-                                     a.dt_max, a.dt_fixed);
-        sDt[cl] = T(dtd);
-        __syncthreads();
-        // ---- 2
-        {
-            const int n0 = sCount[0], nt = n0 + sCount[1];
-            for (int i = threadIdx.x; i < nt; i += TILE) {
-                const bool inside = i >= n0;
-                const unsigned task = inside ? sTask[3 * TILE - 1 - (i - n0)] : sTask[i];
-                const int m = task & 3u, tl = (task >> 2) & 1023u, jb = (task >> 12) & 3u;
-                const bool isL = (task >> 14) & 1u;
-                const int kl = inside ? (int)((task >> 15) & 1023u) : -1;
-                const int tc = c0 + tl;
-                const int k = inside ? c0 + kl : sK[m * TILE + tl];
-                const auto ge = ldx(a.he_nrm, m * a.n + tc);
-                const T nx = ge.x, ny = ge.y;
-                if (k < 0) {  // boundary flux (Sec. 6.1), printed form, global frame
-                    const T4 Ut = ldx(a.Uin, tc);
-                    const int st = (int)((unsigned)ldx(a.nbr, tc).w >> kScenShift);
-                    const ScenParams sp = a.scen[st];
-                    const T q_in = k == kBcInflow
-                                       ? T(inflow_at(sp, a.ser_t, a.ser_q,
-                                                     bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)])) *
-                                           sp.inv_inflow_len)
-                                       : T(0);
-                    T G[3];
-                    boundary_flux<T, T4>(k, Ut, nx, ny, g, eps, q_in, T(sp.outflow_stage), G);
-                    T4 fb;
-                    fb.x = G[0]; fb.y = G[1]; fb.z = G[2]; fb.w = T(0);
-                    sR[m * TILE + tl] = fb;
-                    continue;
-                }
-                const T4 ov = sR[m * TILE + tl], oq = sQ[m * TILE + tl];
-                const bool oh = sH[m * TILE + tl] != 0;
-                T4 kv, kq;
-                bool kh;
-                if (inside) {
-                    kv = sR[jb * TILE + kl];
-                    kq = sQ[jb * TILE + kl];
-                    kh = sH[jb * TILE + kl] != 0;
-                } else {
-                    // far side from its 2-ring, in its own frame (normal -n)
-                    const T4 Uk = ldx(a.Uin, k);
-                    const int4 nk = ldx(a.nbr, k);
-                    const int ka = pick3(nk, (jb + 1) % 3), kb = pick3(nk, (jb + 2) % 3);
-                    const T4 Uka = a.Uin[ka >= 0 ? ka : k], Ukb = a.Uin[kb >= 0 ? kb : k];
-                    kv.x = Uk.x;
-                    kv.y = Uk.w;
-                    frame_vel(Uk, -nx, -ny, eps, kv.z, kv.w);
-                    T eu, vu;
-                    kh = waf_upwind(Uka, ka >= 0, Ukb, kb >= 0, -nx, -ny, eps, eu, vu);
-                    kq.x = Uk.x + Uk.w;
-                    kq.y = tangential(Uk, -nx, -ny, eps);
-                    kq.z = eu;
-                    kq.w = vu;
-                }
-                // hydrostatic reconstruction (first-order states)
-                const T be = tmax(ov.y, kv.y);
-                const T hso = tmax(T(0), ov.x + ov.y - be);
-                const T hsk = tmax(T(0), kv.x + kv.y - be);
-                // canonical orientation: L's own frame is the canonical one,
-                // R's is opposite (its normal and tangential components flip)
-                const T4 &Lv = isL ? ov : kv, &Rv = isL ? kv : ov, &Lq = isL ? oq : kq, &Rq = isL ? kq : oq;
-                const T hL = isL ? hso : hsk, hR = isL ? hsk : hso;
-                T UL[3], UR[3];
-                UL[0] = hL; UL[1] = hL * Lv.z; UL[2] = hL * Lv.w;
-                UR[0] = hR; UR[1] = -(hR * Rv.z); UR[2] = -(hR * Rv.w);
-                WafIn<T> w;
-                w.eL = Lq.x; w.eR = Rq.x;
-                w.vL = Lq.y; w.vR = -Rq.y;
-                w.eLu = Lq.z; w.eRu = Rq.z;
-                w.vLu = Lq.w; w.vRu = -Rq.w;
-                w.hasLu = isL ? oh : kh;
-                w.hasRu = isL ? kh : oh;
-                T F[3];
-                const T dtt = sDt[tl];
-                flux_waf<T, WAFM>(g, eps, fdiv(dtt, ldx(a.he_dfw, m * a.n + tc)), UL, UR, w, F);
-                if (a.waf_pos) {
-                    const T Ro = sRad[tl];
-                    const T Rk = inside ? sRad[kl] : ((const T *)a.cell)[4 * (size_t)k + 1];
-                    waf_positivity(g, eps, UL, UR, Lv.x, isL ? Ro : Rk, Rv.x, isL ? Rk : Ro, dtt, F);
-                }
-                const T sg = isL ? T(1) : T(-1);
-                const T nLx = sg * nx, nLy = sg * ny;
-                const T G0 = F[0], G1 = F[1] * nLx - F[2] * nLy, G2 = F[1] * nLy + F[2] * nLx;
-                T4 fo;
-                half_edge_flux(sg, G0, G1, G2, T(0.5) * g * (ov.x * ov.x - hso * hso), nx, ny, fo.x,
-                               fo.y, fo.z);
-                fo.w = T(0);
-                sR[m * TILE + tl] = fo;
-                if (inside) {
-                    T4 fk;
-                    half_edge_flux(-sg, G0, G1, G2, T(0.5) * g * (kv.x * kv.x - hsk * hsk), -nx, -ny,
-                                   fk.x, fk.y, fk.z);
-                    fk.w = T(0);
-                    sR[jb * TILE + kl] = fk;
-                }
-            }
+        // boundary fluxes (Sec. 6.1), printed form, global frame
+        for (int i = nt + cl; i < nt + (d.w >> 16); i += NT) {
+            const StageArgs<T> &a = args_again<T>();
+            const unsigned e = load_entry<false>(ent, i).x;
+            const int l = e & 1023u, m = (e >> 20) & 3u, k = -(int)(e >> 24);
+            const T2 nb = ldx(nrm, i);
+            const int st = a.n_scen == 1 ? 0 : (d.z >= 0 ? d.z : (int)((unsigned)a.nbr[c0 + l].w >> kScenShift));
+            const ScenParams sp = a.scen[st];
+            const T q_in = k == kBcInflow
+                               ? T(inflow_at(sp, a.ser_t, a.ser_q,
+                                             bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)])) *
+                                   sp.inv_inflow_len)
+                               : T(0);
+            T G[3];
+            boundary_flux<T, T4>(k, sU[l], nb.x, nb.y, g, eps, q_in, T(sp.outflow_stage), G);
+            sF[m * TILE + l] = G[0];
+            sF[(3 + m) * TILE + l] = G[1];
+            sF[(6 + m) * TILE + l] = G[2];
         }
         __syncthreads();
         // ---- 3
+        const StageArgs<T> &b = args_again<T>();
         CflVal<T> cfl = cfl_none<T>();
         if (active) {
-            const T4 Uc = Ukeep;
-            const T dt = sDt[cl];
+            const T4 Uc = sU[cl];
+            const T dt = mixed ? sDt[cl] : dt0;
+            if (!kWide) {
+                lam0 = ldx(b.he_lam, c);
+                lam1 = ldx(b.he_lam, b.n + c);
+                lam2 = ldx(b.he_lam, 2 * b.n + c);
+                man2 = ldx(b.man2, c);
+            }
+            const T lam[3] = {lam0, lam1, lam2};
             T acc0 = T(0), acc1 = T(0), acc2 = T(0);
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-                const T lam = ldx(a.he_lam, m * a.n + c);
-                const T4 f = sR[m * TILE + cl];
-                acc0 += lam * f.x;
-                acc1 += lam * f.y;
-                acc2 += lam * f.z;
+                acc0 += lam[m] * sF[m * TILE + cl];
+                acc1 += lam[m] * sF[(3 + m) * TILE + cl];
+                acc2 += lam[m] * sF[(6 + m) * TILE + cl];
             }
             T nh = Uc.x - dt * acc0;
             T nu = Uc.y - dt * acc1;
@@ -1296,21 +1274,22 @@ __global__ void __launch_bounds__(TILE) k_stage_tiled_waf(StageArgs<T> a)
             }
             T4 out;
             out.x = nh; out.y = nu; out.z = nv; out.w = Uc.w;
-            stx(a.Uout, c, out);
-            pack_own(a, c, nh, nu, nv);
+            stx(b.Uout, c, out);
+            pack_own(b, c, nh, nu, nv);
             // health counts owned cells: a ghost cell's new state is provisional
             // (the next exchange replaces it)
-            if (flags && ((word >> kOwnedBit) & 1u)) atomicOr(a.health, flags);
+            const bool owned = c < b.n_owned;
+            if (flags && owned) atomicOr(b.health, flags);
             cfl.scen = s;
-            if (((word >> kOwnedBit) & 1u) && nh > eps) {
+            if (owned && nh > eps) {
                 const T r = frcp(nh);
                 const T u = nu * r, v = nv * r;
                 const T lm = sqrt(u * u + v * v) + sqrt(g * nh);
-                cfl = cfl_cell<T>(a.cfl_rule, s, sRad[cl], lm);
+                cfl = cfl_cell<T>(b.cfl_rule, s, sRad[cl], lm);
             }
         }
-        cfl_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, cfl, sCfl);
-        if (tile + (int)gridDim.x < ntiles) __syncthreads();
+        cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
+        if (tv + (int)gridDim.x < ntiles) __syncthreads();
     }
 }
 
@@ -1460,7 +1439,7 @@ void release_mesh(swe_ctx *c)
     for (TilePlan &p : c->plans) release_plan(c, p);
     if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
     dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->rad); dfree(c, c->he_geo); dfree(c, c->he_dist);
-    dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw); dfree(c, c->he_nrm);
+    dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw);
     dfree(c, c->U[0]); dfree(c, c->U[1]); dfree(c, c->U1); dfree(c, c->tmp3); dfree(c, c->bed);
     dfree_t(c, c->phi); dfree_t(c, c->clock); dfree_t(c, c->scen); dfree_t(c, c->ser_t); dfree_t(c, c->ser_q);
     dfree_t(c, c->send_idx); dfree_t(c, c->pk_off); dfree_t(c, c->pk_ent);
@@ -1507,11 +1486,10 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
     // edge length over the cell area
     // Stored edge-major (half-edge m of cell c at m * n + c), so that a
     // wave's loads of one local edge are contiguous.
-    // The tiled WAF kernel takes the unit normal and the centroid distance
-    // of its Courant numbers from two more edge-major arrays (WAF contexts
-    // only): it has no use for the MUSCL weights.
+    // WAF's Courant numbers take the centroid distance from one more
+    // edge-major array (WAF contexts only).
     const bool waf = c->cfg.scheme == SWE_WAF;
-    std::vector<T> co(12 * n), lam(3 * n), gam(3 * n), dfw(waf ? 3 * n : 0), nrm(waf ? 6 * n : 0);
+    std::vector<T> co(12 * n), lam(3 * n), gam(3 * n), dfw(waf ? 3 * n : 0);
     for (size_t cc = 0; cc < n; ++cc)
         for (size_t m = 0; m < 3; ++m) {
             const size_t h = 3 * cc + m, e = m * n + cc;
@@ -1522,17 +1500,11 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
             co[4 * e + 3] = T(ge[3] * gd[1]);
             lam[e] = T(ge[2] * g.cell[4 * cc]);
             gam[e] = T(ge[3] * gd[2]);
-            if (waf) {
-                dfw[e] = T(gd[3]);
-                nrm[2 * e] = T(ge[0]);
-                nrm[2 * e + 1] = T(ge[1]);
-            }
+            if (waf) dfw[e] = T(gd[3]);
         }
     if (waf) {
         HIP_OK(c, dalloc(c, (void **)&c->he_dfw, 3 * sizeof(T) * n));
         HIP_OK(c, hipMemcpy(c->he_dfw, dfw.data(), 3 * sizeof(T) * n, hipMemcpyHostToDevice));
-        HIP_OK(c, dalloc(c, (void **)&c->he_nrm, 6 * sizeof(T) * n));
-        HIP_OK(c, hipMemcpy(c->he_nrm, nrm.data(), 6 * sizeof(T) * n, hipMemcpyHostToDevice));
     }
     HIP_OK(c, dalloc(c, (void **)&c->he_co, 12 * sizeof(T) * n));
     HIP_OK(c, hipMemcpy(c->he_co, co.data(), 12 * sizeof(T) * n, hipMemcpyHostToDevice));
@@ -1579,9 +1551,9 @@ template <typename T> void launch_plan_geometry(swe_ctx *c, const TilePlan &p)
 {
     hipLaunchKernelGGL(k_plan_geometry<T>, dim3(p.ntiles), dim3(256), 0, c->stream, c->n_total, p.tile,
                        (const int4 *)p.desc, (const int *)p.halo, (const uint2 *)p.ent, p.hs, p.es,
-                       (const typename V4<T>::type *)c->he_co, (const T *)c->he_gam,
+                       (const typename V4<T>::type *)c->he_co, (const T *)c->he_gam, (const T *)c->he_dfw,
                        (typename V2<T>::type *)p.nrm, (typename V4<T>::type *)p.wgt,
-                       (typename V2<T>::type *)p.gam);
+                       (typename V2<T>::type *)p.gam, (T *)p.dfw);
 }
 
 // The ranges of cells that become tiles: `tile` cells each, a range whose
@@ -1651,14 +1623,15 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out)
         const bool muscl = c->cfg.scheme == SWE_MUSCL;
         const bool learned = muscl && c->cfg.limiter == SWE_LEARNED;
         const size_t nt = q.ntiles, ne = nt * q.es, ts = c->tsize;
-        const size_t sz[6] = {16 * nt, 4 * nt * q.hs, 8 * ne, 2 * ts * ne, muscl ? 4 * ts * ne : 0,
-                              learned ? 2 * ts * ne : 0};
-        size_t off[7] = {0};
-        for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + ((sz[i] + 255) & ~(size_t)255);
-        HIP_OK(c, dalloc(c, &q.mem, off[6]));
+        const bool waf = c->cfg.scheme == SWE_WAF;
+        const size_t sz[7] = {16 * nt, 4 * nt * q.hs, 8 * ne, 2 * ts * ne, muscl ? 4 * ts * ne : 0,
+                              learned ? 2 * ts * ne : 0, waf ? ts * ne : 0};
+        size_t off[8] = {0};
+        for (int i = 0; i < 7; ++i) off[i + 1] = off[i] + ((sz[i] + 255) & ~(size_t)255);
+        HIP_OK(c, dalloc(c, &q.mem, off[7]));
         p = q;  // owned by the context from here on
-        void **at[6] = {&p.desc, &p.halo, &p.ent, &p.nrm, &p.wgt, &p.gam};
-        for (int i = 0; i < 6; ++i) *at[i] = sz[i] ? (char *)p.mem + off[i] : nullptr;
+        void **at[7] = {&p.desc, &p.halo, &p.ent, &p.nrm, &p.wgt, &p.gam, &p.dfw};
+        for (int i = 0; i < 7; ++i) *at[i] = sz[i] ? (char *)p.mem + off[i] : nullptr;
         hipError_t e = hipMemcpyAsync(p.desc, rg.data(), sz[0], hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) {
             launch_plan_any(c, tile, p.ntiles, 1, p.hs, p.es, p.desc, p.halo, p.ent);
@@ -1678,7 +1651,7 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out)
 // The plan a step's launch uses, null for the kernels without one.
 inline bool uses_plan(const swe_ctx *c)
 {
-    return !c->cfg.cell_kernel && c->cfg.scheme != SWE_WAF;
+    return !c->cfg.cell_kernel && (c->cfg.scheme != SWE_WAF || c->cfg.integrator == SWE_EULER);
 }
 
 // Tile and threads of the tiled kernel unless the configuration or the
@@ -1701,6 +1674,7 @@ inline Shape wanted_shape(const swe_ctx *c)
     if (s.tile == 0) s.tile = !few ? 256 : ((long long)n <= 64LL * ncu ? 64 : 128);
     if (c->tsize == 8) s.tile = std::min(s.tile, 256);
     if (c->wide >= 0) s.wide = c->wide != 0;
+    if (c->cfg.scheme == SWE_WAF) s.tile = std::min(s.tile, 256);
     if (s.tile == 512) s.wide = false;
     return s;
 }
@@ -1710,6 +1684,13 @@ int current_plan(swe_ctx *c, TilePlan **out)
     *out = nullptr;
     if (!uses_plan(c)) return SWE_OK;
     return ensure_plan(c, wanted_shape(c).tile, out);
+}
+
+// Bytes of LDS of a launch over a plan.
+template <typename T> size_t plan_lds(const swe_ctx *c, int tile, int hs)
+{
+    if (c->cfg.scheme == SWE_WAF) return waf_lds<T>(tile, hs);
+    return tiled_lds<T>(tile, hs, c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED, false);
 }
 
 // The shape of a launch over this plan.  Eight waves per SIMD where a launch
@@ -1773,21 +1754,23 @@ template <typename T, int TILE, int NT, int OCC> KernelFn<T> pick_tiled(int sche
 
 template <typename T> KernelFn<T> pick_cell_kernel(int scheme, int lim, int wafm);
 
-// Stage kernel of a configuration: the tiled kernel for first-order HLLC and
-// MUSCL (tile = block size 64, 128 or 256), the cell kernel for WAF.
-template <typename T, int TILE> KernelFn<T> pick_tiled_waf(int wafm)
+template <typename T, int TILE, int NT> KernelFn<T> pick_tiled_waf(int wafm)
 {
-    if (wafm == kWafGodunov) return k_stage_tiled_waf<T, kWafGodunov, TILE>;
-    if (wafm == kWafUnlimited) return k_stage_tiled_waf<T, kWafUnlimited, TILE>;
-    return k_stage_tiled_waf<T, kWafSuperbee, TILE>;
+    if (wafm == kWafGodunov) return k_stage_tiled_waf<T, kWafGodunov, TILE, NT>;
+    if (wafm == kWafUnlimited) return k_stage_tiled_waf<T, kWafUnlimited, TILE, NT>;
+    return k_stage_tiled_waf<T, kWafSuperbee, TILE, NT>;
 }
 
+// Stage kernel of a configuration: the tiled kernels, or the
+// one-thread-per-cell kernel (WAF with RK2, and where asked for).
 template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, Shape sh, int cell, bool euler)
 {
     if (scheme == kWAF && !cell && euler) {  // tiled WAF: Euler only (as the paper's WAF)
-        if (sh.tile == 64) return pick_tiled_waf<T, 64>(wafm);
-        if (sh.tile == 128 || sizeof(T) == 8) return pick_tiled_waf<T, 128>(wafm);
-        return pick_tiled_waf<T, 256>(wafm);
+        if (sh.tile == 64)
+            return sh.wide ? pick_tiled_waf<T, 64, tile_threads(64, true)>(wafm) : pick_tiled_waf<T, 64, 64>(wafm);
+        if (sh.tile == 128)
+            return sh.wide ? pick_tiled_waf<T, 128, tile_threads(128, true)>(wafm) : pick_tiled_waf<T, 128, 128>(wafm);
+        return sh.wide ? pick_tiled_waf<T, 256, tile_threads(256, true)>(wafm) : pick_tiled_waf<T, 256, 256>(wafm);
     }
     if (scheme != kWAF && !cell) {
         constexpr int W = SWE_TILED_WAVES;
@@ -1876,8 +1859,7 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     a.he_co = (const T4 *)c->he_co;
     a.he_lam = (const T *)c->he_lam;
     a.he_gam = (const T *)c->he_gam;
-    a.he_dfw = (const T *)c->he_dfw;
-    a.he_nrm = (const typename V2<T>::type *)c->he_nrm;
+    a.rad = (const T *)c->rad;
     a.clock = c->clock;
     a.ncopy = c->ncopy;
     a.scen = c->scen;
@@ -1898,10 +1880,7 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     const bool euler = c->cfg.integrator == SWE_EULER;
     const bool cell_kernel = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool lrn = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
-    // the cell kernel and the WAF tiles stop at 256 cells (FP64 WAF tiles at
-    // 128: LDS)
-    Shape sh{std::min(c->block ? c->block : 256, 256), false, false};
-    if (c->cfg.scheme == SWE_WAF && !cell_kernel && sizeof(T) == 8) sh.tile = std::min(sh.tile, 128);
+    Shape sh{std::min(c->block ? c->block : 256, 256), false, false};  // the cell kernel: at most 256 threads
     TilePlan *plan = nullptr;
     const int prc = current_plan(c, &plan);  // built by the call that uploaded the mesh
     if (prc != SWE_OK) return prc;
@@ -1913,13 +1892,14 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
         a.tnrm = (const typename V2<T>::type *)plan->nrm;
         a.twgt = (const T4 *)plan->wgt;
         a.tgam = (const typename V2<T>::type *)plan->gam;
+        a.tdfw = (const T *)plan->dfw;
         a.hs = plan->hs;
         a.es = plan->es;
         a.ntiles = plan->ntiles;
     }
     const int ntiles = plan ? plan->ntiles : (c->n_total + sh.tile - 1) / sh.tile;
     const int threads = plan ? tile_threads(sh.tile, sh.wide) : sh.tile;
-    const size_t lds = plan ? tiled_lds<T>(sh.tile, plan->hs, lrn, false) : 0;
+    const size_t lds = plan ? plan_lds<T>(c, sh.tile, plan->hs) : 0;
     KernelFn<T> k = pick_kernel<T>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell_kernel, euler);
     dim3 grid(cell_kernel ? ntiles : stage_grid(c, (const void *)k, threads, ntiles, lds));
     const dim3 blk(threads);
@@ -2058,12 +2038,7 @@ int swe_create(const swe_config *cfg, swe_ctx **out)
     c->cfg = *cfg;
     c->dev = cfg->device;
     c->tsize = cfg->precision == SWE_F64 ? 8 : 4;
-    // default tile: chosen by size (wanted_shape), 64 for the FP32 tiled WAF
-    // kernel (its LDS per cell is larger, and smaller tiles keep more of them
-    // in flight)
-    const bool waf_tiled32 = cfg->scheme == SWE_WAF && cfg->integrator == SWE_EULER &&
-                             !cfg->cell_kernel && cfg->precision == SWE_F32;
-    c->block = cfg->block ? cfg->block : (waf_tiled32 ? 64 : 0);
+    c->block = cfg->block;
     c->own_stream = cfg->stream == nullptr;
     if (!c->own_stream) c->stream = (hipStream_t)cfg->stream;
     if (hipSetDevice(c->dev) != hipSuccess ||
@@ -2581,7 +2556,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     const bool learned = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
     for (int B : {64, 128, 256, 512})
     for (int W = 0; W < 3; ++W) {  // a thread per cell, per edge, per cell with eight waves per SIMD
-        if (B == 512 && (!tiled || f64)) continue;  // FP32 tiled kernel only
+        if (B == 512 && (!tiled || f64 || c->cfg.scheme == SWE_WAF)) continue;  // FP32 HLLC1 and MUSCL tiles only
         if (W == 1 && (!tiled || B == 512)) continue;
         if (W == 2 && (!tiled || B != 256 || f64 || learned || c->cfg.scheme != SWE_MUSCL)) continue;
         for (int persist = 0; persist < 2 && rc == SWE_OK; ++persist) {
@@ -2596,8 +2571,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
             if (persist) {
                 const Shape sh{B, W == 1, W == 2};
                 const int threads = plan ? tile_threads(B, sh.wide) : B;
-                const size_t lds = !plan ? 0 : (f64 ? tiled_lds<double>(B, plan->hs, learned, false)
-                                                    : tiled_lds<float>(B, plan->hs, learned, false));
+                const size_t lds = !plan ? 0 : (f64 ? plan_lds<double>(c, B, plan->hs) : plan_lds<float>(c, B, plan->hs));
                 const void *k = f64 ? (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler)
                                     : (const void *)pick_kernel<float>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler);
                 const int res = resident_blocks(c, k, threads, lds);

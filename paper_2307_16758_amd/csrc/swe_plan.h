@@ -211,13 +211,14 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
 
 // Geometry of the entries, from the per-half-edge arrays of the mesh
 // (edge-major): the unit normal of L and, where asked for, the MUSCL weights
-// (L's backward and forward, R's backward and forward) and the learned
-// limiter's central weights of L and R.  One block per tile.
+// (L's backward and forward, R's backward and forward), the learned
+// limiter's central weights of L and R, and WAF's centroid distance.  One
+// block per tile.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_plan_geometry(int n, int TILE, const int4 *desc, const int *halo, const uint2 *ent, int hs, int es,
-                const typename V4<T>::type *he_co, const T *he_gam, typename V2<T>::type *nrm,
-                typename V4<T>::type *wgt, typename V2<T>::type *gam)
+                const typename V4<T>::type *he_co, const T *he_gam, const T *he_dfw,
+                typename V2<T>::type *nrm, typename V4<T>::type *wgt, typename V2<T>::type *gam, T *dfw)
 {
     const int tile = blockIdx.x, c0 = desc[tile].x, nt = (desc[tile].w & 0xffff) + (desc[tile].w >> 16);
     for (int i = threadIdx.x; i < nt; i += blockDim.x) {
@@ -237,6 +238,7 @@ k_plan_geometry(int n, int TILE, const int4 *desc, const int *halo, const uint2 
             w.x = a.z; w.y = a.w; w.z = b.z; w.w = b.w;
             wgt[at] = w;
         }
+        if (dfw) dfw[at] = he_dfw[(size_t)mL * n + cL];
         if (gam) {
             v.x = he_gam[(size_t)mL * n + cL];
             v.y = he_gam[(size_t)mR * n + cR];
