@@ -106,11 +106,9 @@ typedef struct {
     double eps;        /* wet/dry threshold [m], default 1e-6 */
     double dt_max;     /* cap on the CFL step (<= 0: none); step used when no cell is wet */
     int block;         /* cells per tile of the tiled kernels, threads per block of the
-                          one-thread-per-cell kernel: 64, 128, 256 or 512 (0: by size; 64 for
-                          FP32 WAF with explicit Euler on the tiled kernel); the
-                          one-thread-per-cell kernel, FP64 and WAF use at most 256
-                          (FP64 WAF tiles at most 128), and a mesh whose numbering has no
-                          locality gets smaller tiles */
+                          one-thread-per-cell kernel: 64, 128, 256 or 512 (0: by size); the
+                          one-thread-per-cell kernel, FP64 and WAF use at most 256, and a
+                          mesh whose numbering has no locality gets smaller tiles */
     int cell_kernel;   /* 1: one-thread-per-cell stage kernel for every scheme; 0: the
                           tiled kernels (HLLC1, MUSCL, and WAF with Euler steps; WAF with
                           RK2 uses the cell kernel) */
