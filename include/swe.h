@@ -115,11 +115,9 @@ typedef struct {
     void *stream;      /* NULL: the context creates its own stream (default priority,
                           non-blocking); else a hipStream_t on `device`, borrowed: all of
                           the context's work goes to it and it is never destroyed */
-    int waves;         /* FP32 MUSCL tiled kernel with 256-cell tiles and a classic limiter:
-                          register budget it is built for: 6: up to 72 registers (seven
-                          waves per SIMD), 7: up to 64 (eight); 0 (default): 64 when a
-                          launch spans 8 or more rounds of tiles (then a persistent grid of
-                          the blocks the chip holds), else 72.  Same results either way. */
+    int waves;         /* 0, 6 or 7: asked for a register budget of the FP32 tiled kernel;
+                          its one build now needs fewer registers than either, so every
+                          value gives the same kernel. */
     int phi_every;     /* SWE_LEARNED: phi is evaluated on the steps whose index since the
                           last set_state is a multiple of phi_every (1, 2, 3 or 6; 0: every
                           step), and on the first step after swe_limiter_set_weights or
@@ -232,8 +230,7 @@ int swe_scenario_times(swe_ctx *ctx, double *t);  /* [n_scenarios]; syncs */
  * configured stage kernel (64, 128, 256 or, FP32 tiled kernel only, 512
  * cells per tile or threads per block; tiled kernel: a thread per cell or per
  * edge of a tile; one tile per block or a persistent grid of the blocks
- * the chip holds at once; with 256-cell FP32 tiles, both register budgets)
- * from the current state, keeps the fastest and
+ * the chip holds at once) from the current state, keeps the fastest and
  * restores the state, clocks and time.  The choice never changes results
  * (the tiled kernel is bitwise independent of the tiling, and all builds
  * perform the same operations).

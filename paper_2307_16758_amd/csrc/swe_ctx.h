@@ -59,7 +59,6 @@ struct swe_ctx {
     // one tile per block); picked by swe_autotune when tuned
     int grid_persist = 0;
     int wide = -1;  // tiled kernel: a thread per edge (1) or per cell (0), -1 by size
-    int eight = -1; // tiled FP32 kernel, 256-cell tiles: eight waves per SIMD, -1 by size
     int ncu = 0;    // compute units of the device
     bool tuned = false;
     double computed_inflow_len = 0.0, given_inflow_len = 0.0;

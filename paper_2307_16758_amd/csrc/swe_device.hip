@@ -115,6 +115,18 @@ __device__ __forceinline__ void wave_minmax(V &mn, V &mx)
     mx = lane_value(mx, 63);
 }
 
+// Minimum alone over the 64 lanes of the wave, in every lane.
+template <typename V> __device__ __forceinline__ void wave_min(V &mn)
+{
+    mn = vmin(mn, dpp<0xB1>(mn, mn));
+    mn = vmin(mn, dpp<0x4E>(mn, mn));
+    mn = vmin(mn, dpp<0x124>(mn, mn));
+    mn = vmin(mn, dpp<0x128>(mn, mn));
+    mn = vmin(mn, dpp<0x142, 0xA>(mn, mn));
+    mn = vmin(mn, dpp<0x143, 0xC>(mn, mn));
+    mn = lane_value(mn, 63);
+}
+
 __device__ __forceinline__ int xcd_tile(int bid, int nb)
 {
     // blocks are dealt to the 8 XCDs round-robin; give XCD x one contiguous
@@ -173,45 +185,6 @@ __device__ __forceinline__ double wave_step_dt(const ClockWord *clk, int ncopy, 
     return dt;
 }
 
-// The step in two halves, so that the latency of the clock lines (last
-// written by atomics of the previous kernel) hides behind the stencil work:
-// dt_prefetch loads, per lane, copy (lane mod ncopy) of the partials of the
-// scenario of the wave's first cell; dt_finish reduces them when the wave's
-// cells all belong to that scenario and otherwise falls back to
-// wave_step_dt.  Every lane of the wave calls both.
-struct DtPrefetch {
-    double mn, mx;
-    int S;
-};
-
-__device__ __forceinline__ DtPrefetch dt_prefetch(const ClockWord *clk, int ncopy, int slot,
-                                                  int s_own, double dt_fixed)
-{
-    DtPrefetch p;
-    const unsigned long long act = __ballot(s_own >= 0);
-    p.S = act ? lane_value(s_own, __builtin_ctzll(act)) : 0;
-    p.mn = 0.0;
-    p.mx = 0.0;
-    if (dt_fixed <= 0.0 && act != 0ull) {
-        const ClockWord *q = clk + clock_off(ncopy, p.S, slot) +
-                             (size_t)(1 + ((int)threadIdx.x & (ncopy - 1))) * kClockLine;
-        p.mn = bitsd(q[kCfqMin]);
-        p.mx = bitsd(q[kCfqMax]);
-    }
-    return p;
-}
-
-__device__ __forceinline__ double dt_finish(DtPrefetch p, const ClockWord *clk, int ncopy, int slot,
-                                            int s, int rule, double cfl, double dt_max,
-                                            double dt_fixed)
-{
-    if (dt_fixed > 0.0) return dt_fixed;
-    if (__ballot(s >= 0 && s != p.S) != 0ull)
-        return wave_step_dt(clk, ncopy, slot, s, rule, cfl, dt_max, dt_fixed);
-    group_minmax(p.mn, p.mx, ncopy);
-    return s >= 0 ? cfl_dt(p.mn, p.mx, cfl, dt_max, rule) : 0.0;
-}
-
 // The same step as wave_step_dt for one lane on its own (copies reduced in
 // a loop; min and max are exact, so both agree bitwise).  For rare
 // divergent paths.
@@ -262,6 +235,71 @@ __device__ __forceinline__ void cfl_atomic(ClockWord *q, int rule, const CflVal<
 {
     atomicMin(&q[kCfqMin], dbits(double(v.mn)));
     if (rule == 1) atomicMax(&q[kCfqMax], dbits(double(v.mx)));
+}
+
+// The step of scenario S by one wave, in two halves so that the latency of
+// the clock lines (last written by atomics of the previous kernel) hides
+// behind other loads: every lane loads copy (lane mod ncopy) of the partials,
+// one_wave_dt reduces them.  min and max are exact, so it equals wave_step_dt
+// bitwise.
+struct DtLoads {
+    double mn, mx;
+};
+__device__ __forceinline__ DtLoads one_wave_loads(const ClockWord *clk, int ncopy, int slot, int S, double dt_fixed)
+{
+    DtLoads p{0.0, 0.0};
+    if (dt_fixed <= 0.0) {
+        const ClockWord *q =
+            clk + clock_off(ncopy, S, slot) + (size_t)(1 + ((int)threadIdx.x & (ncopy - 1))) * kClockLine;
+        p.mn = bitsd(q[kCfqMin]);
+        p.mx = bitsd(q[kCfqMax]);
+    }
+    return p;
+}
+__device__ __forceinline__ double one_wave_dt(DtLoads p, int ncopy, int rule, double cfl, double dt_max,
+                                              double dt_fixed)
+{
+    if (dt_fixed > 0.0) return dt_fixed;
+    group_minmax(p.mn, p.mx, ncopy);
+    return cfl_dt(p.mn, p.mx, cfl, dt_max, rule);
+}
+
+// One scenario: a wave's CFL quantities reduced into values all its lanes
+// hold (the maximum only where the rule reads it), and the block's commit of
+// what its waves gathered over all their tiles.
+template <typename T> __device__ __forceinline__ void wave_gather(CflVal<T> &acc, CflVal<T> v, int rule)
+{
+    T mn = v.mn, mx = T(0);
+    if (rule == 1) {
+        mx = v.mx;
+        wave_minmax(mn, mx);
+    } else {
+        wave_min(mn);
+    }
+    if constexpr (sizeof(T) == 4) {  // non-negative: as integers, in scalar registers
+        acc.mn = __builtin_bit_cast(T, vmin(__builtin_bit_cast(unsigned, acc.mn), __builtin_bit_cast(unsigned, mn)));
+        acc.mx = __builtin_bit_cast(T, vmax(__builtin_bit_cast(unsigned, acc.mx), __builtin_bit_cast(unsigned, mx)));
+    } else {
+        acc.mn = vmin(acc.mn, mn);
+        acc.mx = vmax(acc.mx, mx);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void gather_commit(ClockWord *clk, int ncopy, int slot, int rule,
+                                              const CflVal<T> &acc, CflVal<T> *part)
+{
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        CflVal<T> r = part[0];
+        for (int w = 1; w < (int)blockDim.x >> 6; ++w) {
+            r.mn = vmin(r.mn, part[w].mn);
+            r.mx = vmax(r.mx, part[w].mx);
+        }
+        if (r.mn < T(__builtin_huge_val()))  // a wet owned cell
+            cfl_atomic(clk + clock_off(ncopy, 0, slot) + (size_t)(1 + (blockIdx.x & (ncopy - 1))) * kClockLine, rule, r);
+    }
 }
 
 // Block-wide reduction of the CFL quantities into clock slot `slot` of each
@@ -731,17 +769,26 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<T> a)
 // removes the rounding of the large cancelling pressure terms (Sec. 6.2.3's
 // side corrections and centred bed term become
 // g (h- + h)(eta- - eta) / 2; hllc_dev gives F1 - g h*^2 / 2 per side).
+//
+// What bounds it: on 13M cells HBM (281 us per stage launch; about 112 B per
+// cell at 5.2 TB/s, a large copy reaches 4.9), on a million cells, whose
+// arrays stay in the Infinity Cache, vector arithmetic and the launch's ends
+// (22 us).  The cell-by-cell form before the plan took 424 and 34 us: each
+// cell's neighbours gathered three times over and five dependent loads per
+// tile.  Edges do not branch on their own state (a wave of dry cells skips
+// the reconstruction as a whole): with divergent early exits 49 instead of
+// 44.6 us per step on a million cells, and 72 registers instead of 62.
 // Learned limiter in the step's first stage: the tiled instance that also
 // evaluates the network and stores phi (the second stage reads it)
 constexpr int kLearnedNet = 5;
 #ifndef SWE_TILED_WAVES
-#define SWE_TILED_WAVES 7  // FP32: waves per SIMD the register budget is sized for
+#define SWE_TILED_WAVES 7  // FP32: waves per SIMD the register budget is sized for (62 registers: eight)
 #endif
 #ifndef SWE_WAF_WAVES
-#define SWE_WAF_WAVES 6  // (the superbee instance needs 71 registers: seven)
+#define SWE_WAF_WAVES 7  // (63 registers: eight)
 #endif
 #ifndef SWE_TILED_WAVES_LEARNED
-#define SWE_TILED_WAVES_LEARNED 5
+#define SWE_TILED_WAVES_LEARNED 7  // (69 registers)
 #endif
 #ifndef SWE_TILED_WAVES_NET
 #define SWE_TILED_WAVES_NET 4  // the instance that also evaluates the network
@@ -786,6 +833,7 @@ k_stage_tiled(StageArgs<T> args)
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool kWide = NT > TILE;
     __shared__ CflVal<T> sCfl[NT / 64];
+    __shared__ double sStep;  // the step, of a tile of one scenario
     // learned limiter: kNet evaluates phi, kLrn reads it; RL is the limiter
     // of the reconstruction
     constexpr bool kNet = MUSCL_ && LIM == kLearnedNet;
@@ -800,6 +848,11 @@ k_stage_tiled(StageArgs<T> args)
     clock_upkeep(args_again<T>());
     const T g = args.g, eps = args.eps;
     const int ntiles = args.ntiles;
+    // the last wave has the fewest edges: it alone finds the step, once per
+    // block where there is one scenario
+    const bool dt_wave = lane_value((int)(threadIdx.x >> 6), 0) == NT / 64 - 1;
+    bool first = true;
+    CflVal<T> acc = cfl_none<T>();  // one scenario: the wave's CFL quantities
     for (int tv = xcd_tile(blockIdx.x, gridDim.x); tv < ntiles; tv += gridDim.x) {
         const int tile = __builtin_amdgcn_readfirstlane(tv);  // uniform: scalar bases
         const int cl = threadIdx.x;
@@ -827,10 +880,9 @@ k_stage_tiled(StageArgs<T> args)
         }
         const int c0 = d.x, c = c0 + cl, nt = d.w & 0xffff;
         const bool active = cl < d.y;
-        int s = -1;
-        if (active) s = a.n_scen == 1 ? 0 : d.z;
-        if (a.n_scen > 1 && d.z < 0 && active) s = (int)((unsigned)a.nbr[c].w >> kScenShift);
-        const DtPrefetch dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur, s, a.dt_fixed);
+        const bool find_dt = dt_wave && (a.n_scen == 1 ? first : d.z >= 0);
+        DtLoads dtl{};
+        if (find_dt) dtl = one_wave_loads(a.clock, a.ncopy, a.slot_cur, a.n_scen == 1 ? 0 : d.z, a.dt_fixed);
         const auto put = [&](int slot, const T4 &U) {
             const Prim<T> p = prim(U, eps);
             T4 v;
@@ -865,21 +917,22 @@ k_stage_tiled(StageArgs<T> args)
             lam2 = ldx(a.he_lam, 2 * a.n + c);
             man2 = ldx(a.man2, c);
         }
-        // the step: one value for the tile but where it holds several scenarios
-        double dtd = 0.0;
-        if (a.n_scen == 1 || d.z >= 0) {
-            const StageArgs<T> &a = args_again<T>();
-            dtd = lane_value(dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max,
-                                       a.dt_fixed), 0);
-        }
         __syncthreads();
+        if (find_dt) {
+            const StageArgs<T> &a = args_again<T>();
+            const double dt = one_wave_dt(dtl, a.ncopy, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
+            if ((threadIdx.x & 63) == 0) sStep = dt;
+        }
+        first = false;
         // ---- 2: edges
         const int iend = kNet ? (nt + 63) & ~63 : nt;  // the network is evaluated by whole waves
         for (int i = cl; i < iend; i += NT) {
             if (i >= NT) {
-                en = load_entry<MUSCL_>(ent, i);
-                nn = ldx(nrm, i);
-                if (MUSCL_) ww = ldx(wgt, i);
+                int j = i;
+                asm("" : "+v"(j));  // offsets from scalar bases, not three 64-bit pointers per lane
+                en = load_entry<MUSCL_>(ent, j);
+                nn = ldx(nrm, j);
+                if (MUSCL_) ww = ldx(wgt, j);
             }
             const uint2 e = en;
             const T nx = nn.x, ny = nn.y;
@@ -944,7 +997,6 @@ k_stage_tiled(StageArgs<T> args)
                 if (RL == kLearned) { const T2 gg = ldx(gam, i); gL = gg.x; gR = gg.y; }
                 const bool wet = L.x > eps && R.x > eps;
                 recon_side<T, RL>(hL, qL, qR, sP[iLa], sP[iLb], wet, nx, ny, w.x, w.y, gL, phL, eps);
-                __builtin_amdgcn_sched_barrier(0);  // R's upwind states after L's side: fewer registers
                 recon_side<T, RL>(hR, qR, qL, sP[iRa], sP[iRb], wet, nx, ny, w.z, w.w, gR, phR, eps);
             }
             // side correction and centred bed term less the cell's
@@ -1003,8 +1055,13 @@ k_stage_tiled(StageArgs<T> args)
         const StageArgs<T> &b = args_again<T>();
         CflVal<T> cfl = cfl_none<T>();
         const bool owned = c < b.n_owned;
-        if (b.n_scen > 1 && d.z < 0)
+        int s = -1;
+        if (active) s = b.n_scen == 1 ? 0 : d.z;
+        double dtd = sStep;
+        if (b.n_scen > 1 && d.z < 0) {
+            if (active) s = (int)((unsigned)b.nbr[c].w >> kScenShift);
             dtd = wave_step_dt(b.clock, b.ncopy, b.slot_cur, s, b.cfl_rule, b.cfl, b.dt_max, b.dt_fixed);
+        }
         if (active) {
             const T4 Pc = sP[cl];  // h and b of the cell (hu and hv: kept)
             const T dt = T(dtd);
@@ -1068,9 +1125,14 @@ k_stage_tiled(StageArgs<T> args)
                 cfl = cfl_cell<T>(b.cfl_rule, s, cg.y, lm);
             }
         }
-        if (b.kind != 1) cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
+        if (b.kind != 1) {
+            if (b.n_scen == 1) wave_gather(acc, cfl, b.cfl_rule);
+            else cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
+        }
         if (tv + (int)gridDim.x < ntiles) __syncthreads();  // LDS is reused by the next tile
     }
+    const StageArgs<T> &a = args_again<T>();
+    if (a.kind != 1 && a.n_scen == 1) gather_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, acc, sCfl);
 }
 
 // Tiled WAF stage (Euler) on the same tile plan:
@@ -1107,9 +1169,13 @@ k_stage_tiled_waf(StageArgs<T> args)
     T *const sF = reinterpret_cast<T *>(sU + TILE + hs);  // shares, as in k_stage_tiled
     T *const sRad = sF + 9 * TILE;                        // inscribed radius per slot
     T *const sDt = sRad + TILE + hs;                      // step per cell where a tile holds several scenarios
+    __shared__ double sStep;                              // otherwise the step
     clock_upkeep(args_again<T>());
     const T g = args.g, eps = args.eps;
     const int ntiles = args.ntiles;
+    const bool dt_wave = lane_value((int)(threadIdx.x >> 6), 0) == NT / 64 - 1;  // finds the step, as in k_stage_tiled
+    bool first = true;
+    CflVal<T> acc = cfl_none<T>();
     for (int tv = xcd_tile(blockIdx.x, gridDim.x); tv < ntiles; tv += gridDim.x) {
         const int tile = __builtin_amdgcn_readfirstlane(tv);
         const int cl = threadIdx.x;
@@ -1136,7 +1202,10 @@ k_stage_tiled_waf(StageArgs<T> args)
         int s = -1;
         if (active) s = a.n_scen == 1 ? 0 : d.z;
         if (mixed && active) s = (int)((unsigned)a.nbr[c].w >> kScenShift);
-        const DtPrefetch dtp = dt_prefetch(a.clock, a.ncopy, a.slot_cur, s, a.dt_fixed);
+        const bool find_dt = dt_wave && (a.n_scen == 1 ? first : !mixed);
+        DtLoads dtl{};
+        if (find_dt) dtl = one_wave_loads(a.clock, a.ncopy, a.slot_cur, a.n_scen == 1 ? 0 : d.z, a.dt_fixed);
+        first = false;
         const auto put = [&](int slot, int cell) {
             sU[slot] = ldx(a.Uin, cell);
             sRad[slot] = ldx(a.rad, cell);
@@ -1155,24 +1224,24 @@ k_stage_tiled_waf(StageArgs<T> args)
             lam2 = ldx(a.he_lam, 2 * a.n + c);
             man2 = ldx(a.man2, c);
         }
-        double dtd;
-        if (!mixed) {
+        if (find_dt) {
             const StageArgs<T> &a = args_again<T>();
-            dtd = lane_value(dt_finish(dtp, a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max,
-                                       a.dt_fixed), 0);
-            if (cl == 0) sDt[0] = T(dtd);  // (a wave without cells has read no step)
-        } else {
-            dtd = wave_step_dt(a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
-            if (cl < TILE) sDt[cl] = T(dtd);
+            const double dt = one_wave_dt(dtl, a.ncopy, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
+            if ((threadIdx.x & 63) == 0) sStep = dt;
+        } else if (mixed) {
+            const double dt = wave_step_dt(a.clock, a.ncopy, a.slot_cur, s, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
+            if (cl < TILE) sDt[cl] = T(dt);
         }
         __syncthreads();
-        const T dt0 = lane_value(sDt[0], 0);
+        const T dt0 = lane_value(T(sStep), 0);
         // ---- 2
         for (int i = cl; i < nt; i += NT) {
             if (i >= NT) {
-                en = ldx(ent, i);
-                nn = ldx(nrm, i);
-                df = ldx(dfw, i);
+                int j = i;
+                asm("" : "+v"(j));  // (as in k_stage_tiled)
+                en = ldx(ent, j);
+                nn = ldx(nrm, j);
+                df = ldx(dfw, j);
             }
             const T nx = nn.x, ny = nn.y;
             const int iL = en.x & 1023u, iR = (en.x >> 10) & 1023u, mL = (en.x >> 20) & 3u,
@@ -1293,9 +1362,12 @@ k_stage_tiled_waf(StageArgs<T> args)
                 cfl = cfl_cell<T>(b.cfl_rule, s, sRad[cl], lm);
             }
         }
-        cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
+        if (b.n_scen == 1) wave_gather(acc, cfl, b.cfl_rule);
+        else cfl_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, cfl, sCfl);
         if (tv + (int)gridDim.x < ntiles) __syncthreads();
     }
+    const StageArgs<T> &a = args_again<T>();
+    if (a.n_scen == 1) gather_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, acc, sCfl);
 }
 
 // A new state: the caller's values into U (null: U holds them already) and
@@ -1520,13 +1592,11 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
     return SWE_OK;
 }
 
-// Launch shape of the tiled kernel: cells per tile, a thread per edge or per
-// cell, and (256 cells, a thread per cell, FP32 with a classic limiter) the
-// register budget: 72 registers for seven waves per SIMD, or 64 for eight,
-// with a few spilled.
+// Launch shape of the tiled kernels: cells per tile, and a thread per edge
+// (wide) or per cell.
 struct Shape {
     int tile;
-    bool wide, eight;
+    bool wide;
 };
 
 // Halo cells a tile of this size may have.  Morton-ordered meshes have halos
@@ -1659,15 +1729,16 @@ inline bool uses_plan(const swe_ctx *c)
     return !c->cfg.cell_kernel && (c->cfg.scheme != SWE_WAF || c->cfg.integrator == SWE_EULER);
 }
 
-// Tile and threads of the tiled kernel unless the configuration or the
+// Tile and threads of the tiled kernels unless the configuration or the
 // autotuner chose them.  While the chip holds every tile at once a launch
 // costs its tiles' chain of latencies: tiles of 128 cells with a thread per
 // edge (per step: 12.3 us against 15.3 with a thread per cell on 20,160 cells
 // MUSCL FP32, 19.5 against 23.1 on 101,202 cells FP64), of 64 cells while
 // there is a compute unit for each (7.3 against 7.6 us on 16,000 cells
 // first-order FP64).  Larger meshes are bound by what the compute units keep
-// in flight: a thread per cell, 256 cells (49 against 60 us on a million
-// cells MUSCL FP32; learned limiter 37.3 against 39.0 on 250,000).
+// in flight: a thread per cell (on a million cells MUSCL FP32 49 against 60
+// us; learned limiter 37.3 against 39.0 on 250,000) and 256 cells (44.6 us
+// against 48.1 and 51.3 in tiles of 128 and 64 cells).
 inline Shape wanted_shape(const swe_ctx *c)
 {
     const int n = c->n_total, ncu = c->ncu > 0 ? c->ncu : 256;
@@ -1675,7 +1746,7 @@ inline Shape wanted_shape(const swe_ctx *c)
     // 4 (FP64, 128 registers)
     const int held = c->tsize == 8 ? 4 : 7;
     const bool few = (long long)n <= 128LL * held * ncu;
-    Shape s{c->block, few, false};
+    Shape s{c->block, few};
     if (s.tile == 0) s.tile = !few ? 256 : ((long long)n <= 64LL * ncu ? 64 : 128);
     if (c->tsize == 8) s.tile = std::min(s.tile, 256);
     if (c->wide >= 0) s.wide = c->wide != 0;
@@ -1696,20 +1767,6 @@ template <typename T> size_t plan_lds(const swe_ctx *c, int tile, int hs)
 {
     if (c->cfg.scheme == SWE_WAF) return waf_lds<T>(tile, hs);
     return tiled_lds<T>(tile, hs, c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED, false);
-}
-
-// The shape of a launch over this plan.  Eight waves per SIMD where a launch
-// spans eight or more rounds of tiles and runs as a persistent grid (589
-// against 604 us per step on the 13M-cell river); on a million cells they are
-// slower (54 against 49 us).
-inline Shape launch_shape(const swe_ctx *c, const TilePlan &p)
-{
-    Shape s = wanted_shape(c);
-    s.tile = p.tile;
-    s.eight = c->grid_persist >= 0 && p.ntiles >= 8LL * 7 * c->ncu;
-    if (c->cfg.waves) s.eight = c->cfg.waves == 7;
-    if (c->eight >= 0) s.eight = c->eight != 0;
-    return s;
 }
 
 int push_scenarios(swe_ctx *c)
@@ -1791,9 +1848,6 @@ template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, Sha
             [[fallthrough]];
         default:
             if (sh.wide) return pick_tiled<T, 256, tile_threads(256, true), W>(scheme, lim);
-            if constexpr (sizeof(T) == 4)
-                if (sh.eight && scheme == kMUSCL && lim != kLearned && lim != kLearnedNet)
-                    return pick_tiled<T, 256, 256, 8>(scheme, lim);
             return pick_tiled<T, 256, 256, W>(scheme, lim);
         }
     }
@@ -1885,12 +1939,13 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     const bool euler = c->cfg.integrator == SWE_EULER;
     const bool cell_kernel = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool lrn = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
-    Shape sh{std::min(c->block ? c->block : 256, 256), false, false};  // the cell kernel: at most 256 threads
+    Shape sh{std::min(c->block ? c->block : 256, 256), false};  // the cell kernel: at most 256 threads
     TilePlan *plan = nullptr;
     const int prc = current_plan(c, &plan);  // built by the call that uploaded the mesh
     if (prc != SWE_OK) return prc;
     if (plan) {
-        sh = launch_shape(c, *plan);
+        sh = wanted_shape(c);
+        sh.tile = plan->tile;
         a.tdesc = (const int4 *)plan->desc;
         a.thalo = (const int *)plan->halo;
         a.tent = (const uint2 *)plan->ent;
@@ -2550,7 +2605,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     const bool graphs = c->use_graphs;
     c->use_graphs = false;
     float best = 1e30f;
-    int best_b = c->block, best_g = c->grid_persist, best_w = c->wide, best_e = c->eight;
+    int best_b = c->block, best_g = c->grid_persist, best_w = c->wide;
     int rc = SWE_OK;
     // only launch shapes of the configured kernel: they give bitwise the same
     // results (the tiled kernel is tiling-independent), the two kernels do not
@@ -2558,23 +2613,20 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     const bool cell = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool tiled = uses_plan(c);
     const bool f64 = c->cfg.precision == SWE_F64;
-    const bool learned = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
     for (int B : {64, 128, 256, 512})
-    for (int W = 0; W < 3; ++W) {  // a thread per cell, per edge, per cell with eight waves per SIMD
+    for (int W = 0; W < 2; ++W) {  // a thread per cell, or per edge
         if (B == 512 && (!tiled || f64 || c->cfg.scheme == SWE_WAF)) continue;  // FP32 HLLC1 and MUSCL tiles only
         if (W == 1 && (!tiled || B == 512)) continue;
-        if (W == 2 && (!tiled || B != 256 || f64 || learned || c->cfg.scheme != SWE_MUSCL)) continue;
         for (int persist = 0; persist < 2 && rc == SWE_OK; ++persist) {
             c->block = B;
             c->wide = W == 1;
-            c->eight = W == 2;
             c->grid_persist = -1;  // one tile per block
             TilePlan *plan = nullptr;
             rc = current_plan(c, &plan);
             if (rc != SWE_OK) break;
             if (plan && plan->tile != B) continue;  // its tiles do not fit: a smaller size stands for it
             if (persist) {
-                const Shape sh{B, W == 1, W == 2};
+                const Shape sh{B, W == 1};
                 const int threads = plan ? tile_threads(B, sh.wide) : B;
                 const size_t lds = !plan ? 0 : (f64 ? plan_lds<double>(c, B, plan->hs) : plan_lds<float>(c, B, plan->hs));
                 const void *k = f64 ? (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler)
@@ -2593,7 +2645,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
             float ms = 0.f;
             rc = swe_last_step_ms(c, &ms);
             if (rc == SWE_OK && ms < best) {
-                best = ms; best_b = B; best_g = c->grid_persist; best_w = c->wide; best_e = c->eight;
+                best = ms; best_b = B; best_g = c->grid_persist; best_w = c->wide;
             }
         }
     }
@@ -2601,7 +2653,6 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     c->block = best_b;
     c->grid_persist = best_g;
     c->wide = best_w;
-    c->eight = best_e;
     {   // the other sizes' plans go
         TilePlan *plan = nullptr;
         const int prc = current_plan(c, &plan);

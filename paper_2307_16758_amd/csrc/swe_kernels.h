@@ -470,36 +470,35 @@ __device__ __forceinline__ void recon_side(Half<T> &r, const T qc[4], const T qk
                                            const T4 &B, bool wet, T nx, T ny, T al, T be, T ga,
                                            float phi, T eps)
 {
-    if (!(wet && A.x > eps && B.x > eps)) return;
+    // a wave without such a half-edge (dry banks) skips the arithmetic; else
+    // no divergent branch: every lane computes, the ineligible ones keep r
+    const bool so = wet && A.x > eps && B.x > eps;
+    if (__ballot(so) == 0ull) return;
     // upwind state: the mean of the upwind cells (rotation is linear, so the
     // mean velocity is rotated once)
     const T uu = T(0.5) * (A.z + B.z), uv = T(0.5) * (A.w + B.w);
     const T qu[4] = {T(0.5) * (A.x + B.x), T(0.5) * ((A.x + A.y) + (B.x + B.y)), uu * nx + uv * ny,
                      -uu * ny + uv * nx};
     T out[4];
-    bool done = false;
-    if (LIM == kLearned) {
-        if (phi >= 0.0f && phi <= 1.0f) {
-            const T p = T(phi);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[i] = qc[i] + tvd_clip(p * (ga * (qk[i] - qu[i])), al * (qc[i] - qu[i]),
-                                          be * (qk[i] - qc[i]));
-            done = out[0] >= T(0);
-        }
-    }
-    if (!done) {
+    for (int i = 0; i < 4; ++i)
+        out[i] = qc[i] + limit2<T, (LIM == kLearned ? kMinmod : LIM)>(al * (qc[i] - qu[i]), be * (qk[i] - qc[i]));
+    if (LIM == kLearned) {
+        T lrn[4];
+        const T p = T(phi);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            out[i] = qc[i] + limit2<T, (LIM == kLearned ? kMinmod : LIM)>(al * (qc[i] - qu[i]),
-                                                                          be * (qk[i] - qc[i]));
+            lrn[i] = qc[i] + tvd_clip(p * (ga * (qk[i] - qu[i])), al * (qc[i] - qu[i]), be * (qk[i] - qc[i]));
+        const bool use = phi >= 0.0f && phi <= 1.0f && lrn[0] >= T(0);  // a NaN fails
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = use ? lrn[i] : out[i];
     }
-    if (out[0] < T(0)) return;
-    r.h = out[0];
-    r.b = out[1] - out[0];
-    r.eta = out[1];
-    r.un = out[2];
-    r.ut = out[3];
+    const bool ok = so && !(out[0] < T(0));
+    r.h = ok ? out[0] : r.h;
+    r.b = ok ? out[1] - out[0] : r.b;
+    r.eta = ok ? out[1] : r.eta;
+    r.un = ok ? out[2] : r.un;
+    r.ut = ok ? out[3] : r.ut;
 }
 
 // HLLC of Sec. 6.2.1 (the estimates of wave_fan) in pressure-deviation
