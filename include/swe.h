@@ -261,11 +261,12 @@ int swe_step(swe_ctx *ctx, int n_steps, double dt_fixed);
  * the step graph.  SWE_ERR_ARG for a missing send buffer when n_send > 0. */
 int swe_step_overlap(swe_ctx *ctx, double dt_fixed, void *dev_sendbuf, void *pack_done_event);
 
-/* Capture and instantiate the launch graph swe_step replays for runs of
+/* Capture and instantiate the launch graphs swe_step replays for runs of
  * steps with this dt_fixed (dt_fixed <= 0: CFL mode), launching nothing, so
  * that a following swe_step pays no capture on the host.  swe_step builds
- * the same graph on first use when this was not called; a graph is rebuilt
- * when dt_fixed or the launch shape changes.  SWE_ERR_STATE without a state
+ * the same graphs on first use when this was not called; a graph is rebuilt
+ * when dt_fixed or the launch shape changes.  Meshes of more than 200,000
+ * cells are stepped without graphs.  SWE_ERR_STATE without a state
  * (or without the network's weights for SWE_LEARNED). */
 int swe_prepare(swe_ctx *ctx, double dt_fixed);
 

@@ -64,8 +64,9 @@ struct swe_ctx {
     double computed_inflow_len = 0.0, given_inflow_len = 0.0;
     long long step_count = 0;  // steps since set_state (selects clock slots and buffers)
     int block = 0;  // cells per tile or threads per block; 0: by size
-    // graphs: chunk of kGraphSteps steps starting at a step index multiple of it
-    hipGraphExec_t graph = nullptr;
+    // graphs: chunks of kGraphSteps and kLongSteps steps starting at a step
+    // index that is a multiple of kGraphSteps
+    hipGraphExec_t graphs[2] = {nullptr, nullptr};
     double graph_dt = -1.0;
     bool use_graphs = true;
 };

@@ -1483,6 +1483,16 @@ __global__ void k_unpack_ghosts(int n_owned, int n_ghost, const T *buf, typename
 namespace {
 
 constexpr int kGraphSteps = 6;  // lcm of the clock-slot (3) and buffer (2) periods
+// Steps of the long graph: between two graphs the stream idles some 5 us,
+// as long as a step of a small mesh (200 steps of 16,000 cells 1267 us in
+// graphs of 24, 1376 in graphs of 6).
+constexpr int kLongSteps = 24;
+// Largest mesh stepped through graphs.  Its launches take about as long as
+// the host needs to queue one (4 us); above, queueing them one by one leaves
+// no gaps at all and no graph to build (12 steps of 250,000 cells, learned
+// limiter: 447 us against 457; of a million cells 569 against 583; but 60
+// steps of 20,160 cells 776 against 730).
+constexpr int kGraphCells = 200000;
 
 int set_err(swe_ctx *c, int code, const std::string &m)
 {
@@ -1511,10 +1521,18 @@ void release_plan(swe_ctx *c, TilePlan &p)
     p = TilePlan{};
 }
 
+void drop_graphs(swe_ctx *c)
+{
+    for (hipGraphExec_t &g : c->graphs) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
+}
+
 void release_mesh(swe_ctx *c)
 {
     for (TilePlan &p : c->plans) release_plan(c, p);
-    if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
+    drop_graphs(c);
     dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->rad); dfree(c, c->he_geo); dfree(c, c->he_dist);
     dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw);
     dfree(c, c->U[0]); dfree(c, c->U[1]); dfree(c, c->U1); dfree(c, c->tmp3); dfree(c, c->bed);
@@ -2103,7 +2121,10 @@ int swe_create(const swe_config *cfg, swe_ctx **out)
     if (!c->own_stream) c->stream = (hipStream_t)cfg->stream;
     if (hipSetDevice(c->dev) != hipSuccess ||
         (c->own_stream && hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) ||
-        hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
+        // they only time the steps: without a fence a record costs the stream
+        // 3 us less (a step and its exchange on a 400k-cell part 44 instead of 47 us)
+        hipEventCreateWithFlags(&c->ev0, hipEventDisableSystemFence) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev1, hipEventDisableSystemFence) != hipSuccess ||
         dalloc(c, (void **)&c->health, sizeof(int)) != hipSuccess ||
         dalloc(c, (void **)&c->flag, sizeof(int)) != hipSuccess ||
         hipHostMalloc((void **)&c->host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
@@ -2302,7 +2323,7 @@ int swe_set_bc_series_scenario(swe_ctx *c, int scen, int n, const double *t, con
     HIP_OK(c, hipStreamSynchronize(c->stream));
     c->series[scen].first.assign(t, t + n);
     c->series[scen].second.assign(q, q + n);
-    if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
+    drop_graphs(c);
     return push_scenarios(c);
 }
 
@@ -2475,26 +2496,30 @@ int swe_snapshot(swe_ctx *c, void *h, void *hu, void *hv, void *done_event)
     return SWE_OK;
 }
 
-// Capture and instantiate the graph of kGraphSteps steps (the period of the
-// clock slots and of the state buffers, so one graph serves every aligned
-// run of steps) for this dt_fixed, unless it exists.  Nothing is launched.
-static int ensure_graph(swe_ctx *c, double dt_fixed)
+// Capture and instantiate the graph of kGraphSteps (which = 0) or kLongSteps
+// steps (whole periods of the clock slots and of the state buffers, so one
+// graph serves every aligned run of steps) for this dt_fixed, unless it
+// exists.  Nothing is launched.
+static int ensure_graph(swe_ctx *c, int which, double dt_fixed)
 {
-    if (c->graph && c->graph_dt == dt_fixed) return SWE_OK;
-    if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
+    if (c->graph_dt != dt_fixed) drop_graphs(c);
+    c->graph_dt = dt_fixed;
+    hipGraphExec_t &graph = c->graphs[which];
+    if (graph) return SWE_OK;
     hipGraph_t gr = nullptr;
     HIP_OK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     int rc = SWE_OK;
-    for (int s = 0; s < kGraphSteps && rc == SWE_OK; ++s) rc = launch_step_any(c, s, dt_fixed);
+    for (int s = 0; s < (which ? kLongSteps : kGraphSteps) && rc == SWE_OK; ++s) rc = launch_step_any(c, s, dt_fixed);
     hipError_t e = hipStreamEndCapture(c->stream, &gr);
     if (rc != SWE_OK) { if (gr) (void)hipGraphDestroy(gr); return rc; }
     if (e != hipSuccess) return set_err(c, SWE_ERR_DEVICE, "graph capture failed");
-    e = hipGraphInstantiate(&c->graph, gr, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&graph, gr, nullptr, nullptr, 0);
     (void)hipGraphDestroy(gr);
-    if (e != hipSuccess) { c->graph = nullptr; return set_err(c, SWE_ERR_DEVICE, "graph instantiation failed"); }
-    c->graph_dt = dt_fixed;
+    if (e != hipSuccess) { graph = nullptr; return set_err(c, SWE_ERR_DEVICE, "graph instantiation failed"); }
     return SWE_OK;
 }
+
+inline bool in_graphs(const swe_ctx *c) { return c->use_graphs && c->n_total <= kGraphCells; }
 
 static int step_ready(swe_ctx *c)
 {
@@ -2525,7 +2550,9 @@ int swe_prepare(swe_ctx *c, double dt_fixed)
     if (rc != SWE_OK) return rc;
     HIP_OK(c, hipSetDevice(c->dev));
     if (!(dt_fixed > 0.0)) dt_fixed = 0.0;
-    return c->use_graphs ? ensure_graph(c, dt_fixed) : SWE_OK;
+    if (!in_graphs(c)) return SWE_OK;
+    const int rc0 = ensure_graph(c, 0, dt_fixed);
+    return rc0 != SWE_OK ? rc0 : ensure_graph(c, 1, dt_fixed);
 }
 
 int swe_step(swe_ctx *c, int n_steps, double dt_fixed)
@@ -2539,13 +2566,16 @@ int swe_step(swe_ctx *c, int n_steps, double dt_fixed)
     int done = 0;
     while (done < n_steps) {
         const bool aligned = (c->step_count % kGraphSteps) == 0;
-        if (c->use_graphs && aligned && n_steps - done >= kGraphSteps) {
-            const int rc = ensure_graph(c, dt_fixed);
+        if (in_graphs(c) && aligned && n_steps - done >= kGraphSteps) {
+            // the long graph is built for a call that replays it at least twice
+            const int which = n_steps - done >= kLongSteps && (c->graphs[1] || n_steps >= 2 * kLongSteps);
+            const int rc = ensure_graph(c, which, dt_fixed);
             if (rc != SWE_OK) return rc;
-            HIP_OK(c, hipGraphLaunch(c->graph, c->stream));
+            HIP_OK(c, hipGraphLaunch(c->graphs[which], c->stream));
             c->phi_stale = false;  // the chunk's first step evaluates phi
-            c->step_count += kGraphSteps;
-            done += kGraphSteps;
+            const int k = which ? kLongSteps : kGraphSteps;
+            c->step_count += k;
+            done += k;
         } else {
             int rc = launch_step_any(c, c->step_count, dt_fixed, c->phi_stale);
             if (rc != SWE_OK) return rc;
@@ -2667,7 +2697,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     c->phi_stale = true;  // phi was overwritten by the candidates' runs
     dfree(c, saveU);
     dfree(c, saveK);
-    if (c->graph) { (void)hipGraphExecDestroy(c->graph); c->graph = nullptr; }
+    drop_graphs(c);
     if (rc != SWE_OK) return rc;
     c->tuned = true;
     if (block_out) *block_out = best_b;
