@@ -519,9 +519,38 @@ template <typename V> __device__ __forceinline__ V ldx(const V *base, unsigned i
 {
     return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + i * (unsigned)sizeof(V));
 }
+// ... with the hint that nothing else will read the line soon (STREAM): the
+// geometry of a mesh that no cache holds then leaves more of the Infinity
+// Cache to the states.
+template <bool STREAM, typename V> __device__ __forceinline__ V ld_stream(const V *base, unsigned i)
+{
+    if constexpr (!STREAM) {
+        return ldx(base, i);
+    } else {
+        typedef float Words __attribute__((ext_vector_type(sizeof(V) / 4)));
+        const Words w = __builtin_nontemporal_load(
+            reinterpret_cast<const Words *>(reinterpret_cast<const char *>(base) + i * (unsigned)sizeof(V)));
+        V v;
+        __builtin_memcpy(&v, &w, sizeof(V));
+        return v;
+    }
+}
 template <typename V> __device__ __forceinline__ void stx(V *base, unsigned i, const V &v)
 {
     *reinterpret_cast<V *>(reinterpret_cast<char *>(base) + i * (unsigned)sizeof(V)) = v;
+}
+
+// Manning n^2 of cell c in a tile of scenario st (-1: several): one value
+// where all of the scenario's cells share it, which saves 4 of 112 bytes per
+// cell and stage.
+template <typename T> __device__ __forceinline__ T manning(const StageArgs<T> &a, int st, int c)
+{
+    if (a.n_scen == 1) st = 0;
+    if (st >= 0) {
+        const double m = a.scen[st].man2;
+        if (m >= 0.0) return T(m);
+    }
+    return ldx(a.man2, c);
 }
 
 // Component m (0..2) of an int4 by selects (no local array: a dynamically
@@ -821,10 +850,10 @@ template <bool TWO> __device__ __forceinline__ uint2 load_entry(const uint2 *e, 
     return make_uint2(ldx(reinterpret_cast<const unsigned *>(e), 2 * i), 0u);
 }
 
-template <typename T, bool MUSCL_, int LIM, int TILE, int NT, int OCC = SWE_TILED_WAVES>
+template <typename T, bool MUSCL_, int LIM, int TILE, int NT, bool STREAM = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 ? (LIM == kLearned ? SWE_TILED_WAVES_LEARNED
-                                      : (LIM == kLearnedNet ? SWE_TILED_WAVES_NET : OCC))
+                                      : (LIM == kLearnedNet ? SWE_TILED_WAVES_NET : SWE_TILED_WAVES))
                    : 2)))
 k_stage_tiled(StageArgs<T> args)
 {
@@ -875,8 +904,8 @@ k_stage_tiled(StageArgs<T> args)
         T4 ww{};
         if (cl < a.es) {
             en = load_entry<MUSCL_>(ent, cl);
-            nn = ldx(nrm, cl);
-            if (MUSCL_) ww = ldx(wgt, cl);
+            nn = ld_stream<STREAM>(nrm, cl);
+            if (MUSCL_) ww = ld_stream<STREAM>(wgt, cl);
         }
         const int c0 = d.x, c = c0 + cl, nt = d.w & 0xffff;
         const bool active = cl < d.y;
@@ -915,7 +944,7 @@ k_stage_tiled(StageArgs<T> args)
             lam0 = ldx(a.he_lam, c);
             lam1 = ldx(a.he_lam, a.n + c);
             lam2 = ldx(a.he_lam, 2 * a.n + c);
-            man2 = ldx(a.man2, c);
+            man2 = manning(a, d.z, c);
         }
         __syncthreads();
         if (find_dt) {
@@ -931,8 +960,8 @@ k_stage_tiled(StageArgs<T> args)
                 int j = i;
                 asm("" : "+v"(j));  // offsets from scalar bases, not three 64-bit pointers per lane
                 en = load_entry<MUSCL_>(ent, j);
-                nn = ldx(nrm, j);
-                if (MUSCL_) ww = ldx(wgt, j);
+                nn = ld_stream<STREAM>(nrm, j);
+                if (MUSCL_) ww = ld_stream<STREAM>(wgt, j);
             }
             const uint2 e = en;
             const T nx = nn.x, ny = nn.y;
@@ -1031,7 +1060,7 @@ k_stage_tiled(StageArgs<T> args)
             const StageArgs<T> &a = args_again<T>();
             const unsigned e = load_entry<false>(ent, i).x;
             const int l = e & 1023u, m = (e >> 20) & 3u, k = -(int)(e >> 24);
-            const T2 nb = ldx(nrm, i);
+            const T2 nb = ld_stream<STREAM>(nrm, i);
             const T4 Ub = ldx(a.Uin, c0 + l);
             const int st = a.n_scen == 1 ? 0 : (d.z >= 0 ? d.z : (int)((unsigned)a.nbr[c0 + l].w >> kScenShift));
             const ScenParams sp = a.scen[st];
@@ -1066,10 +1095,10 @@ k_stage_tiled(StageArgs<T> args)
             const T4 Pc = sP[cl];  // h and b of the cell (hu and hv: kept)
             const T dt = T(dtd);
             if (!kWide) {
-                lam0 = ldx(b.he_lam, c);
-                lam1 = ldx(b.he_lam, b.n + c);
-                lam2 = ldx(b.he_lam, 2 * b.n + c);
-                man2 = ldx(b.man2, c);
+                lam0 = ld_stream<STREAM>(b.he_lam, c);
+                lam1 = ld_stream<STREAM>(b.he_lam, b.n + c);
+                lam2 = ld_stream<STREAM>(b.he_lam, 2 * b.n + c);
+                man2 = manning(b, d.z, c);
             }
             const T lam[3] = {lam0, lam1, lam2};
             T acc0 = T(0), acc1 = T(0), acc2 = T(0), lsum = T(0);
@@ -1222,7 +1251,7 @@ k_stage_tiled_waf(StageArgs<T> args)
             lam0 = ldx(a.he_lam, c);
             lam1 = ldx(a.he_lam, a.n + c);
             lam2 = ldx(a.he_lam, 2 * a.n + c);
-            man2 = ldx(a.man2, c);
+            man2 = manning(a, d.z, c);
         }
         if (find_dt) {
             const StageArgs<T> &a = args_again<T>();
@@ -1319,7 +1348,7 @@ k_stage_tiled_waf(StageArgs<T> args)
                 lam0 = ldx(b.he_lam, c);
                 lam1 = ldx(b.he_lam, b.n + c);
                 lam2 = ldx(b.he_lam, 2 * b.n + c);
-                man2 = ldx(b.man2, c);
+                man2 = manning(b, d.z, c);
             }
             const T lam[3] = {lam0, lam1, lam2};
             T acc0 = T(0), acc1 = T(0), acc2 = T(0);
@@ -1615,6 +1644,7 @@ int upload_geometry(swe_ctx *c, const HostGeometry &g)
 struct Shape {
     int tile;
     bool wide;
+    bool stream = false;  // geometry loaded as a stream (256 cells, a thread per cell)
 };
 
 // Halo cells a tile of this size may have.  Morton-ordered meshes have halos
@@ -1757,6 +1787,14 @@ inline bool uses_plan(const swe_ctx *c)
 // in flight: a thread per cell (on a million cells MUSCL FP32 49 against 60
 // us; learned limiter 37.3 against 39.0 on 250,000) and 256 cells (44.6 us
 // against 48.1 and 51.3 in tiles of 128 and 64 cells).
+//
+// Geometry loaded as a stream where a step's arrays are beyond what the 256 MB
+// Infinity Cache holds most of, so that it holds the states (per step, plain
+// and as a stream: 4M cells MUSCL FP32, 460 MB: 180 and 147 us; 13M 550 and
+// 536; 1.6M FP64, 344 MB: 145 and 140); below, the stream gives up what the
+// cache would have kept (2.3M FP32, 265 MB: 84 and 94 us; 1M: 45 and 48).
+constexpr long long kCachedBytes = 300LL << 20;
+
 inline Shape wanted_shape(const swe_ctx *c)
 {
     const int n = c->n_total, ncu = c->ncu > 0 ? c->ncu : 256;
@@ -1770,6 +1808,11 @@ inline Shape wanted_shape(const swe_ctx *c)
     if (c->wide >= 0) s.wide = c->wide != 0;
     if (c->cfg.scheme == SWE_WAF) s.tile = std::min(s.tile, 256);
     if (s.tile == 512) s.wide = false;
+    // what a step reads and writes per cell: the state's buffers, entries,
+    // normals, edge weights over area and, for MUSCL, the slope weights
+    const long long per_cell = c->cfg.scheme == SWE_MUSCL ? 15 + 25LL * (long long)c->tsize
+                                                          : 15 + 14LL * (long long)c->tsize;
+    s.stream = !s.wide && s.tile == 256 && c->cfg.scheme != SWE_WAF && n * per_cell > kCachedBytes;
     return s;
 }
 
@@ -1819,16 +1862,16 @@ int push_scenarios(swe_ctx *c)
 
 template <typename T> using KernelFn = void (*)(StageArgs<T>);
 
-template <typename T, int TILE, int NT, int OCC> KernelFn<T> pick_tiled(int scheme, int lim)
+template <typename T, int TILE, int NT, bool STREAM = false> KernelFn<T> pick_tiled(int scheme, int lim)
 {
-    if (scheme == kHLLC1) return k_stage_tiled<T, false, kMinmod, TILE, NT, OCC>;
+    if (scheme == kHLLC1) return k_stage_tiled<T, false, kMinmod, TILE, NT, STREAM>;
     switch (lim) {
-    case kSuperbee: return k_stage_tiled<T, true, kSuperbee, TILE, NT, OCC>;
-    case kVanAlbada: return k_stage_tiled<T, true, kVanAlbada, TILE, NT, OCC>;
-    case kLearned: return k_stage_tiled<T, true, kLearned, TILE, NT>;
+    case kSuperbee: return k_stage_tiled<T, true, kSuperbee, TILE, NT, STREAM>;
+    case kVanAlbada: return k_stage_tiled<T, true, kVanAlbada, TILE, NT, STREAM>;
+    case kLearned: return k_stage_tiled<T, true, kLearned, TILE, NT, STREAM>;
     case kLearnedNet: return k_stage_tiled<T, true, kLearnedNet, TILE, NT>;
-    case kZeroSlope: return k_stage_tiled<T, true, kZeroSlope, TILE, NT, OCC>;
-    default: return k_stage_tiled<T, true, kMinmod, TILE, NT, OCC>;
+    case kZeroSlope: return k_stage_tiled<T, true, kZeroSlope, TILE, NT, STREAM>;
+    default: return k_stage_tiled<T, true, kMinmod, TILE, NT, STREAM>;
     }
 }
 
@@ -1853,20 +1896,19 @@ template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, Sha
         return sh.wide ? pick_tiled_waf<T, 256, tile_threads(256, true)>(wafm) : pick_tiled_waf<T, 256, 256>(wafm);
     }
     if (scheme != kWAF && !cell) {
-        constexpr int W = SWE_TILED_WAVES;
         switch (sh.tile) {
         case 64:
-            return sh.wide ? pick_tiled<T, 64, tile_threads(64, true), W>(scheme, lim)
-                           : pick_tiled<T, 64, 64, W>(scheme, lim);
+            return sh.wide ? pick_tiled<T, 64, tile_threads(64, true)>(scheme, lim) : pick_tiled<T, 64, 64>(scheme, lim);
         case 128:
-            return sh.wide ? pick_tiled<T, 128, tile_threads(128, true), W>(scheme, lim)
-                           : pick_tiled<T, 128, 128, W>(scheme, lim);
+            return sh.wide ? pick_tiled<T, 128, tile_threads(128, true)>(scheme, lim)
+                           : pick_tiled<T, 128, 128>(scheme, lim);
         case 512:
-            if constexpr (sizeof(T) == 4) return pick_tiled<T, 512, 512, W>(scheme, lim);
+            if constexpr (sizeof(T) == 4)
+                return pick_tiled<T, 512, 512>(scheme, lim);
             [[fallthrough]];
         default:
-            if (sh.wide) return pick_tiled<T, 256, tile_threads(256, true), W>(scheme, lim);
-            return pick_tiled<T, 256, 256, W>(scheme, lim);
+            if (sh.wide) return pick_tiled<T, 256, tile_threads(256, true)>(scheme, lim);
+            return sh.stream ? pick_tiled<T, 256, 256, true>(scheme, lim) : pick_tiled<T, 256, 256>(scheme, lim);
         }
     }
     return pick_cell_kernel<T>(scheme, lim, wafm);
@@ -2290,6 +2332,9 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
         sp.inflow_q = ms[i].inflow_q;
         sp.inv_inflow_len = L > 0 ? 1.0 / L : 0.0;
         sp.outflow_stage = ms[i].outflow_stage;
+        const double *man = ms[i].cell_manning;
+        const bool same = std::all_of(man, man + ms[i].n_total, [man](double v) { return v == man[0]; });
+        sp.man2 = same ? man[0] * man[0] : -1.0;
     }
     rc = push_scenarios(c);
     if (rc != SWE_OK) return rc;

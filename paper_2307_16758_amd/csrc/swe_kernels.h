@@ -39,6 +39,7 @@ struct ScenParams {
     double inv_inflow_len;   // 1 / total inflow edge length
     double outflow_stage;
     int series_off, series_n;  // hydrograph points in the series arrays
+    double man2;             // Manning n^2 where every cell has the same, else -1
 };
 
 // Interface values of one half-edge: depth, bed, normal and tangential

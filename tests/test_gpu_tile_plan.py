@@ -90,3 +90,39 @@ def test_launch_shapes_agree_bitwise(name, precision):
     for a, b in zip(ref[:3], s.read_state()):
         assert np.array_equal(a, b)
     s.close()
+
+
+@pytest.mark.parametrize("name,precision", [("muscl_minmod_rk2", 0), ("waf", 0), ("hllc1", 1)])
+def test_roughness_of_one_value_and_of_many(name, precision):
+    """A scenario whose cells share one Manning n takes it from one place: the
+    same bits as read cell by cell (one dry cell's value made to differ)."""
+    import dataclasses
+    kw = dict(SCHEME_KW[name], precision=precision)
+    mesh, U = _problem(60, 30, precision)
+    assert np.all(mesh.cell_manning == mesh.cell_manning[0]) and mesh.cell_manning[0] > 0
+    dry = int(np.argmax(mesh.cell_b))
+    assert U[0][dry] == 0.0
+    man = mesh.cell_manning.copy()
+    man[dry] *= 2.0
+    ref = _run(mesh, U, kw, 20)
+    got = _run(dataclasses.replace(mesh, cell_manning=man), U, kw, 20)
+    assert ref[0][dry] == 0.0                          # it stayed dry: its n was never used
+    for a, b in zip(ref[:3], got[:3]):
+        assert np.array_equal(a, b)
+    assert got[3] == ref[3]
+
+
+def test_mesh_beyond_the_cache_equals_its_small_tiles():
+    """2.8 million cells (a step's arrays over the bound) load their geometry
+    as a stream in 256-cell tiles; tiles of 512 cells do not: same bits."""
+    from paper_2307_16758_amd.problem import prepare_scenario
+    sc = river_channel(nx=2650, ny=530, seed=9)
+    pr = prepare_scenario(sc)
+    l2g = pr.sub.l2g
+    h = (sc.h[l2g] * (1 + 0.02 * np.sin(0.01 * np.arange(l2g.size)))).astype(np.float32)
+    U = [h, 0.3 * h, 0.1 * h]
+    kw = dict(SCHEME_KW["muscl_minmod_rk2"], precision=0)
+    ref = _run(pr.mesh, U, kw, 4)
+    got = _run(pr.mesh, U, kw, 4, block=512)
+    for a, b in zip(ref[:3], got[:3]):
+        assert np.array_equal(a, b)
