@@ -993,9 +993,9 @@ k_stage_tiled(StageArgs<T> args)
                         }
                         // a missing upwind cell's place holds the other one:
                         // their mean is that one
-                        const bool ok = limiter_features<T, T4>(Us, Uk, edge, Ua, hu, Ub, hu, side ? -nx : nx,
-                                                                side ? -ny : ny, side ? w.z : w.x,
-                                                                side ? w.w : w.y, g, eps, f);
+                        const bool ok = limiter_features<T, T4>(limiter_cell<T, T4>(Us, g), Us, Uk, edge, Ua, hu,
+                                                                Ub, hu, side ? -nx : nx, side ? -ny : ny,
+                                                                side ? w.z : w.x, side ? w.w : w.y, eps, f);
                         mlp_write_row(X[lane], f, ok);
                         wave_lds_sync();
                         const MlpLane L = mlp_lane(a.mlp, lane);

@@ -329,14 +329,16 @@ __device__ __forceinline__ void waf_positivity(T g, T eps, const T UL[3], const 
 
 namespace swe {
 
-// tanh for the limiter features: exact in FP64; in FP32 through one hardware
-// exp2 and one reciprocal (about 1e-6 absolute, far below the BF16 rounding
-// the features then get).
-template <typename T> __device__ __forceinline__ T ftanh(T x) { return tanh(x); }
-template <> __device__ __forceinline__ float ftanh<float>(float x)
+// tanh(a w) for the limiter features, w given as tanh_weight(w): exact in
+// FP64; in FP32 through one hardware exp2 and one reciprocal (about 1e-7
+// absolute, far below the BF16 rounding the features then get).  Above 15
+// the argument is held there (exp2 would overflow); below, exp2 goes to 0.
+template <typename T> __device__ __forceinline__ T tanh_weight(T w) { return w; }
+template <> __device__ __forceinline__ float tanh_weight(float w) { return 2.8853900817779268f * w; }
+template <typename T> __device__ __forceinline__ T ftanh(T a, T w) { return tanh(a * w); }
+template <> __device__ __forceinline__ float ftanh<float>(float a, float w)
 {
-    const float xc = fminf(fmaxf(x, -15.0f), 15.0f);
-    const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * xc);  // exp(2x)
+    const float e = __builtin_amdgcn_exp2f(fminf(a * w, 43.280851f));  // exp(2 a w)
     return (e - 1.0f) * __builtin_amdgcn_rcpf(e + 1.0f);
 }
 
@@ -352,16 +354,41 @@ constexpr int kMlpParams = kMlpH * kMlpIn + kMlpH + kMlpH * kMlpH + kMlpH + kMlp
 // ab af / (af^2 + (0.01 scale)^2) clipped to
 // [-2, 2]; then tanh of the cell's Froude
 // number and of the relative depth jump across the edge.  Scales: h, b:
-// h_c + 0.01 m; q: h_c sqrt(g h_c) + 0.01 m^2/s.  Returns false when the
-// half-edge is not reconstructed to second order (dry stencil cell, no
-// neighbour across the edge, no upwind cell): the features are then zero.
+// h_c + 0.01 m; q: h_c sqrt(g h_c) + 0.01 m^2/s.
+//
+// What depends on the cell alone: the scales' tanh weights, the ratios'
+// regularizations and the Froude input.
+template <typename T> struct LimiterCell {
+    T wh, wq, eh, eq, fr;
+};
+
 template <typename T, typename T4>
-__device__ __forceinline__ bool limiter_features(const T4 &Uc, const T4 &Uk, bool hk_, const T4 &Ua,
-                                                 bool ha, const T4 &Ub, bool hb, T nx, T ny, T al,
-                                                 T be, T g, T eps, float f[kMlpIn])
+__device__ __forceinline__ LimiterCell<T> limiter_cell(const T4 &Uc, T g)
+{
+    LimiterCell<T> L;
+    const T hc = Uc.x;
+    const T sh = hc + T(0.01), sq = hc * sqrt(g * hc) + T(0.01);
+    L.wh = tanh_weight(frcp(sh));
+    L.wq = tanh_weight(frcp(sq));
+    L.eh = T(1e-4) * sh * sh;
+    L.eq = T(1e-4) * sq * sq;
+    const T ih = frcp(hc), u = Uc.y * ih, v = Uc.z * ih;
+    L.fr = ftanh(fdiv(sqrt(u * u + v * v), sqrt(g * tmax(hc, T(1e-6)))), tanh_weight(T(1)));
+    return L;
+}
+
+// The features of one half-edge; Ua and Ub are the upwind states, ha and hb
+// say which exist (a missing one's place holds any finite state of a wet
+// cell).  Returns false when the half-edge is not reconstructed to second
+// order (dry stencil cell, no neighbour across the edge, no upwind cell): the
+// features are then zero.
+template <typename T, typename T4>
+__device__ __forceinline__ bool limiter_features(const LimiterCell<T> &L, const T4 &Uc, const T4 &Uk,
+                                                 bool hk_, const T4 &Ua, bool ha, const T4 &Ub, bool hb,
+                                                 T nx, T ny, T al, T be, T eps, float f[kMlpIn])
 {
     // one test up front (a wave whose half-edges are all dry or one-sided
-    // skips the rest), then no divergent branch: the upwind state is a select
+    // skips the rest), then no divergent branch
     const bool ok = hk_ && Uc.x > eps && Uk.x > eps && (!ha || Ua.x > eps) && (!hb || Ub.x > eps) &&
                     (ha || hb);
     if (!ok) {
@@ -372,37 +399,28 @@ __device__ __forceinline__ bool limiter_features(const T4 &Uc, const T4 &Uk, boo
     const T qc[4] = {Uc.x, Uc.y * nx + Uc.z * ny, -Uc.y * ny + Uc.z * nx, Uc.w};
     const T qk[4] = {Uk.x, Uk.y * nx + Uk.z * ny, -Uk.y * ny + Uk.z * nx, Uk.w};
     // upwind state: the mean of the two upwind cells, or the one that exists
-    const bool both = ha && hb;
-    const T4 &Uo = ha ? Ua : Ub;
-    T qu[4];
-    qu[0] = both ? T(0.5) * (Ua.x + Ub.x) : Uo.x;
-    qu[1] = both ? T(0.5) * ((Ua.y * nx + Ua.z * ny) + (Ub.y * nx + Ub.z * ny)) : Uo.y * nx + Uo.z * ny;
-    qu[2] = both ? T(0.5) * ((-Ua.y * ny + Ua.z * nx) + (-Ub.y * ny + Ub.z * nx))
-                 : -Uo.y * ny + Uo.z * nx;
-    qu[3] = both ? T(0.5) * (Ua.w + Ub.w) : Uo.w;
-    const T hc = Uc.x;
-    const T sh = hc + T(0.01), sq = hc * sqrt(g * hc) + T(0.01);
-    const T sc[4] = {sh, sq, sq, sh};
+    // (weights 1/2 and 1/2, or 1 and 0: exact)
+    const T wa = ha ? (hb ? T(0.5) : T(1)) : T(0), wb = hb ? (ha ? T(0.5) : T(1)) : T(0);
+    const T ux = wa * Ua.y + wb * Ub.y, uy = wa * Ua.z + wb * Ub.z;
+    const T qu[4] = {wa * Ua.x + wb * Ub.x, ux * nx + uy * ny, -ux * ny + uy * nx, wa * Ua.w + wb * Ub.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         // upwind and cross-edge increments over the distance to the edge
         // midpoint (slope times d_mid): the MUSCL weights al = d_mid / d_up
         // and be = d_mid / d_fwd times the differences
         const T ab = al * (qc[k] - qu[k]), af = be * (qk[k] - qc[k]);
-        const T isc = frcp(sc[k]);
+        const bool q = k == 1 || k == 2;
+        const T w = q ? L.wq : L.wh;
         // q_t changes sign in a mirror image: its increments enter by
         // magnitude (the ratio keeps their relative sign)
-        f[3 * k + 0] = float(ftanh((k == 2 ? fabs(ab) : ab) * isc));
-        f[3 * k + 1] = float(ftanh((k == 2 ? fabs(af) : af) * isc));
+        f[3 * k + 0] = float(ftanh(k == 2 ? T(fabs(ab)) : ab, w));
+        f[3 * k + 1] = float(ftanh(k == 2 ? T(fabs(af)) : af, w));
         // regularized at 1% of the scale: smooth where af vanishes
-        const T r = fdiv(ab * af, af * af + T(1e-4) * sc[k] * sc[k]);
+        const T r = fdiv(ab * af, af * af + (q ? L.eq : L.eh));
         f[3 * k + 2] = float(tmin(T(2), tmax(T(-2), r)));
     }
-    const T ih = frcp(hc);
-    const T uc = Uc.y * ih, vc = Uc.z * ih;
-    const T un = uc * nx + vc * ny, ut = -uc * ny + vc * nx;
-    f[12] = float(ftanh(fdiv(sqrt(un * un + ut * ut), sqrt(g * tmax(hc, T(1e-6))))));
-    f[13] = float(ftanh(fdiv(Uk.x - hc, hc + T(0.01))));
+    f[12] = float(L.fr);
+    f[13] = float(ftanh(Uk.x - Uc.x, L.wh));
     return true;
 }
 

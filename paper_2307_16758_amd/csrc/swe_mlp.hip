@@ -86,6 +86,7 @@ __global__ void __launch_bounds__(256) k_limiter_phi(PhiArgs<T> a)
         // a local value becomes a load through a selected pointer, which
         // puts the local value in scratch memory)
         const T4 Un0 = a.U[hn0 ? nb4.x : c], Un1 = a.U[hn1 ? nb4.y : c], Un2 = a.U[hn2 ? nb4.z : c];
+        const LimiterCell<T> LC = limiter_cell<T, T4>(Uc, a.g);
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
             const int ma = (m + 1) % 3, mb = (m + 2) % 3;
@@ -97,8 +98,8 @@ __global__ void __launch_bounds__(256) k_limiter_phi(PhiArgs<T> a)
             const bool hb = mb == 0 ? hn0 : (mb == 1 ? hn1 : hn2);
             float f[kMlpIn];
             const T4 co = a.he_co[m * a.n + c];
-            const bool ok = limiter_features<T, T4>(Uc, Um, hm, Ua, ha, Ub, hb, co.x, co.y, co.z,
-                                                    co.w, a.g, a.eps, f);
+            const bool ok = limiter_features<T, T4>(LC, Uc, Um, hm, Ua, ha, Ub, hb, co.x, co.y, co.z,
+                                                    co.w, a.eps, f);
             mlp_write_row(X[wv][3 * lane + m], f, ok);
         }
     } else {
@@ -167,6 +168,7 @@ __global__ void k_pairs(PairArgs<T> a)
         Un[m] = hn[m] ? a.U[nb[m]] : Uc;
     }
     const T eps = a.eps;
+    const LimiterCell<T> LC = limiter_cell<T, T4>(Uc, a.g);
     for (int m = 0; m < 3; ++m) {
         float *r = a.rec + (size_t)kRec * (3 * c + m);
         const int ma = (m + 1) % 3, mb = (m + 2) % 3;
@@ -175,8 +177,8 @@ __global__ void k_pairs(PairArgs<T> a)
         const T nx = ge.x, ny = ge.y;
         float f[kMlpIn];
         const T4 co = a.he_co[m * a.n + c];
-        bool ok = limiter_features<T, T4>(Uc, Un[m], hn[m], Un[ma], hn[ma], Un[mb], hn[mb], co.x, co.y,
-                                          co.z, co.w, a.g, eps, f);
+        bool ok = limiter_features<T, T4>(LC, Uc, Un[m], hn[m], Un[ma], hn[ma], Un[mb], hn[mb], co.x, co.y,
+                                          co.z, co.w, eps, f);
         for (int i = 0; i < kMlpIn; ++i) r[i] = f[i];
         T qc[4] = {Uc.x, Uc.x + Uc.w, T(0), T(0)};
         frame_vel(Uc, nx, ny, eps, qc[2], qc[3]);

@@ -15,9 +15,9 @@
 // and the output layer take all 32 inputs in one v_mfma_f32_16x16x32_bf16:
 // a lane's eight K slots hold the units of its two accumulators of the layer
 // before (units 4q..4q+3 and 16+4q..16+4q+3 for lane group q), and the A
-// operand takes its weights in the same order.  The output layer of tile q
-// holds W3 in row 4q of its A operand (zeros elsewhere), so its 16 results
-// are element 0 of lanes 16q..16q+15: one select per lane then gathers the
+// operand takes its weights in the same order.  The output layer holds W3 in
+// every row of its A operand, so every lane group has a tile's 16 results in
+// element 0: one select per lane then gathers the
 // four tiles, and the result of row l is in lane l.  Each tile keeps an
 // accumulator of its own, so a non-finite value stays in its tile.  Every
 // result depends only on its own column, so a half-edge's output is the
@@ -105,7 +105,7 @@ __device__ __forceinline__ void wave_lds_sync()
 struct MlpLane {
     s4v W1[2];       // layer 1, units nt*16 + col, inputs kq..kq+3
     bf8v W2[2];      // layer 2, units nt*16 + col, inputs kq..kq+3 and 16+kq..16+kq+3
-    bf8v W3;         // output weights of the same inputs (row 4q of tile q only)
+    bf8v W3;         // output weights of the same inputs, the same in every row
     f4v b1[2], b2[2];  // biases of units nt*16 + kq..kq+3
     float b3;
 };
@@ -153,8 +153,7 @@ __device__ __forceinline__ void mlp_write_row(uint16_t *row, const float f[kMlpI
 __device__ __forceinline__ float mlp_rows_z(const MlpLane &L, const uint16_t (*X)[16], int lane)
 {
     const int col = lane & 15, kq = (lane >> 4) * 4;
-    const bf8v zero8 = {};
-    // b3 in element 0 of every lane: rows 0, 4, 8 and 12 of the accumulator
+    // b3 in element 0 of every lane: rows 0, 4, 8 and 12 of the accumulator (the others are not used)
     const f4v c3 = {L.b3, 0.f, 0.f, 0.f};
     const int grp = lane >> 4;
     float z = 0.0f;
@@ -170,7 +169,7 @@ __device__ __forceinline__ float mlp_rows_z(const MlpLane &L, const uint16_t (*X
         const f4v e0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(L.W2[0], h, L.b2[0], 0, 0, 0);
         const f4v e1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(L.W2[1], h, L.b2[1], 0, 0, 0);
         const bf8v gv = cat8(relu_bf16x4(e0), relu_bf16x4(e1));
-        const f4v o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(col == 4 * q ? L.W3 : zero8, gv, c3, 0, 0, 0);
+        const f4v o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(L.W3, gv, c3, 0, 0, 0);
         z = grp == q ? o[0] : z;
     }
     return z;
