@@ -371,9 +371,9 @@ int swe_trainer_get_params(swe_trainer *tr, float *host_params);
  * the loss), queued on `stream` (a hipStream_t; NULL is the null stream) of
  * the current device, no host synchronisation.  It allocates nothing: the
  * per-block partial sums live in a static device array of this library
- * (512 blocks x 1570 floats, 3.2 MB per GPU, held until the process ends),
- * whose size does not depend on n (the grid is capped at 512 blocks, each
- * looping over chunks of 64 records), so no size is refused for want of
+ * (256 blocks x 1570 floats, 1.6 MB per GPU, held until the process ends),
+ * whose size does not depend on n (the grid is capped at 256 blocks, each
+ * looping over chunks of 128 records), so no size is refused for want of
  * workspace.  Bitwise equal to swe_trainer_loss_grad with the same
  * parameters (same kernels, same grid, same reduction order).  Calls that
  * overlap on one GPU share that array and race: order them on one stream.

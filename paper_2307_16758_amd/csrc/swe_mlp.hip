@@ -250,8 +250,11 @@ __global__ void k_pairs(PairArgs<T> a)
 // in order, the waves of a block, then the blocks in k_train_reduce), so
 // results are deterministic.
 // 65,536 records: 136 us with one thread per record in 64 of a block's 256
-// threads, 17 us this way; the matrix work alone is 4 us.
-constexpr int kChunk = 64;  // records of a block at a time: 16 per wave
+// threads, 15.7 us this way; the matrix work alone is 4 us.  One block of eight
+// waves per compute unit (180 registers allow two per SIMD): blocks of four
+// waves, two per unit, wrote twice the partials and took 17 us.
+constexpr int kChunk = 128;       // records of a block at a time: 16 per wave
+constexpr int kTrainThreads = 512;
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // any float address
 
@@ -272,15 +275,20 @@ __device__ __forceinline__ float row_sum(float x)
     return x;
 }
 
-__global__ void __launch_bounds__(256) k_train_partial(TrainArgs a)
+__global__ void __launch_bounds__(kTrainThreads) k_train_partial(TrainArgs a)
 {
     constexpr int kU = 36, kX = 20;              // row strides: unit rows, input rows
     constexpr int kWave = 16 * (3 * kU + kX);    // floats of one wave's rows
     static_assert(kWave >= kMlpParams + 1, "the waves' sums reuse the rows");
-    __shared__ __align__(16) float lds[4 * kWave];
+    constexpr int kWaves = kTrainThreads / 64;
+    __shared__ __align__(16) float lds[kWaves * kWave];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
     float *sA1 = lds + wave * kWave, *sD2 = sA1 + 16 * kU, *sD1 = sD2 + 16 * kU, *sX = sD1 + 16 * kU;
-    const float *W1 = a.params, *b1 = W1 + kMlpH * kMlpIn, *W2 = b1 + kMlpH, *b2 = W2 + kMlpH * kMlpH;
+    // the parameters come through LDS (the rows are not in use yet): read
+    // straight from memory in operand order they are 64 scattered loads a wave
+    for (int p = threadIdx.x; p < kMlpParams; p += kTrainThreads) lds[p] = a.params[p];
+    __syncthreads();
+    const float *W1 = lds, *b1 = W1 + kMlpH * kMlpIn, *W2 = b1 + kMlpH, *b2 = W2 + kMlpH * kMlpH;
     const float *W3 = b2 + kMlpH, *b3 = W3 + kMlpH;
     // weights as operands: w1[t][s] = W1[16 t + r][4 q + s] (inputs 14 and 15
     // do not exist), w2[t][k][s] = W2[16 t + r][16 k + 4 q + s], and its
@@ -302,6 +310,7 @@ __global__ void __launch_bounds__(256) k_train_partial(TrainArgs a)
         }
     }
     const float z0 = b3[0], wq = a.wv[q], inv_n = 1.0f / (float)a.n;
+    __syncthreads();
     f4v g2[2][2] = {}, g1[2] = {};           // gradients of W2, of W1 and (input 14) of b1
     float gb2[2][4] = {}, gw3[2][4] = {}, gb3 = 0.f, loss = 0.f;
     const int nchunks = (a.n + kChunk - 1) / kChunk;
@@ -431,8 +440,12 @@ __global__ void __launch_bounds__(256) k_train_partial(TrainArgs a)
     if (lane == 0) { out[kMlpParams - 1] = gb3; out[kMlpParams] = loss; }
     __syncthreads();
     float *part = a.partial + (size_t)blockIdx.x * (kMlpParams + 1);
-    for (int p = threadIdx.x; p <= kMlpParams; p += 256)
-        part[p] = (lds[p] + lds[kWave + p]) + (lds[2 * kWave + p] + lds[3 * kWave + p]);
+    for (int p = threadIdx.x; p <= kMlpParams; p += kTrainThreads) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) v += lds[w * kWave + p];
+        part[p] = float(v);
+    }
 }
 
 // Fixed-order sum of the block partials: grad[p], loss (mean over n).  A
@@ -491,11 +504,11 @@ int err(swe_ctx *c, int code, const std::string &m)
 
 }  // namespace
 
-constexpr int kTrainBlocks = 512;  // gradient partials: at most this many blocks
+constexpr int kTrainBlocks = 256;  // gradient partials: at most this many blocks
 constexpr int kMaxDevices = 64;    // devices whose static workspace address is kept
 
 // Per-block gradient partials of swe_trainer_loss_grad_static: a device array
-// of fixed size (3.2 MB), one copy per GPU, held until the process ends.  In
+// of fixed size (1.6 MB), one copy per GPU, held until the process ends.  In
 // host code this name is not a device address: kernels get the address that
 // hipGetSymbolAddress returns for the current device (static_scratch_ptr).
 static __device__ __align__(256) float scratch[kTrainBlocks * (kMlpParams + 1)];
@@ -660,7 +673,7 @@ static int launch_grad(const float *params, const float *rec, int32_t n_rec, con
     for (int k = 0; k < 4; ++k) a.wv[k] = wv[k];
     const int nchunks = (n + kChunk - 1) / kChunk;
     const int G = nchunks < nblocks ? nchunks : nblocks;
-    hipLaunchKernelGGL(k_train_partial, dim3(G), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(k_train_partial, dim3(G), dim3(kTrainThreads), 0, stream, a);
     hipLaunchKernelGGL(k_train_reduce, dim3((kMlpParams + 1 + 63) / 64), dim3(1024), 0, stream,
                        partial, G, n, grad_loss, host);
     return hipGetLastError() == hipSuccess ? SWE_OK : SWE_ERR_DEVICE;
