@@ -1496,15 +1496,15 @@ __global__ void k_pack_ghosts(int n_send, const int *send_idx, const typename V4
     buf[2 * n_send + i] = u.z;
 }
 
-// In-place receive: [3][n_ghost] into the contiguous ghost range.
+// In-place receive: [3][n_ghost] into the contiguous ghost range (the bed in
+// the fourth place stays; not reading it first saves its latency).
 template <typename T>
 __global__ void k_unpack_ghosts(int n_owned, int n_ghost, const T *buf, typename V4<T>::type *U)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_ghost) return;
-    typename V4<T>::type u = U[n_owned + i];
-    u.x = buf[i]; u.y = buf[n_ghost + i]; u.z = buf[2 * n_ghost + i];
-    U[n_owned + i] = u;
+    struct Three { T h, hu, hv; };
+    *reinterpret_cast<Three *>(&U[n_owned + i]) = Three{buf[i], buf[n_ghost + i], buf[2 * n_ghost + i]};
 }
 
 }  // namespace

@@ -541,11 +541,12 @@ __device__ __forceinline__ void hllc_dev(T g, T eps, T hL, T uL, T vL, T hR, T u
     if (!wr) { uR = T(0); vR = T(0); }
     const T qL = wl ? hL * uL : T(0), qR = wr ? hR * uR : T(0);
     const T aL = sqrt(g * hL), aR = sqrt(g * hR);
-    T SL, SR, Ss;
+    T SL, SR;
+    bool left;  // the contact moves right (S* >= 0): the left tangential velocity is carried
     if (!wr) {
-        SL = uL - aL; SR = uL + T(2) * aL; Ss = SR;
+        SL = uL - aL; SR = uL + T(2) * aL; left = SR >= T(0);
     } else if (!wl) {
-        SL = uR - T(2) * aR; SR = uR + aR; Ss = SL;
+        SL = uR - T(2) * aR; SR = uR + aR; left = SL >= T(0);
     } else {
         const T h0 = T(0.5) * (hL + hR) - T(0.25) * (uR - uL) * (hL + hR) * frcp(aR + aL);
         T hs;
@@ -561,7 +562,9 @@ __device__ __forceinline__ void hllc_dev(T g, T eps, T hL, T uL, T vL, T hR, T u
         const T pR = hs > hR ? sqrt((hs + hR) * hs * frcp(T(2) * hR * hR)) : T(1);
         SL = uL - aL * pL;
         SR = uR + aR * pR;
-        Ss = (SL * hR * (uR - SR) - SR * hL * (uL - SL)) * frcp(hR * (uR - SR) - hL * (uL - SL));
+        // only the sign of S* counts, and its denominator
+        // hR (uR - SR) - hL (uL - SL) is negative
+        left = SL * hR * (uR - SR) - SR * hL * (uL - SL) <= T(0);
     }
     const T dP = T(0.5) * g * (hL - hR) * (hL + hR);  // pL - pR
     const T mL = qL * uL, mR = qR * uR;                // advective momentum fluxes
@@ -572,7 +575,7 @@ __device__ __forceinline__ void hllc_dev(T g, T eps, T hL, T uL, T vL, T hR, T u
     const T base = SR * mL - SL * mR + SR * SL * (qR - qL);
     DL = (base + SL * dP) * inv;
     DR = (base + SR * dP) * inv;
-    F2 = F0 * (Ss >= T(0) ? vL : vR);
+    F2 = F0 * (left ? vL : vR);
 }
 
 // A cell's share of an edge (Sec. 6.1): the oriented flux sg * G plus the
