@@ -108,7 +108,10 @@ typedef struct {
     int block;         /* cells per tile of the tiled kernels, threads per block of the
                           one-thread-per-cell kernel: 64, 128, 256 or 512 (0: by size); the
                           one-thread-per-cell kernel, FP64 and WAF use at most 256, and a
-                          mesh whose numbering has no locality gets smaller tiles */
+                          mesh whose numbering has no locality gets smaller tiles.  With 0 a
+                          MUSCL-RK2 step of a small mesh (classic limiter, one scenario, no
+                          ghost cells, up to 98,304 cells FP32 or 49,152 FP64 on 256 compute
+                          units) is one launch instead of two, with the same bits */
     int cell_kernel;   /* 1: one-thread-per-cell stage kernel for every scheme; 0: the
                           tiled kernels (HLLC1, MUSCL, and WAF with Euler steps; WAF with
                           RK2 uses the cell kernel) */
@@ -230,7 +233,8 @@ int swe_scenario_times(swe_ctx *ctx, double *t);  /* [n_scenarios]; syncs */
  * configured stage kernel (64, 128, 256 or, FP32 tiled kernel only, 512
  * cells per tile or threads per block; tiled kernel: a thread per cell or per
  * edge of a tile; one tile per block or a persistent grid of the blocks
- * the chip holds at once) from the current state, keeps the fastest and
+ * the chip holds at once; a small mesh's MUSCL-RK2 step in one launch, which
+ * reports 64 cells) from the current state, keeps the fastest and
  * restores the state, clocks and time.  The choice never changes results
  * (the tiled kernel is bitwise independent of the tiling, and all builds
  * perform the same operations).

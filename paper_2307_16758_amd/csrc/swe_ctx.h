@@ -18,6 +18,9 @@ struct TilePlan {
     void *mem = nullptr;
     void *desc = nullptr, *halo = nullptr, *ent = nullptr, *nrm = nullptr, *wgt = nullptr, *gam = nullptr,
          *dfw = nullptr;
+    // DEEP (a two-stage step in one launch): the plain plan's halo
+    const void *base = nullptr;
+    int base_hs = 0;
 };
 }  // namespace swe
 
@@ -46,6 +49,7 @@ struct swe_ctx {
     swe::ScenParams *scen = nullptr;
     double *ser_t = nullptr, *ser_q = nullptr;
     swe::TilePlan plans[4];  // 64, 128, 256 and 512 cells per tile, built when first needed
+    swe::TilePlan deep;      // of 64-cell tiles (tile -1: does not fit)
     int *health = nullptr, *flag = nullptr, *send_idx = nullptr;
     int *pk_off = nullptr, *pk_ent = nullptr;  // send entries per send cell (CSR)
     int *host = nullptr;  // page-locked: call number of a refused state, health bits

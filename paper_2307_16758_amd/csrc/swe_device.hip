@@ -382,6 +382,13 @@ template <typename T> struct StageArgs {
     const typename V2<T>::type *tgam;
     const T *tdfw;
     int hs, es, ntiles;
+    // DEEP plan (k_step_tiled)
+    const int4 *ddesc;
+    const int *dhalo;
+    const uint2 *dent;
+    const typename V2<T>::type *dnrm;
+    const T4 *dwgt;
+    int dhs, des;
     int n_owned;
     ClockWord *clock;
     int ncopy;                   // CFL partial copies per clock slot (power of two <= 64)
@@ -850,6 +857,88 @@ template <bool TWO> __device__ __forceinline__ uint2 load_entry(const uint2 *e, 
     return make_uint2(ldx(reinterpret_cast<const unsigned *>(e), 2 * i), 0u);
 }
 
+// Both cells' shares of an interior edge (Sec. 6.1 - 6.2) from the slots'
+// primitive values sP: reconstructions, hydrostatic reconstruction, HLLC.
+template <typename T, bool MUSCL_, int RL, typename T4>
+__device__ __forceinline__ void edge_shares(const T4 *sP, int iL, int iR, int iLa, int iLb, int iRa, int iRb,
+                                            T nx, T ny, const T4 &w, T gL, T gR, float phL, float phR,
+                                            T g, T eps, T fL[3], T fR[3])
+{
+    const T4 L = sP[iL];
+    const T4 R = sP[iR];
+    // both sides' values in L's frame (a limiter is odd in its two slopes, so
+    // R's reconstruction in its own opposite frame is the same but for the
+    // signs)
+    const T qL[4] = {L.x, L.x + L.y, L.z * nx + L.w * ny, -L.z * ny + L.w * nx};
+    const T qR[4] = {R.x, R.x + R.y, R.z * nx + R.w * ny, -R.z * ny + R.w * nx};
+    Half<T> hL, hR;
+    hL.h = qL[0]; hL.b = L.y; hL.un = qL[2]; hL.ut = qL[3]; hL.eta = qL[1];
+    hR.h = qR[0]; hR.b = R.y; hR.un = qR[2]; hR.ut = qR[3]; hR.eta = qR[1];
+    if (MUSCL_) {
+        const bool wet = L.x > eps && R.x > eps;
+        recon_side<T, RL>(hL, qL, qR, sP[iLa], sP[iLb], wet, nx, ny, w.x, w.y, gL, phL, eps);
+        recon_side<T, RL>(hR, qR, qL, sP[iRa], sP[iRb], wet, nx, ny, w.z, w.w, gR, phR, eps);
+    }
+    // side correction and centred bed term less the cell's hydrostatic
+    // pressure: g (h- + h)(eta- - eta) / 2 along n
+    const T sbL = T(0.5) * g * (hL.h + L.x) * (hL.eta - (L.x + L.y));
+    const T sbR = T(0.5) * g * (hR.h + R.x) * (hR.eta - (R.x + R.y));
+    // hydrostatic reconstruction
+    const T bmax = tmax(hL.b, hR.b);
+    const T hsL = tmax(T(0), hL.h + hL.b - bmax);
+    const T hsR = tmax(T(0), hR.h + hR.b - bmax);
+    T F0, DL, DR, F2;
+    hllc_dev(g, eps, hsL, hL.un, hL.ut, hsR, hR.un, hR.ut, F0, DL, DR, F2);
+    // each side's normal momentum flux less its own hydrostatic pressure,
+    // rotated back from the canonical frame
+    half_edge_flux(T(1), F0, DL * nx - F2 * ny, DL * ny + F2 * nx, sbL, nx, ny, fL[0], fL[1], fL[2]);
+    half_edge_flux(T(-1), F0, DR * nx - F2 * ny, DR * ny + F2 * nx, sbR, -nx, -ny, fR[0], fR[1], fR[2]);
+}
+
+// A boundary half-edge's share (Sec. 6.1) in the global frame; U the cell's
+// state, k the tag, st its scenario, second: at the end of the step.
+template <typename T, typename T4>
+__device__ __forceinline__ void boundary_share(const StageArgs<T> &a, int k, const T4 &U, T nx, T ny, int st,
+                                               bool second, T G[3])
+{
+    const ScenParams sp = a.scen[st];
+    T q_in = T(0);
+    if (k == kBcInflow) {
+        const double t_st = bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)]) +
+                            (second ? lane_step_dt(a.clock, a.ncopy, a.slot_cur, st, a.cfl_rule, a.cfl,
+                                                   a.dt_max, a.dt_fixed)
+                                    : 0.0);
+        q_in = T(inflow_at(sp, a.ser_t, a.ser_q, t_st) * sp.inv_inflow_len);
+    }
+    boundary_flux_dev<T, T4>(k, U, nx, ny, a.g, a.eps, q_in, T(sp.outflow_stage), G);
+}
+
+// Euler update of a cell from its weighted shares, with Manning and the
+// cleanup; returns health bits.
+template <typename T>
+__device__ __forceinline__ int cell_update(T h, T hu, T hv, T a0, T a1, T a2, T dt, T man2, T g, T eps,
+                                           T &nh, T &nu, T &nv)
+{
+    nh = h - dt * a0;
+    nu = hu - dt * a1;
+    nv = hv - dt * a2;
+    int flags = 0;
+    if (!(isfinite(nh) && isfinite(nu) && isfinite(nv))) flags |= kHealthNonfinite;
+    if (nh < T(0)) {
+        flags |= nh < -eps ? kHealthNegDepth : kHealthClipped;
+        nh = T(0);
+    }
+    if (nh <= eps) {
+        nu = T(0); nv = T(0);
+    } else if (man2 > T(0)) {  // Manning, point-implicit
+        const T sp = sqrt(nu * nu + nv * nv) * frcp(nh);
+        const T f = T(1) + dt * g * man2 * sp * pow_m43(nh);
+        const T rf = frcp(f);
+        nu *= rf; nv *= rf;
+    }
+    return flags;
+}
+
 template <typename T, bool MUSCL_, int LIM, int TILE, int NT, bool STREAM = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 ? (LIM == kLearned ? SWE_TILED_WAVES_LEARNED
@@ -1011,48 +1100,17 @@ k_stage_tiled(StageArgs<T> args)
                 }
                 if (i >= nt) continue;
             }
-            const T4 L = sP[iL];
-            const T4 R = sP[iR];
-            // both sides' values in L's frame (a limiter is odd in its two
-            // slopes, so R's reconstruction in its own opposite frame is the
-            // same but for the signs)
-            const T qL[4] = {L.x, L.x + L.y, L.z * nx + L.w * ny, -L.z * ny + L.w * nx};
-            const T qR[4] = {R.x, R.x + R.y, R.z * nx + R.w * ny, -R.z * ny + R.w * nx};
-            Half<T> hL, hR;
-            hL.h = qL[0]; hL.b = L.y; hL.un = qL[2]; hL.ut = qL[3]; hL.eta = qL[1];
-            hR.h = qR[0]; hR.b = R.y; hR.un = qR[2]; hR.ut = qR[3]; hR.eta = qR[1];
-            if (MUSCL_) {
-                T gL = T(0), gR = T(0);
-                if (RL == kLearned) { const T2 gg = ldx(gam, i); gL = gg.x; gR = gg.y; }
-                const bool wet = L.x > eps && R.x > eps;
-                recon_side<T, RL>(hL, qL, qR, sP[iLa], sP[iLb], wet, nx, ny, w.x, w.y, gL, phL, eps);
-                recon_side<T, RL>(hR, qR, qL, sP[iRa], sP[iRb], wet, nx, ny, w.z, w.w, gR, phR, eps);
-            }
-            // side correction and centred bed term less the cell's
-            // hydrostatic pressure: g (h- + h)(eta- - eta) / 2 along n
-            const T sbL = T(0.5) * g * (hL.h + L.x) * (hL.eta - (L.x + L.y));
-            const T sbR = T(0.5) * g * (hR.h + R.x) * (hR.eta - (R.x + R.y));
-            // hydrostatic reconstruction
-            const T bmax = tmax(hL.b, hR.b);
-            const T hsL = tmax(T(0), hL.h + hL.b - bmax);
-            const T hsR = tmax(T(0), hR.h + hR.b - bmax);
-            T F0, DL, DR, F2;
-            hllc_dev(g, eps, hsL, hL.un, hL.ut, hsR, hR.un, hR.ut, F0, DL, DR, F2);
-            // each side's normal momentum flux less its own hydrostatic
-            // pressure, rotated back from the canonical frame
+            T gL = T(0), gR = T(0);
+            if (RL == kLearned) { const T2 gg = ldx(gam, i); gL = gg.x; gR = gg.y; }
+            T fL[3], fR[3];
+            edge_shares<T, MUSCL_, RL>(sP, iL, iR, iLa, iLb, iRa, iRb, nx, ny, w, gL, gR, phL, phR, g, eps, fL, fR);
             if (iL < TILE) {
-                T f0, f1, f2;
-                half_edge_flux(T(1), F0, DL * nx - F2 * ny, DL * ny + F2 * nx, sbL, nx, ny, f0, f1, f2);
-                sF[mL * TILE + iL] = f0;
-                sF[(3 + mL) * TILE + iL] = f1;
-                sF[(6 + mL) * TILE + iL] = f2;
+#pragma unroll
+                for (int f = 0; f < 3; ++f) sF[(3 * f + mL) * TILE + iL] = fL[f];
             }
             if (iR < TILE) {
-                T f0, f1, f2;
-                half_edge_flux(T(-1), F0, DR * nx - F2 * ny, DR * ny + F2 * nx, sbR, -nx, -ny, f0, f1, f2);
-                sF[mR * TILE + iR] = f0;
-                sF[(3 + mR) * TILE + iR] = f1;
-                sF[(6 + mR) * TILE + iR] = f2;
+#pragma unroll
+                for (int f = 0; f < 3; ++f) sF[(3 * f + mR) * TILE + iR] = fR[f];
             }
         }
         // boundary fluxes (Sec. 6.1), in the global frame
@@ -1063,18 +1121,8 @@ k_stage_tiled(StageArgs<T> args)
             const T2 nb = ld_stream<STREAM>(nrm, i);
             const T4 Ub = ldx(a.Uin, c0 + l);
             const int st = a.n_scen == 1 ? 0 : (d.z >= 0 ? d.z : (int)((unsigned)a.nbr[c0 + l].w >> kScenShift));
-            const ScenParams sp = a.scen[st];
-            T q_in = T(0);
-            if (k == kBcInflow) {
-                const double t_st =
-                    bitsd(a.clock[clock_off(a.ncopy, st, a.slot_cur)]) +
-                    (a.kind == 2 ? lane_step_dt(a.clock, a.ncopy, a.slot_cur, st, a.cfl_rule,
-                                                a.cfl, a.dt_max, a.dt_fixed)
-                                 : 0.0);
-                q_in = T(inflow_at(sp, a.ser_t, a.ser_q, t_st) * sp.inv_inflow_len);
-            }
             T G[3];
-            boundary_flux_dev<T, T4>(k, Ub, nb.x, nb.y, g, eps, q_in, T(sp.outflow_stage), G);
+            boundary_share<T, T4>(a, k, Ub, nb.x, nb.y, st, a.kind == 2, G);
             sF[m * TILE + l] = G[0];
             sF[(3 + m) * TILE + l] = G[1];
             sF[(6 + m) * TILE + l] = G[2];
@@ -1109,29 +1157,8 @@ k_stage_tiled(StageArgs<T> args)
                 acc2 += lam[m] * sF[(6 + m) * TILE + cl];
                 lsum += lam[m];
             }
-            T nh = Pc.x - dt * acc0;
-            T nu = Uc.y - dt * acc1;
-            T nv = Uc.z - dt * acc2;
-            // the inscribed radius from the edge weights: sum_m L_m / |Omega|
-            // = P / |Omega|, so R = 2 |Omega| / P = 2 / that sum; Manning's
-            // n^2 is the only per-cell value read (4 bytes, not 16)
-            T4 cg;
-            cg.y = fdiv(T(2), lsum);
-            cg.z = man2;
-            int flags = 0;
-            if (!(isfinite(nh) && isfinite(nu) && isfinite(nv))) flags |= kHealthNonfinite;
-            if (nh < T(0)) {
-                flags |= nh < -eps ? kHealthNegDepth : kHealthClipped;
-                nh = T(0);
-            }
-            if (nh <= eps) {
-                nu = T(0); nv = T(0);
-            } else if (cg.z > T(0)) {  // Manning, point-implicit
-                const T sp = sqrt(nu * nu + nv * nv) * frcp(nh);
-                const T f = T(1) + dt * g * cg.z * sp * pow_m43(nh);
-                const T rf = frcp(f);
-                nu *= rf; nv *= rf;
-            }
+            T nh, nu, nv;
+            const int flags = cell_update(Pc.x, Uc.y, Uc.z, acc0, acc1, acc2, dt, man2, g, eps, nh, nu, nv);
             if (b.kind == 2) {
                 const T4 U0c = ldx(b.U0, c);
                 nh = T(0.5) * (U0c.x + nh);
@@ -1151,7 +1178,9 @@ k_stage_tiled(StageArgs<T> args)
                 const T r = frcp(nh);
                 const T u = nu * r, v = nv * r;
                 const T lm = sqrt(u * u + v * v) + sqrt(g * nh);
-                cfl = cfl_cell<T>(b.cfl_rule, s, cg.y, lm);
+                // the inscribed radius from the edge weights: sum_m L_m / |Omega|
+                // = P / |Omega|, so R = 2 |Omega| / P = 2 / that sum
+                cfl = cfl_cell<T>(b.cfl_rule, s, fdiv(T(2), lsum), lm);
             }
         }
         if (b.kind != 1) {
@@ -1162,6 +1191,199 @@ k_stage_tiled(StageArgs<T> args)
     }
     const StageArgs<T> &a = args_again<T>();
     if (a.kind != 1 && a.n_scen == 1) gather_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, acc, sCfl);
+}
+
+// A whole MUSCL-RK2 step of a small mesh in one launch (one scenario, classic
+// limiters): a block owns a tile of 64 cells and computes the first stage for
+// the cells of its halo too (about 90: the deep plan of swe_plan.h), then the
+// second for its own.  Every value is the same function of the same operands
+// as in the two launches of k_stage_tiled, so the states are the same bits.
+// While a compute unit holds few tiles a launch costs its chain of latencies
+// (descriptor, lists, states, two barriers, the CFL commit), not its work: one
+// chain with about 250 first-stage edges per 64 cells instead of 110 is
+// shorter than two.  Superbee FP32, per step, two launches and one: 12.2 and
+// 9.5 us on 1,600 cells, 12.4 and 9.4 on 20,160, 13.3 and 12.0 on 78,400,
+// 15.7 and 19.2 on 160,000; FP64 14.8 and 12.2, 15.1 and 12.3, and on 40,000
+// cells 15.9 and 14.9, on 78,400 19.1 and 22.5.  Each stage's first round of
+// edges is loaded ahead (10.2 us on 20,160 cells before); 320 and 512 threads
+// gain nothing where the chip is not full and lose from 20,160 cells FP64 on.
+constexpr int kStepTile = 64, kStepThreads = 256;
+
+template <typename T> size_t step_lds(int hs, int dhs)
+{
+    return sizeof(T) * (4 * (size_t)(kStepTile + hs + dhs) + 9 * (size_t)(kStepTile + hs) + 4 * (size_t)kStepTile);
+}
+
+template <typename T, int LIM>
+__global__ void __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_step_tiled(StageArgs<T> args)
+{
+    constexpr int TILE = kStepTile, NT = kStepThreads;
+    using T4 = typename V4<T>::type;
+    using T2 = typename V2<T>::type;
+    static_assert(NT >= TILE + kDeepHalo, "a thread per cell of the first stage");
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ CflVal<T> sCfl[NT / 64];
+    __shared__ double sStep;
+    const int SA = TILE + args.hs;  // slots of the cells whose first stage is computed
+    T4 *const sP = reinterpret_cast<T4 *>(smem);
+    T4 *const sV = sP + SA + args.dhs;                      // the tile's states after the first stage
+    T *const sF = reinterpret_cast<T *>(sV + TILE);         // component f of half-edge m, slot l at (3 f + m) SA + l
+    clock_upkeep(args_again<T>());
+    const T g = args.g, eps = args.eps;
+    const int cl = threadIdx.x, tile = xcd_tile(blockIdx.x, gridDim.x);
+    const bool dt_wave = lane_value((int)(threadIdx.x >> 6), 0) == NT / 64 - 1;
+    const StageArgs<T> &a = args_again<T>();
+    const int4 d = a.tdesc[tile], dd = a.ddesc[tile];
+    const int *halo = a.thalo + (size_t)tile * a.hs, *dhalo = a.dhalo + (size_t)tile * a.dhs;
+    const int c0 = d.x;
+    const auto cell = [&](int slot) -> int {  // -1: an empty slot
+        if (slot < TILE) return slot < d.y ? c0 + slot : -1;
+        if (slot < SA) return ldx(halo, slot - TILE);
+        return slot < SA + a.dhs ? ldx(dhalo, slot - SA) : -1;
+    };
+    // ---- states into LDS: this thread's cell, then further slots
+    const int id = cell(cl);
+    const uint2 *const ent = a.dent + (size_t)tile * a.des, *const ent2 = a.tent + (size_t)tile * a.es;
+    const T2 *nrm = a.dnrm + (size_t)tile * a.des, *nrm2 = a.tnrm + (size_t)tile * a.es;
+    const T4 *wgt = a.dwgt + (size_t)tile * a.des, *wgt2 = a.twgt + (size_t)tile * a.es;
+    // each stage's first round of edges is on its way early
+    uint2 en = make_uint2(0u, 0u);
+    T2 nn{};
+    T4 ww{};
+    const int nt1 = dd.w & 0xffff, nt2 = d.w & 0xffff;
+    if (cl < nt1) {
+        en = ldx(ent, cl);
+        nn = ldx(nrm, cl);
+        ww = ldx(wgt, cl);
+    }
+    DtLoads dtl{};
+    if (dt_wave) dtl = one_wave_loads(a.clock, a.ncopy, a.slot_cur, 0, a.dt_fixed);
+    const auto put = [&](int slot, const T4 &U) {
+        const Prim<T> p = prim(U, eps);
+        T4 v;
+        v.x = p.h; v.y = p.b; v.z = p.u; v.w = p.v;
+        sP[slot] = v;
+    };
+    const bool first = cl < SA && id >= 0;  // this thread updates slot cl
+    const bool own = first && cl < TILE;
+    T4 Uc{};
+    T lam0 = T(0), lam1 = T(0), lam2 = T(0), man2 = T(0);
+    if (id >= 0) {
+        Uc = ldx(a.Uin, id);
+        put(cl, Uc);
+    }
+    for (int j = cl + NT; j < SA + a.dhs; j += NT) {
+        const int k = cell(j);
+        if (k >= 0) put(j, ldx(a.Uin, k));
+    }
+    if (first) {
+        lam0 = ldx(a.he_lam, id);
+        lam1 = ldx(a.he_lam, a.n + id);
+        lam2 = ldx(a.he_lam, 2 * a.n + id);
+        man2 = manning(a, 0, id);
+    }
+    __syncthreads();
+    if (dt_wave) {
+        const double dt = one_wave_dt(dtl, a.ncopy, a.cfl_rule, a.cfl, a.dt_max, a.dt_fixed);
+        if ((threadIdx.x & 63) == 0) sStep = dt;
+    }
+    const T lam[3] = {lam0, lam1, lam2};
+    T nh = T(0), nu = T(0), nv = T(0), lsum = T(0);
+    int flags = 0;
+    T h = Uc.x, hu = Uc.y, hv = Uc.z;  // what this thread's cell is updated from
+#pragma unroll 1
+    for (int stage = 0; stage < 2; ++stage) {
+        // ---- edges: of all first-stage cells, then of the tile's
+        const uint2 *const e_ = stage ? ent2 : ent;
+        const T2 *const n_ = stage ? nrm2 : nrm;
+        const T4 *const w_ = stage ? wgt2 : wgt;
+        const int x = stage ? d.w : dd.w, nt = x & 0xffff, last = stage ? TILE : SA;
+        for (int i = cl; i < nt; i += NT) {
+            if (i >= NT) {
+                en = ldx(e_, i);
+                nn = ldx(n_, i);
+                ww = ldx(w_, i);
+            }
+            const uint2 e = en;
+            const T4 w = ww;
+            const int iL = e.x & 1023u, iR = (e.x >> 10) & 1023u, mL = (e.x >> 20) & 3u,
+                      mR = (e.x >> 22) & 3u;
+            const int iLa = e.y & 1023u, iLb = (e.y >> 10) & 1023u, iRa = (e.y >> 20) & 1023u,
+                      iRb = (e.y >> 30 << 8) | (e.x >> 24);
+            T fL[3], fR[3];
+            edge_shares<T, true, LIM>(sP, iL, iR, iLa, iLb, iRa, iRb, nn.x, nn.y, w, T(0), T(0), 0.0f, 0.0f, g,
+                                      eps, fL, fR);
+            if (iL < last) {
+#pragma unroll
+                for (int f = 0; f < 3; ++f) sF[(3 * f + mL) * SA + iL] = fL[f];
+            }
+            if (iR < last) {
+#pragma unroll
+                for (int f = 0; f < 3; ++f) sF[(3 * f + mR) * SA + iR] = fR[f];
+            }
+        }
+        for (int i = nt + cl; i < nt + (x >> 16); i += NT) {
+            const unsigned e = ldx(e_, i).x;
+            const int l = e & 1023u, m = (e >> 20) & 3u, k = -(int)(e >> 24);
+            const T2 nb = ldx(n_, i);
+            T G[3];
+            boundary_share<T, T4>(args_again<T>(), k, stage ? sV[l] : ldx(args_again<T>().Uin, cell(l)), nb.x,
+                                  nb.y, 0, stage != 0, G);
+#pragma unroll
+            for (int f = 0; f < 3; ++f) sF[(3 * f + m) * SA + l] = G[f];
+        }
+        if (!stage && cl < nt2) {
+            en = ldx(ent2, cl);
+            nn = ldx(nrm2, cl);
+            ww = ldx(wgt2, cl);
+        }
+        __syncthreads();
+        // ---- update; after the first stage the new values take the slots
+        if (stage ? own : first) {
+            const T dt = T(sStep);
+            T acc0 = T(0), acc1 = T(0), acc2 = T(0);
+            lsum = T(0);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                acc0 += lam[m] * sF[m * SA + cl];
+                acc1 += lam[m] * sF[(3 + m) * SA + cl];
+                acc2 += lam[m] * sF[(6 + m) * SA + cl];
+                lsum += lam[m];
+            }
+            flags |= cell_update(h, hu, hv, acc0, acc1, acc2, dt, man2, g, eps, nh, nu, nv);
+            if (!stage) {
+                h = nh; hu = nu; hv = nv;
+                T4 V;
+                V.x = nh; V.y = nu; V.z = nv; V.w = Uc.w;
+                put(cl, V);
+                if (own) sV[cl] = V;
+            }
+        }
+        if (!stage) __syncthreads();
+    }
+    CflVal<T> cfl = cfl_none<T>();
+    const StageArgs<T> &b = args_again<T>();
+    // (a halo cell's bits are reported by its own tile)
+    if (own) {
+        nh = T(0.5) * (Uc.x + nh);
+        nu = T(0.5) * (Uc.y + nu);
+        nv = T(0.5) * (Uc.z + nv);
+        if (nh <= eps) { nu = T(0); nv = T(0); }
+        T4 out;
+        out.x = nh; out.y = nu; out.z = nv; out.w = Uc.w;
+        stx(b.Uout, id, out);
+        if (flags) atomicOr(b.health, flags);
+        if (nh > eps) {
+            const T r = frcp(nh);
+            const T u = nu * r, v = nv * r;
+            const T lm = sqrt(u * u + v * v) + sqrt(g * nh);
+            cfl = cfl_cell<T>(b.cfl_rule, 0, fdiv(T(2), lsum), lm);
+        }
+    }
+    CflVal<T> acc = cfl_none<T>();
+    wave_gather(acc, cfl, b.cfl_rule);
+    gather_commit(b.clock, b.ncopy, b.slot_next, b.cfl_rule, acc, sCfl);
 }
 
 // Tiled WAF stage (Euler) on the same tile plan:
@@ -1561,6 +1783,7 @@ void drop_graphs(swe_ctx *c)
 void release_mesh(swe_ctx *c)
 {
     for (TilePlan &p : c->plans) release_plan(c, p);
+    release_plan(c, c->deep);
     drop_graphs(c);
     dfree(c, c->nbr); dfree(c, c->cell); dfree(c, c->man2); dfree(c, c->rad); dfree(c, c->he_geo); dfree(c, c->he_dist);
     dfree(c, c->he_co); dfree(c, c->he_lam); dfree(c, c->he_gam); dfree(c, c->he_dfw);
@@ -1656,9 +1879,9 @@ inline int halo_bound(int tile) { return tile == 64 ? 576 : (tile == 128 ? 160 :
 template <int TILE>
 void launch_plan(swe_ctx *c, int nt, int write, int hs, int es, void *desc, void *halo, void *ent)
 {
-    hipLaunchKernelGGL(k_tile_plan<TILE>, dim3(nt), dim3(TILE < 256 ? TILE : 256), 0, c->stream,
+    hipLaunchKernelGGL((k_tile_plan<TILE, false>), dim3(nt), dim3(TILE < 256 ? TILE : 256), 0, c->stream,
                        (const int4 *)c->nbr, (int)(c->cfg.scheme != SWE_HLLC1), write, hs, es,
-                       (int4 *)desc, (int *)halo, (uint2 *)ent);
+                       (int4 *)desc, (int *)halo, (uint2 *)ent, nullptr, 0);
 }
 
 void launch_plan_any(swe_ctx *c, int tile, int nt, int write, int hs, int es, void *desc, void *halo,
@@ -1674,6 +1897,7 @@ template <typename T> void launch_plan_geometry(swe_ctx *c, const TilePlan &p)
 {
     hipLaunchKernelGGL(k_plan_geometry<T>, dim3(p.ntiles), dim3(256), 0, c->stream, c->n_total, p.tile,
                        (const int4 *)p.desc, (const int *)p.halo, (const uint2 *)p.ent, p.hs, p.es,
+                       (const int *)p.base, p.base_hs,
                        (const typename V4<T>::type *)c->he_co, (const T *)c->he_gam, (const T *)c->he_dfw,
                        (typename V2<T>::type *)p.nrm, (typename V4<T>::type *)p.wgt,
                        (typename V2<T>::type *)p.gam, (T *)p.dfw);
@@ -1721,6 +1945,22 @@ int plan_ranges(swe_ctx *c, int tile, std::vector<int4> &rg, bool &ok)
     return SWE_OK;
 }
 
+// One allocation for a plan's arrays (sizes set).
+int alloc_plan(swe_ctx *c, TilePlan &q)
+{
+    const bool muscl = c->cfg.scheme == SWE_MUSCL, waf = c->cfg.scheme == SWE_WAF;
+    const bool learned = muscl && c->cfg.limiter == SWE_LEARNED;
+    const size_t nt = q.ntiles, ne = nt * q.es, ts = c->tsize;
+    const size_t sz[7] = {16 * nt, 4 * nt * q.hs, 8 * ne, 2 * ts * ne, muscl ? 4 * ts * ne : 0,
+                          learned ? 2 * ts * ne : 0, waf ? ts * ne : 0};
+    size_t off[8] = {0};
+    for (int i = 0; i < 7; ++i) off[i + 1] = off[i] + ((sz[i] + 255) & ~(size_t)255);
+    HIP_OK(c, dalloc(c, &q.mem, off[7]));
+    void **at[7] = {&q.desc, &q.halo, &q.ent, &q.nrm, &q.wgt, &q.gam, &q.dfw};
+    for (int i = 0; i < 7; ++i) *at[i] = sz[i] ? (char *)q.mem + off[i] : nullptr;
+    return SWE_OK;
+}
+
 // The tile plan for tiles of B cells, or of a smaller size where their halos
 // do not fit.  Built on first use, on the context's stream; waits for it.
 int ensure_plan(swe_ctx *c, int B, TilePlan **out)
@@ -1743,19 +1983,10 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out)
         }
         q.hs = std::max(4, (q.hs + 3) & ~3);
         q.es = std::max(tile, (q.es + 15) & ~15);  // the kernel's first round loads `tile` places
-        const bool muscl = c->cfg.scheme == SWE_MUSCL;
-        const bool learned = muscl && c->cfg.limiter == SWE_LEARNED;
-        const size_t nt = q.ntiles, ne = nt * q.es, ts = c->tsize;
-        const bool waf = c->cfg.scheme == SWE_WAF;
-        const size_t sz[7] = {16 * nt, 4 * nt * q.hs, 8 * ne, 2 * ts * ne, muscl ? 4 * ts * ne : 0,
-                              learned ? 2 * ts * ne : 0, waf ? ts * ne : 0};
-        size_t off[8] = {0};
-        for (int i = 0; i < 7; ++i) off[i + 1] = off[i] + ((sz[i] + 255) & ~(size_t)255);
-        HIP_OK(c, dalloc(c, &q.mem, off[7]));
+        const int arc = alloc_plan(c, q);
+        if (arc != SWE_OK) return arc;
         p = q;  // owned by the context from here on
-        void **at[7] = {&p.desc, &p.halo, &p.ent, &p.nrm, &p.wgt, &p.gam, &p.dfw};
-        for (int i = 0; i < 7; ++i) *at[i] = sz[i] ? (char *)p.mem + off[i] : nullptr;
-        hipError_t e = hipMemcpyAsync(p.desc, rg.data(), sz[0], hipMemcpyHostToDevice, c->stream);
+        hipError_t e = hipMemcpyAsync(p.desc, rg.data(), 16 * rg.size(), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) {
             launch_plan_any(c, tile, p.ntiles, 1, p.hs, p.es, p.desc, p.halo, p.ent);
             if (c->tsize == 8) launch_plan_geometry<double>(c, p);
@@ -1769,6 +2000,66 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out)
         *out = &p;
         return SWE_OK;
     }
+}
+
+// The deep plan over the plain one of 64-cell tiles.  deep.tile = -1, and
+// two launches per step, where a halo or the LDS is over its bound or there is
+// no memory for it (about 140 bytes per cell FP32).
+int ensure_deep(swe_ctx *c, const TilePlan &base)
+{
+    if (c->deep.tile != 0) return SWE_OK;
+    constexpr int TILE = kStepTile;
+    c->deep.tile = -1;
+    if (base.hs > kDeepHalo) return SWE_OK;
+    TilePlan q;
+    q.tile = TILE;
+    q.ntiles = base.ntiles;
+    q.base = base.halo;
+    q.base_hs = base.hs;
+    std::vector<int4> rg(base.ntiles), dd(base.ntiles);
+    const size_t bytes = sizeof(int4) * rg.size();
+    void *buf = nullptr;
+    HIP_OK(c, dalloc(c, &buf, bytes));
+    hipError_t e = hipMemcpyAsync(buf, base.desc, bytes, hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(rg.data(), base.desc, bytes, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL((k_tile_plan<TILE, true>), dim3(q.ntiles), dim3(TILE), 0, c->stream,
+                           (const int4 *)c->nbr, 1, 0, 0, 0, (int4 *)buf, nullptr, nullptr,
+                           (const int *)q.base, q.base_hs);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(dd.data(), buf, bytes, hipMemcpyDeviceToHost, c->stream);
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    dfree(c, buf);
+    HIP_OK(c, e);
+    HIP_OK(c, es);
+    for (const int4 &r : dd) {
+        q.hs = std::max(q.hs, r.z);
+        q.es = std::max(q.es, r.w);
+    }
+    q.hs = std::max(4, (q.hs + 3) & ~3);
+    q.es = (q.es + 15) & ~15;
+    const size_t lds = c->tsize == 8 ? step_lds<double>(base.hs, q.hs) : step_lds<float>(base.hs, q.hs);
+    if (TILE + base.hs + q.hs > kMaxSlots || lds > 48 * 1024) return SWE_OK;
+    if (alloc_plan(c, q) != SWE_OK) {
+        (void)hipGetLastError();
+        return SWE_OK;
+    }
+    c->deep = q;
+    e = hipMemcpyAsync(q.desc, rg.data(), bytes, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL((k_tile_plan<TILE, true>), dim3(q.ntiles), dim3(TILE), 0, c->stream,
+                           (const int4 *)c->nbr, 1, 1, q.hs, q.es, (int4 *)q.desc, (int *)q.halo,
+                           (uint2 *)q.ent, (const int *)q.base, q.base_hs);
+        if (c->tsize == 8) launch_plan_geometry<double>(c, q);
+        else launch_plan_geometry<float>(c, q);
+        e = hipGetLastError();
+    }
+    const hipError_t es2 = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || es2 != hipSuccess) release_plan(c, c->deep);
+    HIP_OK(c, e);
+    HIP_OK(c, es2);
+    return SWE_OK;
 }
 
 // The plan a step's launch uses, null for the kernels without one.
@@ -1816,10 +2107,34 @@ inline Shape wanted_shape(const swe_ctx *c)
     return s;
 }
 
+// A two-stage step in one launch (k_step_tiled): one scenario, a classic
+// limiter, the shape left to the size, no ghost rows (a part's thin send and
+// ghost layers have halos over the bound), and a mesh whose tiles the chip holds
+// all at once (6 blocks of 256 threads per compute unit FP32, 80 registers; 3
+// FP64, 142).  Beyond, the first stages of the halos cost more than a launch
+// (FP32: 13.8 us in two and 12.8 in one on 98,304 cells, 15.7 and 19.2 on
+// 160,000; FP64: 16.1 and 15.5 on 48,800, 19.1 and 22.5 on 78,400).
+inline bool wants_deep(const swe_ctx *c)
+{
+    const int ncu = c->ncu > 0 ? c->ncu : 256;
+    return uses_plan(c) && c->cfg.scheme == SWE_MUSCL && c->cfg.integrator == SWE_RK2 &&
+           c->cfg.limiter != SWE_LEARNED && c->n_scen == 1 && c->block == 0 && c->wide < 0 &&
+           c->n_owned == c->n_total && c->n_send == 0 &&
+           c->n_total <= (long long)kStepTile * (c->tsize == 8 ? 3 : 6) * ncu;
+}
+
+inline bool steps_deep(const swe_ctx *c) { return c->deep.tile > 0 && wants_deep(c); }
+
 int current_plan(swe_ctx *c, TilePlan **out)
 {
     *out = nullptr;
     if (!uses_plan(c)) return SWE_OK;
+    if (wants_deep(c)) {
+        const int rc = ensure_plan(c, kStepTile, out);
+        if (rc != SWE_OK) return rc;
+        const int rd = ensure_deep(c, **out);
+        if (rd != SWE_OK || c->deep.tile > 0) return rd;
+    }
     return ensure_plan(c, wanted_shape(c).tile, out);
 }
 
@@ -1912,6 +2227,16 @@ template <typename T> KernelFn<T> pick_kernel(int scheme, int lim, int wafm, Sha
         }
     }
     return pick_cell_kernel<T>(scheme, lim, wafm);
+}
+
+template <typename T> KernelFn<T> pick_step(int lim)
+{
+    switch (lim) {
+    case kSuperbee: return k_step_tiled<T, kSuperbee>;
+    case kVanAlbada: return k_step_tiled<T, kVanAlbada>;
+    case kZeroSlope: return k_step_tiled<T, kZeroSlope>;
+    default: return k_step_tiled<T, kMinmod>;
+    }
 }
 
 template <typename T> KernelFn<T> pick_cell_kernel(int scheme, int lim, int wafm)
@@ -2017,13 +2342,30 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
         a.es = plan->es;
         a.ntiles = plan->ntiles;
     }
+    T4 *Ucur = (T4 *)c->U[step & 1];
+    if (plan && steps_deep(c)) {  // both stages in one launch
+        const TilePlan &q = c->deep;
+        a.ddesc = (const int4 *)q.desc;
+        a.dhalo = (const int *)q.halo;
+        a.dent = (const uint2 *)q.ent;
+        a.dnrm = (const typename V2<T>::type *)q.nrm;
+        a.dwgt = (const T4 *)q.wgt;
+        a.dhs = q.hs;
+        a.des = q.es;
+        a.kind = 0;
+        a.Uin = Ucur;
+        a.Uout = (T4 *)c->U[(step + 1) & 1];
+        hipLaunchKernelGGL(pick_step<T>(c->cfg.limiter), dim3(q.ntiles), dim3(kStepThreads),
+                           step_lds<T>(plan->hs, q.hs), c->stream, a);
+        HIP_OK(c, hipGetLastError());
+        return SWE_OK;
+    }
     const int ntiles = plan ? plan->ntiles : (c->n_total + sh.tile - 1) / sh.tile;
     const int threads = plan ? tile_threads(sh.tile, sh.wide) : sh.tile;
     const size_t lds = plan ? plan_lds<T>(c, sh.tile, plan->hs) : 0;
     KernelFn<T> k = pick_kernel<T>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell_kernel, euler);
     dim3 grid(cell_kernel ? ntiles : stage_grid(c, (const void *)k, threads, ntiles, lds));
     const dim3 blk(threads);
-    T4 *Ucur = (T4 *)c->U[step & 1];
     // the learned limiter's phi is evaluated from U^n of the steps whose
     // index is a multiple of phi_every (every step by default; a step between
     // reuses the stored phi): by a kernel of its own ahead of the step, or
@@ -2581,6 +2923,11 @@ int swe_step_kernel(const swe_ctx *c, const char **name, int *launches_per_step)
     const bool cell_kernel = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool learned = c->cfg.scheme == SWE_MUSCL && c->cfg.limiter == SWE_LEARNED;
     const int stages = euler ? 1 : 2;
+    if (steps_deep(c)) {
+        *name = "k_step_tiled";
+        *launches_per_step = 1;
+        return SWE_OK;
+    }
     if (cell_kernel) *name = "k_stage";
     else if (c->cfg.scheme == SWE_WAF) *name = "k_stage_tiled_waf";
     else *name = learned && !c->cfg.phi_in_stage ? "k_stage_tiled+k_limiter_phi" : "k_stage_tiled";
@@ -2688,18 +3035,21 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     const bool cell = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool tiled = uses_plan(c);
     const bool f64 = c->cfg.precision == SWE_F64;
-    for (int B : {64, 128, 256, 512})
+    for (int B : {0, 64, 128, 256, 512})  // 0: both stages in one launch
     for (int W = 0; W < 2; ++W) {  // a thread per cell, or per edge
         if (B == 512 && (!tiled || f64 || c->cfg.scheme == SWE_WAF)) continue;  // FP32 HLLC1 and MUSCL tiles only
         if (W == 1 && (!tiled || B == 512)) continue;
-        for (int persist = 0; persist < 2 && rc == SWE_OK; ++persist) {
+        if (B == 0 && W == 1) continue;
+        for (int persist = 0; persist < (B ? 2 : 1) && rc == SWE_OK; ++persist) {
             c->block = B;
-            c->wide = W == 1;
+            c->wide = B ? W : -1;
             c->grid_persist = -1;  // one tile per block
+            if (B == 0 && !wants_deep(c)) break;
             TilePlan *plan = nullptr;
             rc = current_plan(c, &plan);
             if (rc != SWE_OK) break;
-            if (plan && plan->tile != B) continue;  // its tiles do not fit: a smaller size stands for it
+            if (B == 0 && !steps_deep(c)) break;
+            if (B && plan && plan->tile != B) continue;  // its tiles do not fit: a smaller size stands for it
             if (persist) {
                 const Shape sh{B, W == 1};
                 const int threads = plan ? tile_threads(B, sh.wide) : B;
@@ -2734,6 +3084,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
         if (rc == SWE_OK) rc = prc;
         for (TilePlan &p : c->plans)
             if (&p != plan) release_plan(c, p);
+        if (!steps_deep(c)) release_plan(c, c->deep);
     }
     (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
     (void)hipMemcpyAsync(c->clock, saveK, clock_bytes(c), hipMemcpyDeviceToDevice, c->stream);
@@ -2745,7 +3096,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     drop_graphs(c);
     if (rc != SWE_OK) return rc;
     c->tuned = true;
-    if (block_out) *block_out = best_b;
+    if (block_out) *block_out = best_b ? best_b : kStepTile;
     if (grid_out) *grid_out = best_g;
     return SWE_OK;
 }

@@ -32,6 +32,7 @@ namespace swe {
 
 constexpr unsigned kNoCell = 1023u;
 constexpr int kMaxSlots = 1023;  // 10-bit slots, kNoCell excluded
+constexpr int kDeepHalo = 128;   // largest plain halo of a tile of a DEEP plan
 
 // One block per tile, threads = min(TILE, 256).  desc[tile] comes in with x:
 // the tile's first cell and y: its cells.  write == 0: z becomes the halo's
@@ -39,23 +40,62 @@ constexpr int kMaxSlots = 1023;  // 10-bit slots, kNoCell excluded
 // tile holds several), w the edges to other cells and, from bit 16, the
 // boundary edges, and the tile's halo list (-1 after its end) and entries are
 // written.  ring2: list the far cells' other neighbours too.
-template <int TILE>
+//
+// DEEP: the plan of a whole two-stage step in one launch.  The cells are the
+// tile's and, in the slots from TILE on, those of its plain halo (base, base_hs
+// places, -1 after its end): their first stage is computed too.  The halo is
+// theirs, in the slots from TILE + base_hs on, and the entries are all of
+// their edges.
+template <int TILE, bool DEEP>
 __global__ void __launch_bounds__(TILE < 256 ? TILE : 256)
-k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, int *halo, uint2 *ent)
+k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, int *halo, uint2 *ent,
+            const int *base, int base_hs)
 {
-    constexpr int NT = TILE < 256 ? TILE : 256, CPT = TILE / NT;
-    constexpr int CAP = TILE * 9 <= 1024 ? 1024 : (TILE * 9 <= 2048 ? 2048 : (TILE * 9 <= 4096 ? 4096 : 8192));
+    constexpr int NT = TILE < 256 ? TILE : 256, CELLS = TILE + (DEEP ? kDeepHalo : 0);
+    constexpr int CAP = CELLS * 9 <= 1024 ? 1024 : (CELLS * 9 <= 2048 ? 2048 : (CELLS * 9 <= 4096 ? 4096 : 8192));
+    __shared__ int sBase[DEEP ? kDeepHalo : 1];
+    __shared__ int sNb;
     __shared__ int sC[CAP];
     __shared__ int sScan[NT];
     __shared__ unsigned long long sScan64[NT];
     __shared__ int sCnt, sUniq;
     const int t = threadIdx.x, tile = blockIdx.x, c0 = desc[tile].x, c1 = c0 + desc[tile].y;
-    if (t == 0) sCnt = 0;
+    const int nown = c1 - c0;
+    if (t == 0) { sCnt = 0; sNb = 0; }
     __syncthreads();
-    const auto inside = [&](int k) { return k >= c0 && k < c1; };
+    if constexpr (DEEP) {
+        int mine = 0;
+        for (int i = t; i < base_hs; i += NT) {
+            const int k = base[(size_t)tile * base_hs + i];
+            sBase[i] = k;
+            mine += k >= 0;
+        }
+        atomicAdd(&sNb, mine);
+        __syncthreads();
+    }
+    const int nbase = sNb, ncell = nown + nbase;
+    // place of cell k in an ascending list, -1 if it is not there
+    const auto find = [](const int *list, int m, int k) {
+        int lo = 0, hi = m;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (list[mid] < k) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo < m && list[lo] == k ? lo : -1;
+    };
+    // slot of a cell of the tile, -1 outside
+    const auto inner = [&](int k) {
+        if (k >= c0 && k < c1) return k - c0;
+        const int j = DEEP ? find(sBase, nbase, k) : -1;
+        return j < 0 ? -1 : TILE + j;
+    };
+    const auto inside = [&](int k) { return inner(k) >= 0; };
+    const auto cell_at = [&](int i) { return i < nown ? c0 + i : sBase[DEEP ? i - nown : 0]; };
+    const int per = (ncell + NT - 1) / NT;  // cells of a thread, contiguous
     const auto third = [](const int4 &v, int m) { return m == 0 ? v.x : (m == 1 ? v.y : v.z); };
-    for (int c = c0 + t; c < c1; c += NT) {
-        const int4 q = nbr[c];
+    for (int ic = t; ic < ncell; ic += NT) {
+        const int4 q = nbr[cell_at(ic)];
         for (int m = 0; m < 3; ++m) {
             const int k = third(q, m);
             if (k < 0 || inside(k)) continue;
@@ -125,10 +165,8 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
     // edges: counts per cell (inside | outside | boundary, 21 bits each)
     unsigned long long mine = 0;
     int smin = 0x7fffffff, smax = -1;
-    for (int i = 0; i < CPT; ++i) {
-        const int c = c0 + t * CPT + i;
-        if (c >= c1) break;
-        const int4 q = nbr[c];
+    for (int i = t * per; i < (t + 1) * per && i < ncell; ++i) {
+        const int4 q = nbr[cell_at(i)];
         const int s = (int)((unsigned)q.w >> kScenShift);
         smin = s < smin ? s : smin;
         smax = s > smax ? s : smax;
@@ -163,26 +201,20 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
     if (t == 0) desc[tile] = make_int4(c0, c1 - c0, mixed ? -1 : first, (ni + no) | (nb << 16));
     for (int i = t; i < hs; i += NT) halo[(size_t)tile * hs + i] = i < nh ? sC[i] : -1;
     const auto slot = [&](int k) -> unsigned {
-        if (inside(k)) return (unsigned)(k - c0);
-        int lo = 0, hi = nh - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (sC[mid] < k) lo = mid + 1;
-            else hi = mid;
-        }
-        return (unsigned)(TILE + lo);
+        const int in = inner(k);
+        return (unsigned)(in >= 0 ? in : TILE + (DEEP ? base_hs : 0) + find(sC, nh, k));
     };
     uint2 *e = ent + (size_t)tile * es;
     int ai = (int)(before & 0x1fffff), ao = ni + (int)((before >> 21) & 0x1fffff),
         ab = ni + no + (int)(before >> 42);
-    for (int i = 0; i < CPT; ++i) {
-        const int c = c0 + t * CPT + i;
-        if (c >= c1) break;
+    for (int i = t * per; i < (t + 1) * per && i < ncell; ++i) {
+        const int c = cell_at(i);
+        const unsigned sc = (unsigned)(i < nown ? i : TILE + i - nown);
         const int4 q = nbr[c];
         for (int m = 0; m < 3; ++m) {
             const int k = third(q, m);
             if (k < 0) {
-                e[ab++] = make_uint2((unsigned)(c - c0) | (kNoCell << 10) | ((unsigned)m << 20) |
+                e[ab++] = make_uint2(sc | (kNoCell << 10) | ((unsigned)m << 20) |
                                          ((unsigned)(-k) << 24), 0u);
                 continue;
             }
@@ -198,7 +230,7 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
             if (ka < 0) ka = kb;
             if (kb < 0) kb = ka;
             if (ka < 0) ka = kb = k;
-            const unsigned sc = (unsigned)(c - c0), sk = slot(k);
+            const unsigned sk = slot(k);
             unsigned xa = sc, xb = sc, ya = sk, yb = sk;
             if (ring2) { xa = slot(ca); xb = slot(cb); ya = slot(ka); yb = slot(kb); }
             const unsigned L = isL ? sc : sk, R = isL ? sk : sc, mL = isL ? m : jb, mR = isL ? jb : m;
@@ -217,21 +249,28 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_plan_geometry(int n, int TILE, const int4 *desc, const int *halo, const uint2 *ent, int hs, int es,
+                const int *base, int base_hs,
                 const typename V4<T>::type *he_co, const T *he_gam, const T *he_dfw,
                 typename V2<T>::type *nrm, typename V4<T>::type *wgt, typename V2<T>::type *gam, T *dfw)
 {
     const int tile = blockIdx.x, c0 = desc[tile].x, nt = (desc[tile].w & 0xffff) + (desc[tile].w >> 16);
+    // base: a DEEP plan (base_hs is 0 otherwise)
+    const auto cell = [&](int slot) {
+        if (slot < TILE) return c0 + slot;
+        slot -= TILE;
+        return slot < base_hs ? base[(size_t)tile * base_hs + slot] : halo[(size_t)tile * hs + slot - base_hs];
+    };
     for (int i = threadIdx.x; i < nt; i += blockDim.x) {
         const size_t at = (size_t)tile * es + i;
         const unsigned x = ent[at].x;
         const int L = x & 1023u, R = (x >> 10) & 1023u, mL = (x >> 20) & 3u, mR = (x >> 22) & 3u;
-        const int cL = L < TILE ? c0 + L : halo[(size_t)tile * hs + (L - TILE)];
+        const int cL = cell(L);
         const auto a = he_co[(size_t)mL * n + cL];
         typename V2<T>::type v;
         v.x = a.x; v.y = a.y;
         nrm[at] = v;
         if (R == (int)kNoCell) continue;
-        const int cR = R < TILE ? c0 + R : halo[(size_t)tile * hs + (R - TILE)];
+        const int cR = cell(R);
         if (wgt) {
             const auto b = he_co[(size_t)mR * n + cR];
             typename V4<T>::type w;
