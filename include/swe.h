@@ -145,9 +145,10 @@ typedef struct {
                           network in a kernel of its own ahead of each step; 1 evaluates
                           it inside the step's first stage (phi stored for the second;
                           the far side of a tile-crossing edge evaluated where it is
-                          needed), which saves that kernel's loads but adds its
-                          arithmetic to a stage that is already half arithmetic-bound:
-                          slower on the meshes measured.  Same results either way. */
+                          needed), which saves that kernel's launch and loads but
+                          adds its arithmetic to a stage: faster on small meshes (15.6
+                          against 18.2 us per step on 20,160 cells), equal at 250,000,
+                          slower above.  Same results either way. */
 } swe_config;
 
 /* One sub-domain (or a whole mesh: n_owned == n_total, n_peers == 0).

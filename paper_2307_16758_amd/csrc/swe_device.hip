@@ -1,10 +1,13 @@
-// Device runtime of libswe.so: the fused stage kernel of the explicit
+// Device runtime of libswe.so: the fused stage kernels of the explicit
 // shallow-water step (Delmas & Soulaimani, Sec. 6.1 - 6.2), the CFL
 // reduction, ghost packing (Sec. 6.4) and the C ABI of include/swe.h.
 //
-// One thread per cell.  Cells are numbered in Morton order (send cells
-// first), so a block's 1- and 2-ring gathers stay in the XCD's L2; blocks are
-// remapped so that each of the 8 XCDs sweeps one contiguous range of tiles.
+// Tiled kernels (k_stage_tiled, k_stage_tiled_waf, k_step_tiled): a block
+// owns consecutive cells and evaluates every edge of theirs once, from the
+// tile plan of swe_plan.h; k_stage, the general form, is one thread per cell.
+// Cells are numbered in Morton order (send cells first), so a tile's halo is
+// short and stays in the XCD's L2; blocks are remapped so that each of the 8
+// XCDs sweeps one contiguous range of tiles.
 // Every interior edge flux is evaluated in the canonical orientation (L = the
 // cell of smaller global id, L's normal) from identical operands wherever it
 // is evaluated, so the two mass contributions cancel bitwise and results do
@@ -365,15 +368,12 @@ template <typename T> struct StageArgs {
     int n, n_scen;
     const int4 *nbr;
     const T4 *cell, *he_geo, *he_dist;
-    const T *man2;  // Manning n^2 per cell (tiled MUSCL kernel: its only per-cell record)
-    // per half-edge, edge-major (m * n + c): nx, ny, d_mid / d_up, d_mid / d_fwd;
-    // L / area; d_mid / d_central
-    const T4 *he_co;
-    const T *he_lam, *he_gam;
+    const T *man2;    // Manning n^2 per cell (read where a scenario has several values)
+    const T *he_lam;  // L / area per half-edge, edge-major (m * n + c)
     const T *rad;  // inscribed radius per cell (tiled WAF)
     const T4 *Uin, *U0;
     T4 *Uout;
-    // tile plan of the tiled kernels (see PlanView)
+    // tile plan of the tiled kernels (swe_plan.h)
     const int4 *tdesc;
     const int *thalo;
     const uint2 *tent;
@@ -382,7 +382,7 @@ template <typename T> struct StageArgs {
     const typename V2<T>::type *tgam;
     const T *tdfw;
     int hs, es, ntiles;
-    // DEEP plan (k_step_tiled)
+    // deep plan (k_step_tiled)
     const int4 *ddesc;
     const int *dhalo;
     const uint2 *dent;
@@ -806,7 +806,7 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<T> a)
 // side corrections and centred bed term become
 // g (h- + h)(eta- - eta) / 2; hllc_dev gives F1 - g h*^2 / 2 per side).
 //
-// What bounds it: on 13M cells HBM (281 us per stage launch; about 112 B per
+// What bounds it: on 13M cells HBM (268 us per stage launch; about 108 B per
 // cell at 5.2 TB/s, a large copy reaches 4.9), on a million cells, whose
 // arrays stay in the Infinity Cache, vector arithmetic and the launch's ends
 // (22 us).  The cell-by-cell form before the plan took 424 and 34 us: each
@@ -1396,8 +1396,8 @@ k_step_tiled(StageArgs<T> args)
 //     (printed form) into LDS;
 //  3. cell sums, update, Manning, cleanup, CFL commit.
 // The operands of an edge are the same in whichever tile it is evaluated.
-// On the wet million-cell dam break a step takes 35.5 us in 256-cell tiles
-// (36.5 and 37.1 in 128- and 64-cell ones), 45.5 before the tile plan (two
+// On the wet million-cell dam break a step takes 30.5 us in 256-cell tiles
+// (32.1 and 35.6 in 128- and 64-cell ones), 45.5 before the tile plan (two
 // LDS records per half-edge filled by a first sweep, the far sides of
 // tile-crossing edges gathered in the second); three quarters of the launch
 // is vector arithmetic.
@@ -2071,13 +2071,14 @@ inline bool uses_plan(const swe_ctx *c)
 // Tile and threads of the tiled kernels unless the configuration or the
 // autotuner chose them.  While the chip holds every tile at once a launch
 // costs its tiles' chain of latencies: tiles of 128 cells with a thread per
-// edge (per step: 12.3 us against 15.3 with a thread per cell on 20,160 cells
-// MUSCL FP32, 19.5 against 23.1 on 101,202 cells FP64), of 64 cells while
-// there is a compute unit for each (7.3 against 7.6 us on 16,000 cells
-// first-order FP64).  Larger meshes are bound by what the compute units keep
-// in flight: a thread per cell (on a million cells MUSCL FP32 49 against 60
-// us; learned limiter 37.3 against 39.0 on 250,000) and 256 cells (44.6 us
-// against 48.1 and 51.3 in tiles of 128 and 64 cells).
+// edge (per step: 5.5 us against 6.4 with a thread per cell on 20,160 cells
+// first-order FP32, 17.8 against 21.2 at best on 101,202 cells MUSCL FP64), of
+// 64 cells while there is a compute unit for each (6.2 against 6.4 us on
+// 16,000 cells first-order FP64).  Larger meshes are bound by what the compute
+// units keep in flight: a thread per cell (on a million cells MUSCL FP32 44.0
+// against 52.0 us at best with one per edge; learned limiter 31.9 against 33.7
+// on 250,000) and 256 cells (44.0 us against 46.3 and 50.1 in tiles of 128 and
+// 64 cells).
 //
 // Geometry loaded as a stream where a step's arrays are beyond what the 256 MB
 // Infinity Cache holds most of, so that it holds the states (per step, plain
@@ -2089,8 +2090,8 @@ constexpr long long kCachedBytes = 300LL << 20;
 inline Shape wanted_shape(const swe_ctx *c)
 {
     const int n = c->n_total, ncu = c->ncu > 0 ? c->ncu : 256;
-    // blocks of 256 threads a compute unit holds: 7 (FP32, 72 registers) or
-    // 4 (FP64, 128 registers)
+    // blocks of 256 threads a compute unit is counted to hold: 7 (FP32) or 4
+    // (FP64, 128 registers)
     const int held = c->tsize == 8 ? 4 : 7;
     const bool few = (long long)n <= 128LL * held * ncu;
     Shape s{c->block, few};
@@ -2268,7 +2269,7 @@ inline int resident_blocks(const swe_ctx *c, const void *kernel, int B, size_t l
 // Blocks of a tiled stage launch: one per tile, or, when the configuration
 // asks for it or the launch spans many rounds of tiles (8 or more), a
 // persistent grid of the blocks the chip holds at once, each sweeping tiles
-// (measured: 2.7% faster on the 13M-cell river; on a mesh of a few rounds
+// (536 against 540 us per step on the 13M-cell river; on a mesh of a few rounds
 // the hardware's own dispatch of one tile per block balances better)
 inline int stage_grid(const swe_ctx *c, const void *kernel, int B, int ntiles, size_t lds)
 {
@@ -2300,9 +2301,7 @@ int launch_step(swe_ctx *c, long long step, double dt_fixed, bool phi_force = fa
     a.man2 = (const T *)c->man2;
     a.he_geo = (const T4 *)c->he_geo;
     a.he_dist = (const T4 *)c->he_dist;
-    a.he_co = (const T4 *)c->he_co;
     a.he_lam = (const T *)c->he_lam;
-    a.he_gam = (const T *)c->he_gam;
     a.rad = (const T *)c->rad;
     a.clock = c->clock;
     a.ncopy = c->ncopy;

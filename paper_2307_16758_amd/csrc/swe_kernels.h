@@ -30,7 +30,8 @@ enum { kHealthNonfinite = 1, kHealthNegDepth = 2, kHealthClipped = 4 };
 // (rule 1), and the maximum of lambda_i, as the bit patterns of non-negative
 // doubles, whose integer order is their numeric order.  Blocks commit to
 // copy (block index mod ncopy), so concurrent atomics spread over ncopy
-// lines; readers reduce the copies.
+// lines; readers reduce the copies.  A fourth slot stages the clock of a
+// state that is being set.
 constexpr int kClockLine = 16;  // 64-bit words per 128-byte line
 enum { kCfqMin = 0, kCfqMax = 1 };
 
