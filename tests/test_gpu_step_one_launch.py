@@ -28,10 +28,12 @@ def _problem(nx, ny, precision, **part):
     return pr, [a.astype(dt) for a in (h, 0.3 * h, 0.1 * h * np.cos(0.07 * x))]
 
 
-def _run(pr, U, kw, steps, dt=0.0, **cfg):
+def _run(pr, U, kw, steps, dt=0.0, series=None, **cfg):
     from paper_2307_16758_amd import swe
     s = swe.Solver(**kw, **cfg)
     s.mesh_upload(pr.mesh)
+    if series:
+        s.set_bc_series(*series)
     s.set_state(*U)
     kernel = s.step_kernel()
     s.step(steps, dt)
@@ -52,7 +54,9 @@ def _same(a, b):
 def test_one_launch_is_two(name, precision, nx, ny):
     pr, U = _problem(nx, ny, precision)
     kw = _kw(name, precision)
-    for cfg in (dict(), dict(cfl_rule=1), dict(dt=0.02)):
+    # the second stage takes its inflow at the end of the step
+    series = ([0.0, 0.3, 0.6, 5.0], [20.0, 90.0, 15.0, 60.0])
+    for cfg in (dict(), dict(cfl_rule=1), dict(dt=0.02), dict(series=series)):
         k1, one = _run(pr, U, kw, 31, **cfg)
         k2, two = _run(pr, U, kw, 31, block=128, **cfg)
         assert k1 == ("k_step_tiled", 1) and k2 == ("k_stage_tiled", 2)
