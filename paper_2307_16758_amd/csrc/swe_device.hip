@@ -1010,20 +1010,24 @@ k_stage_tiled(StageArgs<T> args)
         };
         T4 Uc{};
         if (active) Uc = ldx(a.Uin, c);
+        // (slots without a cell become dry)
         if constexpr (kWide) {
             if (hid >= 0) Uc = ldx(a.Uin, hid);
-            if (active || hid >= 0) put(cl, Uc);
+            if (cl < TILE + a.hs) put(cl, Uc);
         } else {
             if (active) put(cl, Uc);
-            if (hid >= 0) put(TILE + cl, ldx(a.Uin, hid));
+            T4 Uh{};
+            if (hid >= 0) Uh = ldx(a.Uin, hid);
+            if (cl < a.hs) put(TILE + cl, Uh);
         }
         if constexpr (kLrn) {
             if (hid >= 0) sId[hj] = hid;
         }
         for (int j = hj + NT; j < a.hs; j += NT) {
             hid = ldx(halo, j);
-            if (hid < 0) break;
-            put(TILE + j, ldx(a.Uin, hid));
+            T4 Uh{};
+            if (hid >= 0) Uh = ldx(a.Uin, hid);
+            put(TILE + j, Uh);
             if constexpr (kLrn) sId[j] = hid;
         }
         // the update's operands (not wide: loaded there, they would cost
@@ -1075,15 +1079,11 @@ k_stage_tiled(StageArgs<T> args)
                                   ib = side ? iRb : iLb;
                         float f[kMlpIn];
                         T4 Us{}, Uk{}, Ua{}, Ub{};
-                        bool hu = false;
-                        if (edge) {
-                            Us = sU[ic]; Uk = sU[ik]; Ua = sU[ia]; Ub = sU[ib];
-                            hu = ia != ic;
-                        }
-                        // a missing upwind cell's place holds the other one:
-                        // their mean is that one
-                        const bool ok = limiter_features<T, T4>(limiter_cell<T, T4>(Us, g), Us, Uk, edge, Ua, hu,
-                                                                Ub, hu, side ? -nx : nx, side ? -ny : ny,
+                        if (edge) { Us = sU[ic]; Uk = sU[ik]; Ua = sU[ia]; Ub = sU[ib]; }
+                        // a missing upwind cell's place holds the other one
+                        // (their mean is that one), or a dry cell
+                        const bool ok = limiter_features<T, T4>(limiter_cell<T, T4>(Us, g), Us, Uk, edge, Ua, true,
+                                                                Ub, true, side ? -nx : nx, side ? -ny : ny,
                                                                 side ? w.z : w.x, side ? w.w : w.y, eps, f);
                         mlp_write_row(X[lane], f, ok);
                         wave_lds_sync();
@@ -1269,13 +1269,13 @@ k_step_tiled(StageArgs<T> args)
     const bool own = first && cl < TILE;
     T4 Uc{};
     T lam0 = T(0), lam1 = T(0), lam2 = T(0), man2 = T(0);
-    if (id >= 0) {
-        Uc = ldx(a.Uin, id);
-        put(cl, Uc);
-    }
+    if (id >= 0) Uc = ldx(a.Uin, id);
+    if (cl < SA + a.dhs) put(cl, Uc);  // (slots without a cell become dry)
     for (int j = cl + NT; j < SA + a.dhs; j += NT) {
         const int k = cell(j);
-        if (k >= 0) put(j, ldx(a.Uin, k));
+        T4 Uh{};
+        if (k >= 0) Uh = ldx(a.Uin, k);
+        put(j, Uh);
     }
     if (first) {
         lam0 = ldx(a.he_lam, id);
@@ -1457,17 +1457,17 @@ k_stage_tiled_waf(StageArgs<T> args)
         DtLoads dtl{};
         if (find_dt) dtl = one_wave_loads(a.clock, a.ncopy, a.slot_cur, a.n_scen == 1 ? 0 : d.z, a.dt_fixed);
         first = false;
-        const auto put = [&](int slot, int cell) {
-            sU[slot] = ldx(a.Uin, cell);
-            sRad[slot] = ldx(a.rad, cell);
+        const auto put = [&](int slot, int cell) {  // (a slot without a cell becomes dry)
+            T4 U{};
+            if (cell >= 0) {
+                U = ldx(a.Uin, cell);
+                sRad[slot] = ldx(a.rad, cell);
+            }
+            sU[slot] = U;
         };
         if (active) put(cl, c);
-        if (hid >= 0) put(TILE + hj, hid);
-        for (int j = hj + NT; j < a.hs; j += NT) {
-            hid = ldx(halo, j);
-            if (hid < 0) break;
-            put(TILE + j, hid);
-        }
+        if (hj >= 0 && hj < a.hs) put(TILE + hj, hid);
+        for (int j = hj + NT; j < a.hs; j += NT) put(TILE + j, ldx(halo, j));
         T lam0 = T(0), lam1 = T(0), lam2 = T(0), man2 = T(0);
         if (kWide && active) {
             lam0 = ldx(a.he_lam, c);
@@ -1508,11 +1508,10 @@ k_stage_tiled_waf(StageArgs<T> args)
             WafIn<T> w;
             w.eL = L.x + L.w; w.eR = R.x + R.w;
             w.vL = tangential(L, nx, ny, eps); w.vR = tangential(R, nx, ny, eps);
-            // a missing upwind cell's place holds the other one, or the cell
-            // itself where both are missing
-            const bool uL = iLa != iL, uR = iRa != iR;
-            w.hasLu = waf_upwind(sU[iLa], uL, sU[iLb], uL, nx, ny, eps, w.eLu, w.vLu);
-            w.hasRu = waf_upwind(sU[iRa], uR, sU[iRb], uR, nx, ny, eps, w.eRu, w.vRu);
+            // a missing upwind cell's place holds the other one, or a dry cell
+            // where both are missing
+            w.hasLu = waf_upwind(sU[iLa], true, sU[iLb], true, nx, ny, eps, w.eLu, w.vLu);
+            w.hasRu = waf_upwind(sU[iRa], true, sU[iRb], true, nx, ny, eps, w.eRu, w.vRu);
             // hydrostatic reconstruction (first-order states)
             const T be = tmax(L.w, R.w);
             const T hL = tmax(T(0), L.x + L.w - be);
@@ -1981,7 +1980,7 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out)
             q.hs = std::max(q.hs, r.z);
             q.es = std::max(q.es, r.w);
         }
-        q.hs = std::max(4, (q.hs + 3) & ~3);
+        q.hs = (q.hs + 4) & ~3;  // the last slot stays free: the dry one
         q.es = std::max(tile, (q.es + 15) & ~15);  // the kernel's first round loads `tile` places
         const int arc = alloc_plan(c, q);
         if (arc != SWE_OK) return arc;
@@ -2037,7 +2036,7 @@ int ensure_deep(swe_ctx *c, const TilePlan &base)
         q.hs = std::max(q.hs, r.z);
         q.es = std::max(q.es, r.w);
     }
-    q.hs = std::max(4, (q.hs + 3) & ~3);
+    q.hs = (q.hs + 4) & ~3;
     q.es = (q.es + 15) & ~15;
     const size_t lds = c->tsize == 8 ? step_lds<double>(base.hs, q.hs) : step_lds<float>(base.hs, q.hs);
     if (TILE + base.hs + q.hs > kMaxSlots || lds > 48 * 1024) return SWE_OK;

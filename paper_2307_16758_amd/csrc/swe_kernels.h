@@ -480,11 +480,11 @@ __device__ __forceinline__ T limit2(T sb, T sf)
 // Interface values of one side of an interior edge (Sec. 6.2.3), in the
 // edge's frame: qc the side's cell, qk the cell across (h, eta, normal and
 // tangential velocity), A and B the side's upwind cells (h, b, u, v; the same
-// one twice where one is missing).  The distances are folded into weights:
-// al = d_mid / d_up and be = d_mid / d_fwd for the limited slope, ga = d_mid /
-// d_central for the learned limiter's scaled central slope.  r comes in with
-// the first-order values and keeps them where a stencil cell is dry or the
-// reconstructed depth is negative.
+// one twice where one is missing, a dry one where both are).  The distances
+// are folded into weights: al = d_mid / d_up and be = d_mid / d_fwd for the
+// limited slope, ga = d_mid / d_central for the learned limiter's scaled
+// central slope.  r comes in with the first-order values and keeps them where
+// a stencil cell is dry or the reconstructed depth is negative.
 template <typename T, int LIM, typename T4>
 __device__ __forceinline__ void recon_side(Half<T> &r, const T qc[4], const T qk[4], const T4 &A,
                                            const T4 &B, bool wet, T nx, T ny, T al, T be, T ga,

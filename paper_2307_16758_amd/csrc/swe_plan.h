@@ -18,9 +18,11 @@
 //   y: La (10) | Lb (10) | Ra (10) | high 2 bits of Rb
 // mL, mR: the edge's local number in L and R; La, Lb (Ra, Rb): the two other
 // neighbours of L (R).  Where one of them is missing its place holds the
-// other, so their mean is the existing one; where both are, the cell itself
-// (a zero slope: first order).  A boundary edge has R = kNoCell, its cell as
-// L and minus its tag in the last byte of x.
+// other, so their mean is the existing one; where both are, both hold the last
+// halo slot, which no cell takes and the kernels keep dry: the side then stays
+// first order (with the cell itself there, a zero slope, its bed would come
+// back as eta - h, a rounding away from b).  A boundary edge has R = kNoCell,
+// its cell as L and minus its tag in the last byte of x.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,7 +34,7 @@ namespace swe {
 
 constexpr unsigned kNoCell = 1023u;
 constexpr int kMaxSlots = 1023;  // 10-bit slots, kNoCell excluded
-constexpr int kDeepHalo = 128;   // largest plain halo of a tile of a DEEP plan
+constexpr int kDeepHalo = 132;   // largest plain halo (with its dry slot) of a tile of a DEEP plan
 
 // One block per tile, threads = min(TILE, 256).  desc[tile] comes in with x:
 // the tile's first cell and y: its cells.  write == 0: z becomes the halo's
@@ -226,13 +228,16 @@ k_tile_plan(const int4 *nbr, int ring2, int write, int hs, int es, int4 *desc, i
             int ka = third(p, (jb + 1) % 3), kb = third(p, (jb + 2) % 3);
             if (ca < 0) ca = cb;
             if (cb < 0) cb = ca;
-            if (ca < 0) ca = cb = c;
             if (ka < 0) ka = kb;
             if (kb < 0) kb = ka;
-            if (ka < 0) ka = kb = k;
-            const unsigned sk = slot(k);
+            const unsigned sk = slot(k), dry = (unsigned)(TILE + (DEEP ? base_hs : 0) + hs - 1);
             unsigned xa = sc, xb = sc, ya = sk, yb = sk;
-            if (ring2) { xa = slot(ca); xb = slot(cb); ya = slot(ka); yb = slot(kb); }
+            if (ring2) {
+                xa = ca < 0 ? dry : slot(ca);
+                xb = cb < 0 ? dry : slot(cb);
+                ya = ka < 0 ? dry : slot(ka);
+                yb = kb < 0 ? dry : slot(kb);
+            }
             const unsigned L = isL ? sc : sk, R = isL ? sk : sc, mL = isL ? m : jb, mR = isL ? jb : m;
             const unsigned La = isL ? xa : ya, Lb = isL ? xb : yb, Ra = isL ? ya : xa, Rb = isL ? yb : xb;
             e[in ? ai++ : ao++] = make_uint2(L | (R << 10) | (mL << 20) | (mR << 22) | ((Rb & 255u) << 24),
