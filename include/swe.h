@@ -201,7 +201,9 @@ int swe_set_bc_series(swe_ctx *ctx, int n, const double *t, const double *q);
 
 /* State of all n_total cells in the context's precision (float or double),
  * three SoA arrays.  set_state also sets the time and computes the CFL step
- * of the first step.  Negative or non-finite depths are rejected. */
+ * of the first step.  A state with a negative depth or a non-finite value is
+ * refused (SWE_ERR_STATE) and changes nothing: a run that was going on keeps
+ * its state, time, step and health bits. */
 int swe_set_state(swe_ctx *ctx, const void *h, const void *hu, const void *hv, int where,
                   double t);
 int swe_read_state(swe_ctx *ctx, void *h, void *hu, void *hv, int where);

@@ -53,7 +53,7 @@ struct swe_ctx {
     int *health = nullptr, *flag = nullptr, *send_idx = nullptr;
     int *pk_off = nullptr, *pk_ent = nullptr;  // send entries per send cell (CSR)
     int *host = nullptr;  // page-locked: call number of a refused state, health bits
-    int calls = 1;        // number of the last state set (k_begin_state); 0 and 1 are none's
+    int calls = 1;        // number of the last state set (k_check_state); 0 and 1 are none's
     // host mirrors
     std::vector<swe::ScenParams> h_scen;
     std::vector<std::pair<std::vector<double>, std::vector<double>>> series;  // per scenario

@@ -1620,37 +1620,37 @@ k_stage_tiled_waf(StageArgs<T> args)
     if (a.n_scen == 1) gather_commit(a.clock, a.ncopy, a.slot_next, a.cfl_rule, acc, sCfl);
 }
 
-// A new state: the caller's values into U (null: U holds them already) and
-// its CFL partials into the staging slot, in one pass (the copies, the pack
-// and the CFL pass of a 13M-cell state took 260 us apart; 36 B per cell now,
-// about 100 us).  A negative or non-finite value sets *flag and *host_flag to
-// this call's number.
+// A new state takes two launches, so that a refused one changes nothing of
+// the run: the first reads the caller's values (h null: the state in U),
+// gathers the CFL partials in the staging slot and sets *flag and *host_flag
+// to this call's number where a value is negative or not finite; the second
+// takes the state and its clock, or leaves both alone.  The values come from
+// memory twice where no cache holds them (a 13M-cell state: 156 MB more).
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_begin_state(int n, int n_owned, int n_scen, const int4 *nbr, const T *rad, const T *h, const T *hu,
-              const T *hv, const T *b, typename V4<T>::type *U, ClockWord *clock, int ncopy, int rule,
-              T g, T eps, int *flag, int *host_flag, int call, int *health)
+k_check_state(int n, int n_owned, int n_scen, const int4 *nbr, const T *rad, const T *h, const T *hu,
+              const T *hv, const typename V4<T>::type *U, ClockWord *clock, int ncopy, int rule,
+              T g, T eps, int *flag, int *host_flag, int call)
 {
     __shared__ CflVal<T> part[4];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *health = 0;
     CflVal<T> v = cfl_none<T>();
     // one scenario: the grid may be smaller than the mesh
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
-        typename V4<T>::type u;
+        T x, y, z;
         if (h) {
-            u.x = h[c]; u.y = hu[c]; u.z = hv[c]; u.w = b[c];
-            if (!(isfinite(u.x) && isfinite(u.y) && isfinite(u.z)) || u.x < T(0)) {
+            x = h[c]; y = hu[c]; z = hv[c];
+            if (!(isfinite(x) && isfinite(y) && isfinite(z)) || x < T(0)) {
                 *flag = call;
                 *host_flag = call;
             }
-            U[c] = u;
         } else {
-            u = U[c];
+            const typename V4<T>::type u = U[c];
+            x = u.x; y = u.y; z = u.z;
         }
         v.scen = n_scen == 1 ? 0 : (int)((unsigned)nbr[c].w >> kScenShift);
-        if (c < n_owned && u.x > eps) {
-            const T x = fdiv(u.y, u.x), y = fdiv(u.z, u.x);
-            const CflVal<T> w = cfl_cell<T>(rule, v.scen, rad[c], sqrt(x * x + y * y) + sqrt(g * u.x));
+        if (c < n_owned && x > eps) {
+            const T vx = fdiv(y, x), vy = fdiv(z, x);
+            const CflVal<T> w = cfl_cell<T>(rule, v.scen, rad[c], sqrt(vx * vx + vy * vy) + sqrt(g * x));
             v.mn = tmin(v.mn, w.mn);
             v.mx = tmax(v.mx, w.mx);
         }
@@ -1658,26 +1658,40 @@ k_begin_state(int n, int n_owned, int n_scen, const int4 *nbr, const T *rad, con
     cfl_commit(clock, ncopy, kStagingSlot, rule, v, part);
 }
 
-// The clock of a state that k_begin_state found valid: slot 0 takes the
-// staged partials and the time t, slot 1 is cleared; the staging slot is
-// cleared for the next call either way.  One thread per (scenario, copy).
-__global__ void k_begin_clock(ClockWord *clock, int ncopy, int n_scen, double t, const int *flag, int call)
+// The second launch: unless this call's state was refused, U takes it (h null:
+// it holds it already), the health bits are cleared with it, clock slot 0
+// takes the staged partials and the time t, and slot 1 is cleared; the staging
+// slot is cleared for the next call either way.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_begin_state(int n, const T *h, const T *hu, const T *hv, const T *b, typename V4<T>::type *U,
+              ClockWord *clock, int ncopy, int n_scen, double t, const int *flag, int call, int *health)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_scen * ncopy) return;
-    const int s = e / ncopy, j = e % ncopy;
-    const auto at = [&](int slot) { return clock + clock_off(ncopy, s, slot) + (size_t)(1 + j) * kClockLine; };
-    ClockWord *q = at(kStagingSlot);
-    if (*flag != call) {
-        ClockWord *z = at(0), *o = at(1);
-        z[kCfqMin] = q[kCfqMin];
-        z[kCfqMax] = q[kCfqMax];
-        o[kCfqMin] = kInfBits;
-        o[kCfqMax] = 0ull;
-        if (j == 0) clock[clock_off(ncopy, s, 0)] = dbits(t);
+    const int at0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    const bool good = *flag != call;
+    if (good && h) {
+        if (at0 == 0) *health = 0;
+        for (int c = at0; c < n; c += step) {
+            typename V4<T>::type u;
+            u.x = h[c]; u.y = hu[c]; u.z = hv[c]; u.w = b[c];
+            U[c] = u;
+        }
     }
-    q[kCfqMin] = kInfBits;
-    q[kCfqMax] = 0ull;
+    for (int e = at0; e < n_scen * ncopy; e += step) {
+        const int s = e / ncopy, j = e % ncopy;
+        const auto at = [&](int slot) { return clock + clock_off(ncopy, s, slot) + (size_t)(1 + j) * kClockLine; };
+        ClockWord *q = at(kStagingSlot);
+        if (good) {
+            ClockWord *z = at(0), *o = at(1);
+            z[kCfqMin] = q[kCfqMin];
+            z[kCfqMax] = q[kCfqMax];
+            o[kCfqMin] = kInfBits;
+            o[kCfqMax] = 0ull;
+            if (j == 0) clock[clock_off(ncopy, s, 0)] = dbits(t);
+        }
+        q[kCfqMin] = kInfBits;
+        q[kCfqMax] = 0ull;
+    }
 }
 
 // Per-cell values read on their own: inscribed radius and Manning n^2.
@@ -2633,10 +2647,11 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
     // meet on one, few enough that large batches stay small
     c->ncopy = nm <= 64 ? 16 : (nm <= 1024 ? 8 : 4);
     HIP_OK(c, dalloc(c, (void **)&c->clock, clock_bytes(c)));
-    // the staging slots start cleared (call -1 is no state's)
+    // the staging slots start cleared (call -1 is no state's, refused by its flag)
     HIP_OK(c, hipMemsetAsync(c->flag, 0xff, sizeof(int), c->stream));
-    hipLaunchKernelGGL(k_begin_clock, dim3((unsigned)((nm * c->ncopy + 255) / 256)), dim3(256), 0, c->stream,
-                       c->clock, c->ncopy, nm, 0.0, c->flag, -1);
+    hipLaunchKernelGGL(k_begin_state<float>, dim3((unsigned)((nm * c->ncopy + 255) / 256)), dim3(256), 0, c->stream,
+                       0, nullptr, nullptr, nullptr, nullptr, nullptr, c->clock, c->ncopy, nm, 0.0, c->flag, -1,
+                       c->health);
     HIP_OK(c, hipGetLastError());
     {
         std::vector<double> bd(n);
@@ -2788,30 +2803,30 @@ int swe_set_state(swe_ctx *c, const void *h, const void *hu, const void *hv, int
 namespace {
 
 // Queue a new state (h null: the state in U[0]) and its clock, and wait.
-int begin_state(swe_ctx *c, const void *h, const void *hu, const void *hv, double t, int &bad)
+// bad: it was refused.
+template <typename T>
+int begin_state_t(swe_ctx *c, const void *h, const void *hu, const void *hv, double t, int &bad)
 {
-    const int n = c->n_total, B = 256;
-    int G = (n + B - 1) / B;
-    if (c->n_scen == 1) G = std::min(G, 8 * std::max(1, c->ncu));  // a block's partials are committed once
+    using T4 = typename V4<T>::type;
+    const int n = c->n_total, B = 256, all = (n + B - 1) / B, clk = (c->n_scen * c->ncopy + B - 1) / B;
+    const int few = c->n_scen == 1 ? std::min(all, 8 * std::max(1, c->ncu)) : all;  // a block's partials are committed once
     const int call = ++c->calls;
-    if (c->tsize == 8)
-        hipLaunchKernelGGL(k_begin_state<double>, dim3(G), dim3(B), 0, c->stream, n, c->n_owned, c->n_scen,
-                           (const int4 *)c->nbr, (const double *)c->rad, (const double *)h,
-                           (const double *)hu, (const double *)hv, (const double *)c->bed,
-                           (double4 *)c->U[0], c->clock, c->ncopy, c->cfg.cfl_rule, c->cfg.g, c->cfg.eps,
-                           c->flag, c->host, call, c->health);
-    else
-        hipLaunchKernelGGL(k_begin_state<float>, dim3(G), dim3(B), 0, c->stream, n, c->n_owned, c->n_scen,
-                           (const int4 *)c->nbr, (const float *)c->rad, (const float *)h,
-                           (const float *)hu, (const float *)hv, (const float *)c->bed,
-                           (float4 *)c->U[0], c->clock, c->ncopy, c->cfg.cfl_rule, (float)c->cfg.g,
-                           (float)c->cfg.eps, c->flag, c->host, call, c->health);
-    hipLaunchKernelGGL(k_begin_clock, dim3((c->n_scen * c->ncopy + 255) / 256), dim3(256), 0, c->stream,
-                       c->clock, c->ncopy, c->n_scen, t, c->flag, call);
+    hipLaunchKernelGGL(k_check_state<T>, dim3(few), dim3(B), 0, c->stream, n, c->n_owned, c->n_scen,
+                       (const int4 *)c->nbr, (const T *)c->rad, (const T *)h, (const T *)hu, (const T *)hv,
+                       (const T4 *)c->U[0], c->clock, c->ncopy, c->cfg.cfl_rule, T(c->cfg.g), T(c->cfg.eps),
+                       c->flag, c->host, call);
+    hipLaunchKernelGGL(k_begin_state<T>, dim3(h ? std::max(all, clk) : clk), dim3(B), 0, c->stream, n,
+                       (const T *)h, (const T *)hu, (const T *)hv, (const T *)c->bed, (T4 *)c->U[0], c->clock,
+                       c->ncopy, c->n_scen, t, c->flag, call, c->health);
     HIP_OK(c, hipGetLastError());
     HIP_OK(c, hipStreamSynchronize(c->stream));
     bad = c->host[0] == call;
     return SWE_OK;
+}
+
+int begin_state(swe_ctx *c, const void *h, const void *hu, const void *hv, double t, int &bad)
+{
+    return c->tsize == 8 ? begin_state_t<double>(c, h, hu, hv, t, bad) : begin_state_t<float>(c, h, hu, hv, t, bad);
 }
 
 }  // namespace
