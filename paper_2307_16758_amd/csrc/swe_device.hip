@@ -2766,10 +2766,29 @@ static bool device_buffer(const swe_ctx *c, const void *p)
     return (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged) && a.device == c->dev;
 }
 
-// ... that a kernel can read or write as the context's values
+// ... that a kernel can read or write as the context's values, n_total of
+// them within its allocation (one that is too short goes to the copies, which
+// refuse it)
 static bool kernel_buffer(const swe_ctx *c, const void *p)
 {
-    return (uintptr_t)p % c->tsize == 0 && device_buffer(c, p);
+    if ((uintptr_t)p % c->tsize != 0 || !device_buffer(c, p)) return false;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (size_t)((const char *)p - (const char *)base) + c->tsize * (size_t)c->n_total <= size;
+}
+
+// One of the copies between a caller's array and the staging buffer; a refused
+// one leaves no error for the next launch check to report.
+static int stage_copy(swe_ctx *c, void *dst, const void *src, hipMemcpyKind kind)
+{
+    const hipError_t e = hipMemcpyAsync(dst, src, c->tsize * (size_t)c->n_total, kind, c->stream);
+    if (e != hipSuccess) (void)hipGetLastError();
+    HIP_OK(c, e);
+    return SWE_OK;
 }
 
 int swe_set_state(swe_ctx *c, const void *h, const void *hu, const void *hv, int where, double t)
@@ -2786,7 +2805,8 @@ int swe_set_state(swe_ctx *c, const void *h, const void *hu, const void *hv, int
     const hipMemcpyKind kind = where == SWE_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
     for (int i = 0; i < 3; ++i) {
         if (where == SWE_DEVICE && kernel_buffer(c, src[i])) continue;
-        HIP_OK(c, hipMemcpyAsync(tmp + i * ts * n, src[i], ts * n, kind, c->stream));
+        const int rc = stage_copy(c, tmp + i * ts * n, src[i], kind);
+        if (rc != SWE_OK) return rc;
         src[i] = tmp + i * ts * n;
     }
     int bad = 0;
@@ -2869,8 +2889,11 @@ int swe_read_state(swe_ctx *c, void *h, void *hu, void *hv, int where)
     HIP_OK(c, hipGetLastError());
     const hipMemcpyKind kind = where == SWE_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
     void *out[3] = {h, hu, hv};
-    for (int i = 0; i < 3; ++i)
-        if (dst[i] != out[i]) HIP_OK(c, hipMemcpyAsync(out[i], dst[i], ts * n, kind, c->stream));
+    for (int i = 0; i < 3; ++i) {
+        if (dst[i] == out[i]) continue;
+        const int rc = stage_copy(c, out[i], dst[i], kind);
+        if (rc != SWE_OK) return rc;
+    }
     HIP_OK(c, hipStreamSynchronize(c->stream));
     return health_result(c, c->host[1]);
 }
