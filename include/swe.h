@@ -240,7 +240,10 @@ int swe_scenario_times(swe_ctx *ctx, double *t);  /* [n_scenarios]; syncs */
  * reports 64 cells) from the current state, keeps the fastest and
  * restores the state, clocks and time.  The choice never changes results
  * (the tiled kernel is bitwise independent of the tiling, and all builds
- * perform the same operations).
+ * perform the same operations).  A shape whose tiles do not fit the mesh's
+ * numbering, or whose plan there is no memory for, is left out; beside the
+ * saved state one more plan is held at a time than the running shape's and the
+ * fastest one's.
  * Outputs may be NULL; *persistent_grid is the chosen grid (-1: one tile per
  * block).  Untuned contexts sweep tiles with a persistent grid of the blocks
  * the chip holds at once when a launch has 8 or more rounds of tiles, and

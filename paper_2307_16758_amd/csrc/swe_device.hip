@@ -1975,18 +1975,23 @@ int alloc_plan(swe_ctx *c, TilePlan &q)
 }
 
 // The tile plan for tiles of B cells, or of a smaller size where their halos
-// do not fit.  Built on first use, on the context's stream; waits for it.
-int ensure_plan(swe_ctx *c, int B, TilePlan **out)
+// do not fit (exact: null then).  Built on first use, on the context's stream;
+// waits for it.
+int ensure_plan(swe_ctx *c, int B, TilePlan **out, bool exact = false)
 {
+    *out = nullptr;
     for (int tile = B;; tile >>= 1) {
         TilePlan &p = c->plans[tile == 64 ? 0 : (tile == 128 ? 1 : (tile == 256 ? 2 : 3))];
         if (p.tile > 0) { *out = &p; return SWE_OK; }
+        if (p.tile < 0 && exact) return SWE_OK;
         if (p.tile < 0) continue;  // known not to fit
         std::vector<int4> rg;
         bool ok = false;
         const int rc = plan_ranges(c, tile, rg, ok);
         if (rc != SWE_OK) return rc;
-        if (!ok) { p.tile = -1; continue; }  // 64-cell tiles always fit
+        if (!ok) p.tile = -1;  // 64-cell tiles always fit
+        if (!ok && exact) return SWE_OK;
+        if (!ok) continue;
         TilePlan q;
         q.tile = tile;
         q.ntiles = (int)rg.size();
@@ -2032,7 +2037,10 @@ int ensure_deep(swe_ctx *c, const TilePlan &base)
     std::vector<int4> rg(base.ntiles), dd(base.ntiles);
     const size_t bytes = sizeof(int4) * rg.size();
     void *buf = nullptr;
-    HIP_OK(c, dalloc(c, &buf, bytes));
+    if (dalloc(c, &buf, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return SWE_OK;
+    }
     hipError_t e = hipMemcpyAsync(buf, base.desc, bytes, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(rg.data(), base.desc, bytes, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) {
@@ -2143,13 +2151,15 @@ int current_plan(swe_ctx *c, TilePlan **out)
 {
     *out = nullptr;
     if (!uses_plan(c)) return SWE_OK;
-    if (wants_deep(c)) {
+    const int tile = wanted_shape(c).tile;
+    if (wants_deep(c) && c->deep.tile >= 0) {
         const int rc = ensure_plan(c, kStepTile, out);
         if (rc != SWE_OK) return rc;
         const int rd = ensure_deep(c, **out);
         if (rd != SWE_OK || c->deep.tile > 0) return rd;
+        if (tile != kStepTile) release_plan(c, **out);
     }
-    return ensure_plan(c, wanted_shape(c).tile, out);
+    return ensure_plan(c, tile, out);
 }
 
 // Bytes of LDS of a launch over a plan.
@@ -3064,64 +3074,85 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     c->use_graphs = false;
     float best = 1e30f;
     int best_b = c->block, best_g = c->grid_persist, best_w = c->wide;
-    int rc = SWE_OK;
+    const int block0 = best_b, grid0 = best_g, wide0 = best_w;
     // only launch shapes of the configured kernel: they give bitwise the same
     // results (the tiled kernel is tiling-independent), the two kernels do not
     const bool euler = c->cfg.integrator == SWE_EULER;
     const bool cell = c->cfg.cell_kernel || (c->cfg.scheme == SWE_WAF && !euler);
     const bool tiled = uses_plan(c);
     const bool f64 = c->cfg.precision == SWE_F64;
-    for (int B : {0, 64, 128, 256, 512})  // 0: both stages in one launch
-    for (int W = 0; W < 2; ++W) {  // a thread per cell, or per edge
-        if (B == 512 && (!tiled || f64 || c->cfg.scheme == SWE_WAF)) continue;  // FP32 HLLC1 and MUSCL tiles only
-        if (W == 1 && (!tiled || B == 512)) continue;
-        if (B == 0 && W == 1) continue;
-        for (int persist = 0; persist < (B ? 2 : 1) && rc == SWE_OK; ++persist) {
+    // the plans of the shape that runs now and of the fastest one so far stay,
+    // the others go after their turn: at most one more is held at a time
+    TilePlan *plan0 = nullptr, *best_plan = nullptr;
+    int rc = current_plan(c, &plan0);
+    bool keep_deep = steps_deep(c);
+    const auto release_others = [&] {
+        for (TilePlan &p : c->plans)
+            if (p.tile > 0 && &p != plan0 && &p != best_plan) release_plan(c, p);
+        if (c->deep.tile > 0 && !keep_deep && !(best < 1e30f && best_b == 0)) release_plan(c, c->deep);
+    };
+    for (int B : {0, 64, 128, 256, 512}) {  // 0: both stages in one launch
+        for (int W = 0; W < 2 && rc == SWE_OK; ++W) {  // a thread per cell, or per edge
+            if (B == 512 && (!tiled || f64 || c->cfg.scheme == SWE_WAF)) continue;  // FP32 HLLC1 and MUSCL tiles only
+            if (W == 1 && (!tiled || B == 512)) continue;
+            if (B == 0 && W == 1) continue;
             c->block = B;
             c->wide = B ? W : -1;
-            c->grid_persist = -1;  // one tile per block
-            if (B == 0 && !wants_deep(c)) break;
+            if (B == 0 && !wants_deep(c)) continue;
+            // a shape whose tiles do not fit, or whose plan there is no memory for,
+            // is left out
             TilePlan *plan = nullptr;
-            rc = current_plan(c, &plan);
-            if (rc != SWE_OK) break;
-            if (B == 0 && !steps_deep(c)) break;
-            if (B && plan && plan->tile != B) continue;  // its tiles do not fit: a smaller size stands for it
-            if (persist) {
-                const Shape sh{B, W == 1};
-                const int threads = plan ? tile_threads(B, sh.wide) : B;
-                const size_t lds = !plan ? 0 : (f64 ? plan_lds<double>(c, B, plan->hs) : plan_lds<float>(c, B, plan->hs));
-                const void *k = f64 ? (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler)
-                                    : (const void *)pick_kernel<float>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler);
-                const int res = resident_blocks(c, k, threads, lds);
-                c->grid_persist = res > 0 ? res : ncu * (2048 / B);
+            const int prc = B && tiled ? ensure_plan(c, B, &plan, true) : current_plan(c, &plan);
+            if (prc == SWE_ERR_OOM) {
+                (void)hipGetLastError();
+                c->err.clear();
+                continue;
             }
-            (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
-            (void)hipMemcpyAsync(c->clock, saveK, clock_bytes(c), hipMemcpyDeviceToDevice, c->stream);
-            c->step_count = step0;
-            c->phi_stale = true;
-            rc = swe_step(c, 2, 0.0);  // warm-up
-            if (rc != SWE_OK) break;
-            rc = swe_step(c, n_steps, 0.0);
-            if (rc != SWE_OK) break;
-            float ms = 0.f;
-            rc = swe_last_step_ms(c, &ms);
-            if (rc == SWE_OK && ms < best) {
-                best = ms; best_b = B; best_g = c->grid_persist; best_w = c->wide;
+            rc = prc;
+            if (rc != SWE_OK || (B ? tiled && !plan : !steps_deep(c))) continue;
+            for (int persist = 0; persist < (B ? 2 : 1); ++persist) {
+                c->grid_persist = -1;  // one tile per block
+                if (persist) {
+                    const Shape sh{B, W == 1};
+                    const int threads = plan ? tile_threads(B, sh.wide) : B;
+                    const size_t lds = !plan ? 0 : (f64 ? plan_lds<double>(c, B, plan->hs) : plan_lds<float>(c, B, plan->hs));
+                    const void *k = f64 ? (const void *)pick_kernel<double>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler)
+                                        : (const void *)pick_kernel<float>(c->cfg.scheme, c->cfg.limiter, c->cfg.waf_limiter, sh, cell, euler);
+                    const int res = resident_blocks(c, k, threads, lds);
+                    c->grid_persist = res > 0 ? res : ncu * (2048 / B);
+                }
+                (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
+                (void)hipMemcpyAsync(c->clock, saveK, clock_bytes(c), hipMemcpyDeviceToDevice, c->stream);
+                c->step_count = step0;
+                c->phi_stale = true;
+                rc = swe_step(c, 2, 0.0);  // warm-up
+                if (rc != SWE_OK) break;
+                rc = swe_step(c, n_steps, 0.0);
+                if (rc != SWE_OK) break;
+                float ms = 0.f;
+                rc = swe_last_step_ms(c, &ms);
+                if (rc != SWE_OK) break;
+                if (ms < best) {
+                    best = ms; best_b = B; best_g = c->grid_persist; best_w = c->wide;
+                    best_plan = plan;
+                }
             }
         }
+        if (hipStreamSynchronize(c->stream) == hipSuccess) release_others();
     }
     c->use_graphs = graphs;
+    if (rc == SWE_OK && best < 1e30f) {
+        plan0 = nullptr;
+        keep_deep = false;
+    } else {  // nothing could be timed, or an error: as before
+        best_b = block0; best_g = grid0; best_w = wide0;
+        best_plan = nullptr;
+        best = 1e30f;
+    }
     c->block = best_b;
     c->grid_persist = best_g;
     c->wide = best_w;
-    {   // the other sizes' plans go
-        TilePlan *plan = nullptr;
-        const int prc = current_plan(c, &plan);
-        if (rc == SWE_OK) rc = prc;
-        for (TilePlan &p : c->plans)
-            if (&p != plan) release_plan(c, p);
-        if (!steps_deep(c)) release_plan(c, c->deep);
-    }
+    release_others();
     (void)hipMemcpyAsync(Ucur, saveU, bytes, hipMemcpyDeviceToDevice, c->stream);
     (void)hipMemcpyAsync(c->clock, saveK, clock_bytes(c), hipMemcpyDeviceToDevice, c->stream);
     (void)hipStreamSynchronize(c->stream);
@@ -3132,7 +3163,7 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     drop_graphs(c);
     if (rc != SWE_OK) return rc;
     c->tuned = true;
-    if (block_out) *block_out = best_b ? best_b : kStepTile;
+    if (block_out) *block_out = best_b ? best_b : (steps_deep(c) ? kStepTile : wanted_shape(c).tile);
     if (grid_out) *grid_out = best_g;
     return SWE_OK;
 }
