@@ -187,7 +187,8 @@ const char *swe_strerror(int code);
 /* Copy a mesh to the device: validation (counter-clockwise cells, symmetric
  * neighbours, ghost and send ranges in bounds), geometry (areas, normals,
  * lengths, inscribed radii, MUSCL distances) and the device layout.
- * Replaces any previous mesh; the state must be set again afterwards.
+ * Replaces any previous mesh; the state must be set again afterwards, and a
+ * launch shape that swe_autotune chose for the previous mesh is dropped.
  * SWE_ERR_MESH for a mesh without cells; SWE_ERR_UNSUPPORTED when a
  * per-cell array would exceed 4 GiB (more than about 89 million cells in
  * FP32, 44 million in FP64, per context).  Both size checks come before any

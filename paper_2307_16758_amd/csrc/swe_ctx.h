@@ -59,12 +59,12 @@ struct swe_ctx {
     std::vector<std::pair<std::vector<double>, std::vector<double>>> series;  // per scenario
     std::vector<double> h_ser_t, h_ser_q;
     std::vector<int> scen_off;  // first cell of each scenario, n_scen + 1 entries
-    // launch shape: threads per block and blocks of a persistent launch (0:
-    // one tile per block); picked by swe_autotune when tuned
+    // launch shape: by the configuration and the mesh's size, or what
+    // swe_autotune chose, until the next mesh.  grid_persist: blocks of a
+    // persistent launch (0 by size, -1 one tile per block)
     int grid_persist = 0;
     int wide = -1;  // tiled kernel: a thread per edge (1) or per cell (0), -1 by size
     int ncu = 0;    // compute units of the device
-    bool tuned = false;
     double computed_inflow_len = 0.0, given_inflow_len = 0.0;
     long long step_count = 0;  // steps since set_state (selects clock slots and buffers)
     int block = 0;  // cells per tile or threads per block; 0: by size

@@ -2636,6 +2636,10 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
         }
     }
     release_mesh(c);
+    // a shape that the autotuner chose was the previous mesh's
+    c->block = c->cfg.block;
+    c->wide = -1;
+    c->grid_persist = 0;
     c->n_total = off[nm];
     c->n_owned = nm == 1 ? m->n_owned : c->n_total;
     c->n_scen = nm;
@@ -2708,7 +2712,6 @@ int upload_meshes(swe_ctx *c, const swe_mesh *ms, int nm)
     if (rc != SWE_OK) return rc;
     c->has_mesh = true;
     c->has_state = false;
-    c->tuned = false;
     return SWE_OK;
 }
 
@@ -3162,7 +3165,6 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
     dfree(c, saveK);
     drop_graphs(c);
     if (rc != SWE_OK) return rc;
-    c->tuned = true;
     if (block_out) *block_out = best_b ? best_b : (steps_deep(c) ? kStepTile : wanted_shape(c).tile);
     if (grid_out) *grid_out = best_g;
     return SWE_OK;
