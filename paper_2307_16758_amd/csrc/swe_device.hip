@@ -1746,11 +1746,9 @@ __global__ void k_unpack_ghosts(int n_owned, int n_ghost, const T *buf, typename
 
 namespace {
 
-constexpr int kGraphSteps = 6;  // lcm of the clock-slot (3) and buffer (2) periods
-// Steps of the long graph: between two graphs the stream idles some 5 us,
-// as long as a step of a small mesh (200 steps of 16,000 cells 1267 us in
-// graphs of 24, 1376 in graphs of 6).
-constexpr int kLongSteps = 24;
+// Steps go in graphs of kGraphSteps and kLongSteps: between two graphs the
+// stream idles some 5 us, as long as a step of a small mesh (200 steps of
+// 16,000 cells 1267 us in graphs of 24, 1376 in graphs of 6).
 // Largest mesh stepped through graphs.  Its launches take about as long as
 // the host needs to queue one (4 us); above, queueing them one by one leaves
 // no gaps at all and no graph to build (12 steps of 250,000 cells, learned
@@ -3006,15 +3004,15 @@ int swe_step(swe_ctx *c, int n_steps, double dt_fixed)
     HIP_OK(c, hipEventRecord(c->ev0, c->stream));
     int done = 0;
     while (done < n_steps) {
-        const bool aligned = (c->step_count % kGraphSteps) == 0;
-        if (in_graphs(c) && aligned && n_steps - done >= kGraphSteps) {
-            // the long graph is built for a call that replays it at least twice
-            const int which = n_steps - done >= kLongSteps && (c->graphs[1] || n_steps >= 2 * kLongSteps);
+        const int k = in_graphs(c) ? steps_next(c->step_count, n_steps - done, n_steps, dt_fixed,
+                                                c->graphs[1] != nullptr, c->graph_dt)
+                                   : 1;
+        if (k > 1) {
+            const int which = k == kLongSteps;
             const int rc = ensure_graph(c, which, dt_fixed);
             if (rc != SWE_OK) return rc;
             HIP_OK(c, hipGraphLaunch(c->graphs[which], c->stream));
             c->phi_stale = false;  // the chunk's first step evaluates phi
-            const int k = which ? kLongSteps : kGraphSteps;
             c->step_count += k;
             done += k;
         } else {

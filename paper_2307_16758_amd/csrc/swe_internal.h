@@ -38,4 +38,17 @@ struct HostGeometry {
 // Validates the mesh and fills g.  Returns SWE_OK or SWE_ERR_MESH with msg.
 int prepare_geometry(const swe_mesh &m, int scenario, HostGeometry &g, std::string &msg);
 
+// Steps of the next piece of a run: of the short graph, of the long one, or
+// one.  left: steps still to take; asked: steps of the whole call, each of dt
+// (0: CFL); has_long: a long graph exists, of steps of long_dt.  The long graph
+// is built for a call that replays it at least twice.
+constexpr int kGraphSteps = 6;  // lcm of the clock-slot (3) and buffer (2) periods
+constexpr int kLongSteps = 24;
+inline int steps_next(long long step_count, int left, int asked, double dt, bool has_long, double long_dt)
+{
+    if (step_count % kGraphSteps != 0 || left < kGraphSteps) return 1;
+    if (left >= kLongSteps && ((has_long && long_dt == dt) || asked / 2 >= kLongSteps)) return kLongSteps;
+    return kGraphSteps;
+}
+
 }  // namespace swe
