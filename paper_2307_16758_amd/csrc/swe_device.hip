@@ -1049,7 +1049,9 @@ k_stage_tiled(StageArgs<T> args)
         // ---- 2: edges
         const int iend = kNet ? (nt + 63) & ~63 : nt;  // the network is evaluated by whole waves
         for (int i = cl; i < iend; i += NT) {
-            if (i >= NT) {
+            // (the lanes that only fill a wave for the network read nothing: the
+            // last tile's may be past the plan's end)
+            if (i >= NT && (!kNet || i < nt)) {
                 int j = i;
                 asm("" : "+v"(j));  // offsets from scalar bases, not three 64-bit pointers per lane
                 en = load_entry<MUSCL_>(ent, j);
