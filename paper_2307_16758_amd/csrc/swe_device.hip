@@ -1887,7 +1887,21 @@ struct Shape {
 // of about 65, 92, 130 and 185 cells (64 to 512 cells per tile; the 99th
 // percentile is 1.3 times that); the bounds keep the LDS of nine 256-cell
 // FP32 tiles within a compute unit.  Tiles of 64 cells have at most 576.
-inline int halo_bound(int tile) { return tile == 64 ? 576 : (tile == 128 ? 160 : (tile == 256 ? 208 : 320)); }
+//
+// loose: for a numbering of less locality (rows of a grid, one cell in twenty
+// far away), whose halos are over these bounds, before smaller tiles are
+// taken, whose halos are larger in all.  Per step in 64-cell tiles and so: 2.8M
+// cells with 5% far, MUSCL FP64 537 and 294 us, FP32 192 and 134, WAF 142 and
+// 80; in rows 361 and 354, 191 and 175, 104 and 93; random numberings take
+// 64-cell tiles either way.  The LDS stays under 64 KB; with the network in the
+// stage 256-cell FP64 tiles would not (80 KB).
+inline int halo_bound(const swe_ctx *c, int tile, bool loose)
+{
+    const bool net64 = c->tsize == 8 && c->cfg.limiter == SWE_LEARNED && c->cfg.phi_in_stage;
+    if (loose && tile == 128) return 352;
+    if (loose && tile == 256 && !net64) return 448;
+    return tile == 64 ? 576 : (tile == 128 ? 160 : (tile == 256 ? 208 : 320));
+}
 
 template <int TILE>
 void launch_plan(swe_ctx *c, int nt, int write, int hs, int es, void *desc, void *halo, void *ent)
@@ -1917,12 +1931,12 @@ template <typename T> void launch_plan_geometry(swe_ctx *c, const TilePlan &p)
 }
 
 // The ranges of cells that become tiles: `tile` cells each, a range whose
-// halo is over the bound cut in two until it is not (where the numbering
+// halo is over `bound` cut in two until it is not (where the numbering
 // jumps: the cells sent to several parts, ghost blocks).  More than an eighth
 // of the ranges cut says that the numbering has no locality at this size:
-// ok = false, and smaller tiles are taken.  rg: x first cell, y cells, z halo
+// ok = false, and a looser bound or smaller tiles are taken.  rg: x first cell, y cells, z halo
 // cells, w edges.
-int plan_ranges(swe_ctx *c, int tile, std::vector<int4> &rg, bool &ok)
+int plan_ranges(swe_ctx *c, int tile, int bound, std::vector<int4> &rg, bool &ok)
 {
     const int n = c->n_total;
     rg.clear();
@@ -1946,7 +1960,7 @@ int plan_ranges(swe_ctx *c, int tile, std::vector<int4> &rg, bool &ok)
         HIP_OK(c, es);
         next.clear();
         for (const int4 &r : todo) {
-            if (r.z <= halo_bound(tile)) { rg.push_back(r); continue; }
+            if (r.z <= bound) { rg.push_back(r); continue; }
             const int h = r.y / 2;
             next.push_back(make_int4(r.x, h, 0, 0));
             next.push_back(make_int4(r.x + h, r.y - h, 0, 0));
@@ -1987,7 +2001,9 @@ int ensure_plan(swe_ctx *c, int B, TilePlan **out, bool exact = false)
         if (p.tile < 0) continue;  // known not to fit
         std::vector<int4> rg;
         bool ok = false;
-        const int rc = plan_ranges(c, tile, rg, ok);
+        const int tight = halo_bound(c, tile, false), loose = halo_bound(c, tile, true);
+        int rc = plan_ranges(c, tile, tight, rg, ok);
+        if (rc == SWE_OK && !ok && loose > tight) rc = plan_ranges(c, tile, loose, rg, ok);
         if (rc != SWE_OK) return rc;
         if (!ok) p.tile = -1;  // 64-cell tiles always fit
         if (!ok && exact) return SWE_OK;
