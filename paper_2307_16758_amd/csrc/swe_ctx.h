@@ -24,12 +24,16 @@ struct TilePlan {
 };
 }  // namespace swe
 
+constexpr size_t kHostClock = 64, kHostBytes = 4096;
+
 struct swe_ctx {
     swe_config cfg{};
     int dev = 0;
     hipStream_t stream = nullptr;
     bool own_stream = true;  // false: borrowed from the caller (swe_config.stream)
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    // around the steps of a call: its start, its end without and with a fence,
+    // and the end that was recorded last
+    hipEvent_t ev0 = nullptr, ev1 = nullptr, ev1_fence = nullptr, last_end = nullptr;
     std::string err;
     bool has_mesh = false, has_state = false, ran = false;
     int n_owned = 0, n_total = 0, n_scen = 1, n_send = 0, n_ghost = 0;
@@ -52,7 +56,9 @@ struct swe_ctx {
     swe::TilePlan deep;      // of 64-cell tiles (tile -1: does not fit)
     int *health = nullptr, *flag = nullptr, *send_idx = nullptr;
     int *pk_off = nullptr, *pk_ent = nullptr;  // send entries per send cell (CSR)
-    int *host = nullptr;  // page-locked: call number of a refused state, health bits
+    // page-locked: call number of a refused state, health bits, and from
+    // kHostClock bytes on clock words that were asked for
+    int *host = nullptr;
     int calls = 1;        // number of the last state set (k_check_state); 0 and 1 are none's
     // host mirrors
     std::vector<swe::ScenParams> h_scen;

@@ -2456,11 +2456,23 @@ int launch_step_any(swe_ctx *c, long long step, double dt_fixed, bool phi_force 
 
 int health_result(swe_ctx *c, int bits);
 
+// Health of the run, after the work queued before: one wait (a copy and the
+// wait behind it, not a wait, a copy and another).
 int health_status(swe_ctx *c)
 {
     HIP_OK(c, hipMemcpyAsync(c->host + 1, c->health, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
     return health_result(c, c->host[1]);
+}
+
+// n words of the clock from `first` on, queued as a copy; where they will be
+// after the next wait.  n fits the page-locked words (one slot of any scenario).
+int queue_clock(swe_ctx *c, size_t first, size_t n, const ClockWord **at)
+{
+    ClockWord *p = (ClockWord *)((char *)c->host + kHostClock);
+    HIP_OK(c, hipMemcpyAsync(p, c->clock + first, sizeof(ClockWord) * n, hipMemcpyDeviceToHost, c->stream));
+    *at = p;
+    return SWE_OK;
 }
 
 int health_result(swe_ctx *c, int bits)
@@ -2543,13 +2555,12 @@ int swe_create(const swe_config *cfg, swe_ctx **out)
     if (!c->own_stream) c->stream = (hipStream_t)cfg->stream;
     if (hipSetDevice(c->dev) != hipSuccess ||
         (c->own_stream && hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) ||
-        // they only time the steps: without a fence a record costs the stream
-        // 3 us less (a step and its exchange on a 400k-cell part 44 instead of 47 us)
         hipEventCreateWithFlags(&c->ev0, hipEventDisableSystemFence) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev1, hipEventDisableSystemFence) != hipSuccess ||
+        hipEventCreate(&c->ev1_fence) != hipSuccess ||
         dalloc(c, (void **)&c->health, sizeof(int)) != hipSuccess ||
         dalloc(c, (void **)&c->flag, sizeof(int)) != hipSuccess ||
-        hipHostMalloc((void **)&c->host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&c->host, kHostBytes, hipHostMallocDefault) != hipSuccess ||
         hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->dev) != hipSuccess) {
         swe_destroy(c);
         return SWE_ERR_DEVICE;
@@ -2572,6 +2583,7 @@ void swe_destroy(swe_ctx *c)
     if (c->host) (void)hipHostFree(c->host);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
+    if (c->ev1_fence) (void)hipEventDestroy(c->ev1_fence);
     if (c->stream && c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -2774,9 +2786,9 @@ int swe_scenario_times(swe_ctx *c, double *t)
 {
     if (!c || !t) return set_err(c, SWE_ERR_ARG, "null");
     if (!c->has_state) return set_err(c, SWE_ERR_STATE, "no state");
-    HIP_OK(c, hipStreamSynchronize(c->stream));
     std::vector<ClockWord> k(clock_bytes(c) / sizeof(ClockWord));
-    HIP_OK(c, hipMemcpy(k.data(), c->clock, clock_bytes(c), hipMemcpyDeviceToHost));
+    HIP_OK(c, hipMemcpyAsync(k.data(), c->clock, clock_bytes(c), hipMemcpyDeviceToHost, c->stream));
+    HIP_OK(c, hipStreamSynchronize(c->stream));
     for (int s = 0; s < c->n_scen; ++s)
         std::memcpy(&t[s], &k[clock_off(c->ncopy, s, (int)(c->step_count % 3))], sizeof(double));
     return health_status(c);
@@ -2973,6 +2985,21 @@ static int ensure_graph(swe_ctx *c, int which, double dt_fixed)
 
 inline bool in_graphs(const swe_ctx *c) { return c->use_graphs && c->n_total <= kGraphCells; }
 
+// The event that ends a timed run of steps; neither it nor the one that starts
+// it needs a fence to time them.  Without one a record costs the stream 3 us less
+// (a step and its exchange on a 400k-cell part 44 instead of 47 us; a step and
+// swe_read_state of 16,000 cells 45.5 instead of 47.2), but a caller's own wait
+// right behind the step then needs a packet of its own: with the cell kernel
+// the end has a fence (one step of 6,402 cells and a wait for the device, WAF
+// RK2: 31 us, 34 without).
+static int record_end(swe_ctx *c)
+{
+    c->last_end = uses_plan(c) ? c->ev1 : c->ev1_fence;
+    HIP_OK(c, hipEventRecord(c->last_end, c->stream));
+    c->ran = true;
+    return SWE_OK;
+}
+
 static int step_ready(swe_ctx *c)
 {
     if (!c->has_state) return set_err(c, SWE_ERR_STATE, "no state");
@@ -3041,9 +3068,7 @@ int swe_step(swe_ctx *c, int n_steps, double dt_fixed)
             done += 1;
         }
     }
-    HIP_OK(c, hipEventRecord(c->ev1, c->stream));
-    c->ran = true;
-    return SWE_OK;
+    return record_end(c);
 }
 
 int swe_step_overlap(swe_ctx *c, double dt_fixed, void *dev_sendbuf, void *pack_done_event)
@@ -3063,9 +3088,7 @@ int swe_step_overlap(swe_ctx *c, double dt_fixed, void *dev_sendbuf, void *pack_
     c->phi_stale = false;
     if (pack_done_event) HIP_OK(c, hipEventRecord((hipEvent_t)pack_done_event, c->stream));
     c->step_count += 1;
-    HIP_OK(c, hipEventRecord(c->ev1, c->stream));
-    c->ran = true;
-    return SWE_OK;
+    return record_end(c);
 }
 
 int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
@@ -3189,15 +3212,17 @@ int swe_autotune(swe_ctx *c, int n_steps, int *block_out, int *grid_out)
 int swe_sync(swe_ctx *c)
 {
     if (!c) return SWE_ERR_ARG;
+    if (c->has_state) return health_status(c);
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    return c->has_state ? health_status(c) : SWE_OK;
+    return SWE_OK;
 }
 
 int swe_health(swe_ctx *c, int *bits)
 {
     if (!c || !bits) return set_err(c, SWE_ERR_ARG, "null");
+    HIP_OK(c, hipMemcpyAsync(c->host + 1, c->health, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    HIP_OK(c, hipMemcpy(bits, c->health, sizeof(int), hipMemcpyDeviceToHost));
+    *bits = c->host[1];
     return SWE_OK;
 }
 
@@ -3205,22 +3230,24 @@ int swe_time(swe_ctx *c, double *t)
 {
     if (!c || !t) return set_err(c, SWE_ERR_ARG, "null");
     if (!c->has_state) return set_err(c, SWE_ERR_STATE, "no state");
-    HIP_OK(c, hipStreamSynchronize(c->stream));
-    HIP_OK(c, hipMemcpy(t, c->clock + clock_off(c->ncopy, 0, (int)(c->step_count % 3)),
-                        sizeof(double), hipMemcpyDeviceToHost));
-    return health_status(c);
+    const ClockWord *k = nullptr;
+    int rc = queue_clock(c, clock_off(c->ncopy, 0, (int)(c->step_count % 3)), 1, &k);
+    if (rc != SWE_OK) return rc;
+    rc = health_status(c);
+    std::memcpy(t, k, sizeof(double));
+    return rc;
 }
 
 int swe_local_dt(swe_ctx *c, double *dt)
 {
     if (!c || !dt) return set_err(c, SWE_ERR_ARG, "null");
     if (!c->has_state) return set_err(c, SWE_ERR_STATE, "no state");
-    HIP_OK(c, hipStreamSynchronize(c->stream));
     // reduce the copies of scenario 0's current slot, as the kernels do
     const int nc = c->ncopy;
-    std::vector<ClockWord> k((size_t)(nc + 1) * kClockLine);
-    HIP_OK(c, hipMemcpy(k.data(), c->clock + clock_off(nc, 0, (int)(c->step_count % 3)),
-                        sizeof(ClockWord) * k.size(), hipMemcpyDeviceToHost));
+    const ClockWord *k = nullptr;
+    const int rc = queue_clock(c, clock_off(nc, 0, (int)(c->step_count % 3)), (size_t)(nc + 1) * kClockLine, &k);
+    if (rc != SWE_OK) return rc;
+    HIP_OK(c, hipStreamSynchronize(c->stream));
     ClockWord mnb = kInfBits, mxb = 0ull;
     for (int j = 0; j < nc; ++j) {
         const ClockWord *q = &k[(size_t)(1 + j) * kClockLine];
@@ -3289,8 +3316,8 @@ int swe_last_step_ms(swe_ctx *c, float *ms)
 {
     if (!c || !ms) return SWE_ERR_ARG;
     if (!c->ran) return set_err(c, SWE_ERR_STATE, "no step yet");
-    HIP_OK(c, hipEventSynchronize(c->ev1));
-    HIP_OK(c, hipEventElapsedTime(ms, c->ev0, c->ev1));
+    HIP_OK(c, hipEventSynchronize(c->last_end));
+    HIP_OK(c, hipEventElapsedTime(ms, c->ev0, c->last_end));
     return SWE_OK;
 }
 
