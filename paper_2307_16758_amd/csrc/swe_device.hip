@@ -806,14 +806,14 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<T> a)
 // side corrections and centred bed term become
 // g (h- + h)(eta- - eta) / 2; hllc_dev gives F1 - g h*^2 / 2 per side).
 //
-// What bounds it: on 13M cells HBM (268 us per stage launch; about 108 B per
-// cell at 5.2 TB/s, a large copy reaches 4.9), on a million cells, whose
-// arrays stay in the Infinity Cache, vector arithmetic and the launch's ends
-// (22 us).  The cell-by-cell form before the plan took 424 and 34 us: each
-// cell's neighbours gathered three times over and five dependent loads per
-// tile.  Edges do not branch on their own state (a wave of dry cells skips
-// the reconstruction as a whole): with divergent early exits 49 instead of
-// 44.6 us per step on a million cells, and 72 registers instead of 62.
+// What bounds it: on 13M cells HBM (265 us per stage launch; 110 B per cell at
+// 5.4 TB/s, a large copy reaches 4.9), on a million cells, whose arrays stay in
+// the Infinity Cache, vector arithmetic and the launch's ends (22 us).  The
+// cell-by-cell form before the plan took 424 and 34 us: each cell's neighbours
+// gathered three times over and five dependent loads per tile.  Edges do not
+// branch on their own state (a wave of dry cells skips the reconstruction as a
+// whole): with divergent early exits 49 instead of 44.6 us per step on a
+// million cells, and 72 registers instead of 62.
 // Learned limiter in the step's first stage: the tiled instance that also
 // evaluates the network and stores phi (the second stage reads it)
 constexpr int kLearnedNet = 5;
@@ -1752,10 +1752,13 @@ namespace {
 // stream idles some 5 us, as long as a step of a small mesh (200 steps of
 // 16,000 cells 1267 us in graphs of 24, 1376 in graphs of 6).
 // Largest mesh stepped through graphs.  Its launches take about as long as
-// the host needs to queue one (4 us); above, queueing them one by one leaves
+// the host needs to queue one (3 us); above, queueing them one by one leaves
 // no gaps at all and no graph to build (12 steps of 250,000 cells, learned
 // limiter: 447 us against 457; of a million cells 569 against 583; but 60
-// steps of 20,160 cells 776 against 730).
+// steps of 20,160 cells 776 against 730).  The price is the host's time per
+// step queued, hidden while one thread drives one GPU: at 250,000 cells first
+// order 3.0 us against 2.4 in graphs of 6, MUSCL-RK2 5.3 against 3.0, learned
+// 7.5 against 3.5, for kernels of 9, 20 and 33 us.
 constexpr int kGraphCells = 200000;
 
 int set_err(swe_ctx *c, int code, const std::string &m)
