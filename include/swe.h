@@ -317,7 +317,8 @@ int swe_unpack_ghosts(swe_ctx *ctx, const void *dev_recvbuf);
 int swe_ghost_sizes(const swe_ctx *ctx, int32_t *n_send, int32_t *n_ghost);
 
 /* Wall time of the kernels of the last swe_step call (ms, measured with HIP
- * events on the context stream; syncs). */
+ * events on the context stream; waits for their end, but is no fence for what
+ * a caller's own kernels wrote to host memory before them, as swe_sync is). */
 int swe_last_step_ms(swe_ctx *ctx, float *ms);
 
 /* ---- learned slope limiter (an addition of this library) ---------------

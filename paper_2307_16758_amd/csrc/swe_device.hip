@@ -2170,15 +2170,17 @@ int current_plan(swe_ctx *c, TilePlan **out)
 {
     *out = nullptr;
     if (!uses_plan(c)) return SWE_OK;
-    const int tile = wanted_shape(c).tile;
+    TilePlan *base = nullptr;
     if (wants_deep(c) && c->deep.tile >= 0) {
-        const int rc = ensure_plan(c, kStepTile, out);
+        const int rc = ensure_plan(c, kStepTile, &base);
         if (rc != SWE_OK) return rc;
-        const int rd = ensure_deep(c, **out);
+        const int rd = ensure_deep(c, *base);
+        *out = base;
         if (rd != SWE_OK || c->deep.tile > 0) return rd;
-        if (tile != kStepTile) release_plan(c, **out);
     }
-    return ensure_plan(c, tile, out);
+    const int rc = ensure_plan(c, wanted_shape(c).tile, out);
+    if (rc == SWE_OK && base && base != *out) release_plan(c, *base);  // the deep plan did not fit
+    return rc;
 }
 
 // Bytes of LDS of a launch over a plan.
